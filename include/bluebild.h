@@ -66,14 +66,18 @@ typedef enum {
   BB_ERR_STATE = 7        /* wrong object state (e.g. destroying a context with live handles) */
 } bb_status;
 
-/* Contraction arithmetic of the synthesis (FP64 phase arguments in every mode):
- *  BB_PREC_FP32     FP32 MFMA, four real products per complex product
- *  BB_PREC_BF16X3   BF16 hi/lo split of both operands, hi*hi + hi*lo + lo*hi in FP32 accumulators
- *  BB_PREC_FP32_3M  FP32 MFMA, three real products per complex product (Gauss):
+/* Contraction arithmetic of the synthesis (FP64 phase arguments and FP32
+ * accumulators in every mode).  Every operand value is split into two 16-bit
+ * words, hi + lo, and a real product is hi*hi + hi*lo + lo*hi on 16-bit MFMAs:
+ * fp16 words in the FP32 modes (22 bits, the eigenvectors scaled by powers of
+ * two; images at least as close to 64 bits as with FP32 MFMAs), bf16 words in
+ * the BF16 modes (16 bits).
+ *  BB_PREC_FP32     four real products per complex product
+ *  BB_PREC_BF16X3   four real products, BF16 words
+ *  BB_PREC_FP32_3M  three real products per complex product (Gauss):
  *                   conj(w) b = (k1 - k3) + j (k1 + k2), k1 = (wr - wi) br,
  *                   k2 = wr (bi - br), k3 = -wi (br + bi)
- *  BB_PREC_BF16X3_3M  the three-product form with BF16 hi/lo operands and three
- *                   compensating products each, FP32 accumulators */
+ *  BB_PREC_BF16X3_3M  three real products, BF16 words */
 typedef enum { BB_PREC_FP32 = 0, BB_PREC_BF16X3 = 1, BB_PREC_FP32_3M = 2, BB_PREC_BF16X3_3M = 3 } bb_precision;
 typedef enum { BB_FILTER_LSQ = 0, BB_FILTER_STD = 1 } bb_filter;
 

@@ -49,7 +49,8 @@ struct Layout {  // byte offsets into a handle's workspace
 size_t staging_bytes(int L_pad, int K_alloc, size_t* off_xs = nullptr, size_t* off_wts = nullptr,
                      size_t* off_levs = nullptr, size_t* off_kbr = nullptr, size_t* off_perm = nullptr) {
   size_t o = 0;
-  o += align_up((size_t)2 * K_alloc * 2 * L_pad * 4);  // apack (fp32; bf16 hi+lo has the same size)
+  // apack: at most three planes of hi + lo words, 12 bytes per (eigenpair, antenna), then wexp
+  o += align_up((size_t)16 * K_alloc * L_pad);
   if (off_xs) *off_xs = o;
   o += align_up((size_t)L_pad * 4 * 8);
   if (off_wts) *off_wts = o;
@@ -193,6 +194,7 @@ InstDesc staging_desc(bb_synth h, char* base, int L, int K, double wl, int slot)
   d.levs = reinterpret_cast<int*>(base + levs);
   d.kbr = reinterpret_cast<int2*>(base + kbr);
   d.perm = reinterpret_cast<int*>(base + perm);
+  d.wexp = reinterpret_cast<int*>(base + (size_t)12 * d.K_alloc * d.L_pad);
   (void)h;
   return d;
 }
@@ -208,11 +210,9 @@ bb_status launch_single(bb_context ctx, SingleMeta* meta, int* err, const InstDe
   int nt = 0;
   if (!bb::synth_tile_info(precision, tile, nullptr, &nt, nullptr))
     return fail(ctx, BB_ERR_INVALID_ARG, "unknown tile %d", tile);
-  InstDesc dd = d;
-  dd.rows16 = bb::synth_tile_rows(precision, tile) == 16 ? 1 : 0;  // operand order of the tile
-  hipLaunchKernelGGL(write_meta_kernel, dim3(1), dim3(1), 0, s, meta, dd, dd.slot);
+  hipLaunchKernelGGL(write_meta_kernel, dim3(1), dim3(1), 0, s, meta, d, d.slot);
   BB_HIP(ctx, hipGetLastError());
-  BB_HIP(ctx, bb::launch_stage(&meta->desc, &meta->dyn, 1, d.K_alloc, d.L_pad, n_levels, precision, err, s));
+  BB_HIP(ctx, bb::launch_stage(&meta->desc, &meta->dyn, 1, d.K_alloc, n_levels, precision, err, s));
   if (ev_staged) BB_HIP(ctx, hipEventRecord(ev_staged, s));
   bb::FwdParams p{};
   p.pix = pix;
@@ -226,6 +226,7 @@ bb_status launch_single(bb_context ctx, SingleMeta* meta, int* err, const InstDe
   p.img = images;
   p.img_ld = n_pix;
   p.n_levels = n_levels;
+  p.max_L_pad = d.L_pad;
   p.n_tiles = (n_pix + nt - 1) / nt;
   p.n_groups = 1;
   BB_HIP(ctx, bb::launch_synth_tile(p, precision, tile, s));
@@ -988,10 +989,9 @@ bb_status plan_batch(bb_synth h, int32_t n_inst, const bb_instance* inst, int64_
   return BB_OK;
 }
 
-// Descriptors of every instance of a planned batch, their staging regions in
-// `ws`, each staged in the operand order of its K class's tile in `tiles`.
+// Descriptors of every instance of a planned batch, their staging regions in `ws`.
 void batch_descs(bb_synth h, const bb_instance* inst, int32_t n_inst, int64_t n_ant_rows, const double* ant,
-                 const void* W, const float* d, const int32_t* lev, char* ws, const int* tiles, BatchPlan& bp) {
+                 const void* W, const float* d, const int32_t* lev, char* ws, BatchPlan& bp) {
   size_t stage = bp.off_stage;
   bp.descs.resize(n_inst);
   for (int i = 0; i < n_inst; ++i) {
@@ -1006,7 +1006,6 @@ void batch_descs(bb_synth h, const bb_instance* inst, int32_t n_inst, int64_t n_
     dd.wcol = nullptr;
     dd.d = d + b.eig_off;
     dd.lev_in = lev + b.eig_off;
-    dd.rows16 = bb::synth_tile_rows(h->opt.precision, tiles[bb::synth_k_class(dd.K_alloc)]) == 16 ? 1 : 0;
     bp.descs[i] = dd;
   }
 }
@@ -1046,6 +1045,7 @@ bb_status launch_buckets(bb_synth h, const BatchPlan& bp, char* ws, float* image
     p.img = images;
     p.img_ld = h->n_pix;
     p.n_levels = h->opt.n_levels;
+    p.max_L_pad = bp.max_L_pad;
     int nt = 0;
     if (!bb::synth_tile_info(h->opt.precision, bk.tile, nullptr, &nt, nullptr))
       return fail(ctx, BB_ERR_INVALID_ARG, "unknown tile %d", bk.tile);
@@ -1086,7 +1086,7 @@ bb_status bb_synth_collect_eig_batched(bb_synth h, int32_t n_inst, const bb_inst
   if (ws_bytes < bp.total) return fail(ctx, BB_ERR_WORKSPACE, "workspace %zu < required %zu", ws_bytes, bp.total);
   BB_HIP(ctx, hipSetDevice(ctx->device));
   char* ws = static_cast<char*>(workspace);
-  batch_descs(h, inst, n_inst, n_ant_rows, ant_xyz_packed, W_packed, d_packed, level_packed, ws, h->tiles, bp);
+  batch_descs(h, inst, n_inst, n_ant_rows, ant_xyz_packed, W_packed, d_packed, level_packed, ws, bp);
   hipStream_t s = ctx->stream;
   if (bb_host::debug_fill()) BB_HIP(ctx, bb::launch_fill_poison(ws, bp.total, s));
   BB_HIP(ctx, hipEventRecord(h->ev[0], s));
@@ -1094,7 +1094,7 @@ bb_status bb_synth_collect_eig_batched(bb_synth h, int32_t n_inst, const bb_inst
   st = upload_plan(ctx, bp, ws, n_inst, true);
   if (st != BB_OK) return st;
   BB_HIP(ctx, bb::launch_stage(reinterpret_cast<InstDesc*>(ws + bp.off_descs), reinterpret_cast<InstDyn*>(ws + bp.off_dyn),
-                               n_inst, bp.max_K_alloc, bp.max_L_pad, h->opt.n_levels, h->opt.precision,
+                               n_inst, bp.max_K_alloc, h->opt.n_levels, h->opt.precision,
                                at<int>(h, h->lay.err), s));
   BB_HIP(ctx, hipEventRecord(h->ev[2], s));
   st = launch_buckets(h, bp, ws, h->images);
@@ -1172,13 +1172,13 @@ bb_status bb_synth_autotune_batched(bb_synth h, int32_t n_inst, const bb_instanc
   BB_HIP(ctx, hipSetDevice(ctx->device));
   hipStream_t s = ctx->stream;
   char* ws = static_cast<char*>(workspace);
-  batch_descs(h, inst, n_inst, n_ant_rows, ant_xyz_packed, W_packed, d_packed, level_packed, ws, h->tiles, full);
+  batch_descs(h, inst, n_inst, n_ant_rows, ant_xyz_packed, W_packed, d_packed, level_packed, ws, full);
   if (bb_host::debug_fill()) BB_HIP(ctx, bb::launch_fill_poison(ws, full.total, s));
   st = upload_plan(ctx, full, ws, n_inst, true);
   if (st != BB_OK) return st;
   BB_HIP(ctx, bb::launch_stage(reinterpret_cast<InstDesc*>(ws + full.off_descs),
                                reinterpret_cast<InstDyn*>(ws + full.off_dyn), n_inst, full.max_K_alloc,
-                               full.max_L_pad, h->opt.n_levels, h->opt.precision, at<int>(h, h->lay.err), s));
+                               h->opt.n_levels, h->opt.precision, at<int>(h, h->lay.err), s));
   BB_HIP(ctx, bb::launch_fill_zero(scratch_images, (int64_t)h->opt.n_slots * h->opt.n_levels * h->n_pix, s));
   bool present[bb::kKClasses] = {false, false, false, false};
   for (int i = 0; i < n_inst; ++i) present[bb::synth_k_class(bb::round_up(inst[i].n_eig, 32))] = true;
@@ -1195,21 +1195,9 @@ bb_status bb_synth_autotune_batched(bb_synth h, int32_t n_inst, const bb_instanc
       BatchPlan bp;
       st = plan_batch(h, n_inst, inst, n_ant_rows, n_w_elems, n_eig_elems, tiles, c, bp);
       if (st != BB_OK) return st;
-      // restage this class's instances when the tile takes the other operand order
-      const int rows16 = bb::synth_tile_rows(h->opt.precision, t) == 16 ? 1 : 0;
-      bool restage = false;
-      for (int i = 0; i < n_inst; ++i)
-        if (bb::synth_k_class(full.descs[i].K_alloc) == c && full.descs[i].rows16 != rows16) {
-          full.descs[i].rows16 = rows16;
-          restage = true;
-        }
       bp.descs = full.descs;
-      st = upload_plan(ctx, bp, ws, n_inst, restage);
+      st = upload_plan(ctx, bp, ws, n_inst, false);
       if (st != BB_OK) return st;
-      if (restage)
-        BB_HIP(ctx, bb::launch_stage(reinterpret_cast<InstDesc*>(ws + full.off_descs),
-                                     reinterpret_cast<InstDyn*>(ws + full.off_dyn), n_inst, full.max_K_alloc,
-                                     full.max_L_pad, h->opt.n_levels, h->opt.precision, at<int>(h, h->lay.err), s));
       st = launch_buckets(h, bp, ws, scratch_images);  // warm-up
       if (st != BB_OK) return st;
       BB_HIP(ctx, hipEventRecord(h->ev[0], s));
@@ -1316,9 +1304,7 @@ bb_status bb_synth_eig_backward(bb_synth h, int32_t n_ant, int32_t n_eig, double
   BB_HIP(ctx, hipEventRecord(h->ev[1], s));
   hipLaunchKernelGGL(write_meta_kernel, dim3(1), dim3(1), 0, s, meta, dsc, 0);
   BB_HIP(ctx, hipGetLastError());
-  // three planes: the recompute of E runs the three-product FP32 form
-  BB_HIP(ctx, bb::launch_stage(&meta->desc, &meta->dyn, 1, dsc.K_alloc, dsc.L_pad, h->opt.n_levels, 2,
-                               at<int>(h, h->lay.err), s));
+  BB_HIP(ctx, bb::launch_stage_meta(&meta->desc, &meta->dyn, 1, h->opt.n_levels, false, at<int>(h, h->lay.err), s));
   BB_HIP(ctx, hipEventRecord(h->ev[2], s));
   bb::FwdParams p{};
   p.pix = h->pix;
@@ -1332,13 +1318,12 @@ bb_status bb_synth_eig_backward(bb_synth h, int32_t n_ant, int32_t n_eig, double
   p.img = nullptr;
   p.img_ld = h->n_pix;
   p.n_levels = h->opt.n_levels;
-  const int nt = bb::fields_tile_pixels(dsc.K_alloc);
-  p.n_tiles = (h->n_pix + nt - 1) / nt;
+  p.max_L_pad = dsc.L_pad;
   p.n_groups = 1;
   p.e_out = reinterpret_cast<float*>(ws + bp.off_E);
   p.e_ld = h->n_pix;
   p.e_rows = dsc.K_alloc;
-  BB_HIP(ctx, bb::launch_fields(p, dsc.K_alloc, s));
+  BB_HIP(ctx, bb::launch_fields(p, dsc.K_alloc, dsc.L_pad, s));
   bb::BwdParams b{};
   b.pix = h->pix;
   b.pix_ld = h->n_pix;

@@ -41,8 +41,6 @@ struct InstDesc {
   double scale;          // 1 / wavelength: positions in turns per unit direction
   int L, K, L_pad, K_alloc;
   int slot, W_c128;
-  int rows16;            // staged operand order: 1 = 16-row blocks (tiles on 16x16x4 MFMAs), 0 = 32-row
-  int pad1;
   // workspace regions owned by this instance
   void* apack;           // packed real-embedded W^H, MFMA operand order
   double* xs;            // [L_pad][4] scaled positions
@@ -51,11 +49,13 @@ struct InstDesc {
   int2* kbr;             // [K_alloc/32] (lowest, highest) level of each 32-block, then
                          // [K_alloc/16] the same for each 16-block
   int* perm;             // [K_alloc] source eigenpair of each sorted position (-1 = pad)
+  int* wexp;             // [K_alloc] binary exponent that undoes the staged column's scale
 };
 
 struct InstDyn {
   int K_pad;             // kept eigenpairs rounded up to 32
   int K_eff;
+  int fast_phase;        // positions small enough for the phases' fast form (phase_pair)
 };
 
 struct FwdParams {
@@ -71,6 +71,7 @@ struct FwdParams {
   float* img;              // [n_slots][n_levels][img_ld]
   int64_t img_ld;
   int n_levels;
+  int max_L_pad;           // largest padded antenna count of the launch's instances
   int64_t n_tiles;
   float* e_out;            // backward only: E planes [2][e_rows][e_ld]
   int64_t e_ld;
@@ -78,8 +79,15 @@ struct FwdParams {
 };
 
 // Staging (launchers in synth_kernels.hip).
-hipError_t launch_stage(const InstDesc* d_descs, InstDyn* d_dyn, int n_inst, int max_K_alloc, int max_L_pad,
-                        int n_levels, int precision, int* d_err, hipStream_t s);
+// launch_stage_meta: level order, weights and positions (relative to the first
+// antenna, or as they are); launch_stage: that and the packed operand of the
+// precision's synthesis kernel.
+hipError_t launch_stage_meta(const InstDesc* d_descs, InstDyn* d_dyn, int n_inst, int n_levels, bool relative,
+                             int* d_err, hipStream_t s);
+hipError_t launch_stage(const InstDesc* d_descs, InstDyn* d_dyn, int n_inst, int max_K_alloc, int n_levels,
+                        int precision, int* d_err, hipStream_t s);
+// Resident workgroups of a kernel with static LDS on the current device.
+int resident_blocks(const void* kernel, int threads);
 
 // Synthesis tiles.  K class of an instance: 0..3 for kept eigenpairs rounded
 // up to 32 of at most 32, 64, 128, or more.  Each precision has a list of
@@ -92,9 +100,6 @@ int synth_default_tile(int precision, int k_class);
 bool synth_tile_info(int precision, int id, int* kc, int* nt, int* waves);
 // Whether a class may use a tile (its eigenpairs per pass do not exceed the class's largest K).
 bool synth_tile_allowed(int precision, int id, int k_class);
-// Rows of a tile's eigenpair blocks (32, or 16 for tiles on 16x16x4 MFMAs); the
-// instances a tile runs must be staged in that order (InstDesc::rows16).
-int synth_tile_rows(int precision, int id);
 hipError_t launch_synth_tile(const FwdParams& p, int precision, int id, hipStream_t s);
 // The default tile for the largest K_alloc of the call.
 hipError_t launch_synth(const FwdParams& p, int max_K_alloc, int precision, int tile_pixels_out[1],
@@ -274,10 +279,9 @@ hipError_t launch_nufft_spread_tiles(const NufftGeom& g, const NufftInst* insts,
                                      int* nch, int* choff, float* grid, int64_t n_cell, hipStream_t s);
 
 // Backward.
-// E recompute (FP32 MFMA, three-product form, one instance staged as three
-// planes) into two planes [2][K_alloc][n_pix].
-hipError_t launch_fields(const FwdParams& p, int K_alloc, hipStream_t s);
-int fields_tile_pixels(int K_alloc);
+// E recompute (FP32 MFMA, three-product form; fields.hip) into two planes
+// [2][K_alloc][n_pix]; the instance's metadata staged (launch_stage_meta).
+hipError_t launch_fields(const FwdParams& p, int K_alloc, int L_pad, hipStream_t s);
 
 struct BwdParams {
   const double* pix; int64_t pix_ld; int64_t n_pix;

@@ -3,26 +3,47 @@
 // Per (time step, channel) instance the image of each energy level is
 //     I_l(p) += sum_{k in l} d_k |E_kp|^2,   E = W^H B,   B_lp = exp(+j 2 pi <x_l, p> / lambda_w)
 // (standard synthesis, Section 2.4; levels and filters, Section 2.6 and
-// Algorithm 1).  The complex product is done as a real GEMM on the embedding
-//     [Er; Ei] = [[Wr^T, Wi^T], [-Wi^T, Wr^T]] [Br; Bi]
-// with antennas interleaved (re, im) along the contraction axis.
+// Algorithm 1).
+//
+// The contraction runs on 16-bit MFMAs with FP32 accumulators: every operand
+// value is the sum of two 16-bit words, hi + lo, and a product is hi hi + hi lo
+// + lo hi.  With fp16 words (the FP32 modes; the columns of W scaled by powers
+// of two, the phases in [-sqrt 2, sqrt 2]) hi + lo holds 22 bits, the dropped
+// lo lo is below 2^-24 of the product, and one MFMA adds 32 products to an
+// accumulator where an FP32 one adds 2 or 4, so that fewer roundings meet the
+// running sum: against 64 bits the images are closer than with FP32 MFMAs
+// (relative error of all levels, measured: 512 antennas x 512 eigenpairs
+// 1.0e-7 against 1.2e-7 in the three-product form and 3.2e-7 against 5.0e-7 in
+// the four-product form at 65 km; 64 x 64 1.2e-7 against 1.7e-7), at 2.7 times
+// the products per second of the FP32 matrix rate.  With bf16 words (the BF16
+// modes) hi + lo holds 16 bits.
+//
+// The complex product takes four real products (planes Wr, Wi and Br, Bi) or,
+// with Gauss, three: conj(w) b = (k1 - k3) + j (k1 + k2), k1 = (wr - wi) br,
+// k2 = wr (bi - br), k3 = -wi (br + bi).
 //
 // Kernel structure (one workgroup = one pixel tile of one image slot):
 //   for each instance of the slot (its scaled positions copied to LDS once),
 //   for each K pass, for each 32-antenna chunk:
-//     MFMA: real-embedded W^H operand streamed from HBM/L2 in operand order
-//       and prefetched one MFMA group ahead, B operand from LDS, accumulators
-//       for [Er; Ei] in registers
-//     phase generation of the next chunk, a slice per MFMA group: FP64
-//       <x_l, p> in turns, exact FP64 reduction to [-1/2, 1/2], hardware FP32
-//       sin/cos in turns -> the other B buffer in LDS (double-buffered)
+//     MFMA (16x16x32): W^H operand from L2 in operand order, B operand from LDS,
+//       both read ahead of their use
+//     phase generation of the next chunk, a slice per MFMA step: FP64 <x_l, p>
+//       in turns modulo 1, hardware FP32 sin/cos in turns, the hi / lo split ->
+//       the other B buffer in LDS (double-buffered)
 //   epilogue of a pass: d_k (Er^2 + Ei^2) reduced over k in-lane, across the
-//     two half-waves, and into per-level partial sums in LDS
+//     four row groups, and into per-level partial sums in LDS
 //   end of the tile: sum over waves in a fixed order, one read-modify-write of
 //     the images (one writer per pixel and launch: deterministic, no atomics).
 // Neither B (L x N_pix) nor E (K x N_pix) is ever written to HBM.
-// synth_fwd16_kernel is the same structure for the three-product FP32 form on
-// 16-row eigenpair blocks (16x16x4 MFMAs), for instances with few eigenpairs.
+//
+// What bounds it: the card's power.  16-bit MFMAs on random data hold 2.4 GHz
+// only while the matrix pipes are partly idle: a loop of nothing but
+// 16x16x32 fp16 MFMAs reaches 1.75 PFLOP/s (32x32x16: 1.5, hence the smaller
+// MFMA), and 1.39 with the W loads, LDS reads and phase instructions of this
+// kernel beside them; a large fp16 matrix product of the vendor library
+// reaches 1.12.  512 antennas x 512 eigenpairs x 1024^2 pixels x 16 epochs:
+// 66.3 ms in the three-product form (1.19 PFLOP/s, 6.6e13 products/s) against
+// 197.8 ms on FP32 MFMAs (85 % of their peak).
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -32,6 +53,8 @@
 #include "bb_internal.h"
 
 namespace bb {
+
+constexpr size_t kMaxLds = 160 * 1024;  // LDS of a gfx950 compute unit
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -52,15 +75,29 @@ __device__ __forceinline__ const BB_GLOBAL T* as_global(const void* p) {
   return (const BB_GLOBAL T*)p;
 }
 
-// Phase of one (antenna, pixel) pair: xs = position / wavelength, so t is the
-// phase in turns.  The reduction t - rint(t) is exact in FP64 and leaves
-// f in [-1/2, 1/2]; gfx950's transcendental unit takes its sine and cosine
-// argument in turns (sin(2 pi f)), with an absolute error near 1.3e-7 there.
-// xs points into the workgroup's LDS copy of the instance's positions.
-__device__ __forceinline__ void phase_pair(const BB_LDS double* __restrict__ xs, double px, double py, double pz,
+// Phase of one (antenna, pixel) pair: xs = position / wavelength, so the phase
+// in turns is t = <xs, p>, needed modulo 1; gfx950's transcendental unit takes
+// its sine and cosine argument in turns (sin(2 pi f)), with an absolute error
+// near 1.3e-7 on [-1/2, 1/2].
+//
+// FAST: the FP64 multiply-adds start from kPhaseBias = 1.5 * 2^20, where FP64
+// has a spacing of 2^-32, so the low word of the sum is t modulo 1 in units of
+// 2^-32 (two's complement, so f in [-1/2, 1/2)), within three roundings of
+// 2^-33 turns, far below the 2^-26 of the conversion to FP32 that follows
+// either way.  It needs |t| < 2^19.  Otherwise t - rint(t), exact in FP64.
+constexpr double kPhaseBias = 0x1.8p20;
+constexpr double kPhaseFastMax = 0x1p19;  // largest sum of |xs| components for the fast form
+template <bool FAST>
+__device__ __forceinline__ void phase_pair(double x, double y, double z, double px, double py, double pz, double bias,
                                            float& c, float& s) {
-  const double t = fma(xs[2], pz, fma(xs[1], py, xs[0] * px));
-  const float f = (float)(t - rint(t));
+  float f;
+  if (FAST) {
+    const double t = fma(z, pz, fma(y, py, fma(x, px, bias)));
+    f = (float)(int)(uint32_t)__builtin_bit_cast(uint64_t, t) * 0x1p-32f;
+  } else {
+    const double t = fma(z, pz, fma(y, py, x * px));
+    f = (float)(t - rint(t));
+  }
   s = __builtin_amdgcn_sinf(f);
   c = __builtin_amdgcn_cosf(f);
 }
@@ -69,7 +106,7 @@ __device__ __forceinline__ void phase_pair(const BB_LDS double* __restrict__ xs,
 // Staging, part 1 (one workgroup per instance): sort eigenpairs by level
 // (stable, dropping level -1), scaled positions, per-32-block level ranges.
 __global__ __launch_bounds__(256) void stage_meta_kernel(const InstDesc* __restrict__ descs,
-                                                         InstDyn* __restrict__ dyn, int n_levels,
+                                                         InstDyn* __restrict__ dyn, int n_levels, bool relative,
                                                          int* __restrict__ err) {
   const InstDesc D = descs[blockIdx.x];
   __shared__ int s_lev[kMaxEig];
@@ -95,10 +132,8 @@ __global__ __launch_bounds__(256) void stage_meta_kernel(const InstDesc* __restr
       acc += s_cnt[l];
     }
     s_base[n_levels] = acc;
-    InstDyn o;
-    o.K_eff = acc;
-    o.K_pad = round_up(acc, 32);
-    dyn[blockIdx.x] = o;
+    dyn[blockIdx.x].K_eff = acc;
+    dyn[blockIdx.x].K_pad = round_up(acc, 32);
   }
   __syncthreads();
   const int K_eff = s_base[n_levels];
@@ -138,18 +173,30 @@ __global__ __launch_bounds__(256) void stage_meta_kernel(const InstDesc* __restr
     }
     D.kbr[i] = make_int2(lo, hi);
   }
+  // positions relative to the first antenna (a common shift multiplies every
+  // E_kp of a pixel by one phase factor, which |E|^2 does not see)
+  double r0 = 0.0, r1 = 0.0, r2 = 0.0;
+  if (relative) {
+    r0 = D.ant[0];
+    r1 = D.ant[D.ant_ld];
+    r2 = D.ant[2 * D.ant_ld];
+  }
+  bool near = true;
   for (int l = tid; l < D.L_pad; l += blockDim.x) {
     double v0 = 0.0, v1 = 0.0, v2 = 0.0;
     if (l < D.L) {
-      v0 = D.ant[l] * D.scale;
-      v1 = D.ant[l + D.ant_ld] * D.scale;
-      v2 = D.ant[l + 2 * D.ant_ld] * D.scale;
+      v0 = (D.ant[l] - r0) * D.scale;
+      v1 = (D.ant[l + D.ant_ld] - r1) * D.scale;
+      v2 = (D.ant[l + 2 * D.ant_ld] - r2) * D.scale;
     }
     D.xs[4 * l + 0] = v0;
     D.xs[4 * l + 1] = v1;
     D.xs[4 * l + 2] = v2;
     D.xs[4 * l + 3] = 0.0;
+    near = near && fabs(v0) + fabs(v1) + fabs(v2) < 0.999 * kPhaseFastMax;  // false for NaN
   }
+  near = __syncthreads_and(near);
+  if (tid == 0) dyn[blockIdx.x].fast_phase = near;
 }
 
 __device__ __forceinline__ void load_w(const InstDesc& D, int l, int col, float& wr, float& wi) {
@@ -164,498 +211,338 @@ __device__ __forceinline__ void load_w(const InstDesc& D, int l, int col, float&
   }
 }
 
-// Staging, part 2, FP32: one float4 = 4 consecutive antennas of one lane of
-// one MFMA A-operand fragment (32x32x2: lane = row + 32 * (re/im)).
-__global__ __launch_bounds__(256) void stage_pack_f32_kernel(const InstDesc* __restrict__ descs) {
+// Staging, part 2 (one workgroup per (32 eigenpairs, instance)): the W^H
+// operand in MFMA order, each value split into two 16-bit words hi + lo.
+//
+// An eigenpair's column is first scaled by a power of two of its own: its
+// largest component lands in [2^13, 2^14), so that hi and lo of every value
+// down to 2^-27 of the largest hold 22 bits (fp16 has 11, and the split rounds
+// to nearest twice), and smaller ones are within 2^-39 of the largest.  The
+// scaling is exact and undone in the epilogue (D.wexp).  BF16 words have
+// FP32's range and take no scale (exponent 0).
+//
+// Planes: NPL = 2 (four real products): Wr, Wi; NPL = 3 (Gauss, conj(w) b =
+// (k1 - k3) + j (k1 + k2)): Wr - Wi, Wr, -Wi.  Vectors of 8 antennas, ordered
+// (16-eigenpair block, 32-antenna step, plane, hi / lo, lane): lane = row +
+// 16 kk holds antennas 32 step + 8 kk + e, the operand of one 16x16x32 MFMA.
+template <class H, int NPL>
+__global__ __launch_bounds__(512) void stage_pack_kernel(const InstDesc* __restrict__ descs) {
+  typedef H h8 __attribute__((ext_vector_type(8)));
   const InstDesc D = descs[blockIdx.y];
-  const int G4 = D.L_pad / 4;
-  const int64_t total = (int64_t)(D.K_alloc / 32) * 2 * G4 * 64;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int lane = (int)(idx % 64);
-  int64_t rest = idx / 64;
-  const int g = (int)(rest % G4);
-  rest /= G4;
-  const int ri = (int)(rest % 2);
-  const int kb = (int)(rest / 2);
-  const int k = kb * 32 + (lane & 31);
-  const int h = lane >> 5;
+  if ((int)blockIdx.x * 32 >= D.K_alloc) return;
+  constexpr bool kScaled = std::is_same<H, _Float16>::value;
+  __shared__ float s_max[16][32];
+  const int tid = threadIdx.x;
+  // thread = (part of the antennas, eigenpair), the eigenpair's row in its
+  // 16-block in the low four bits so that it is also an operand lane
+  const int col32 = (tid & 15) + 16 * (tid >> 8);
+  const int k = blockIdx.x * 32 + col32;
   const int src = D.perm[k];
-  f32x4 out;
-  for (int s = 0; s < 4; ++s) {
-    const int l = 4 * g + s;
-    float wr = 0.0f, wi = 0.0f;
-    if (src >= 0 && l < D.L) load_w(D, l, D.wcol ? D.wcol[src] : src, wr, wi);
-    // Er row: (Wr, Wi) pairs with (Br, Bi); Ei row: (-Wi, Wr)
-    out[s] = ri == 0 ? (h == 0 ? wr : wi) : (h == 0 ? -wi : wr);
-  }
-  ((f32x4*)D.apack)[idx] = out;
-}
-
-// Staging, part 2, BF16 x3: hi = bf16(a), lo = bf16(a - hi) of the real
-// embedding, 8 contraction rows per lane (32x32x16: lane = row + 32 * (k / 8)).
-__global__ __launch_bounds__(256) void stage_pack_bf16_kernel(const InstDesc* __restrict__ descs) {
-  const InstDesc D = descs[blockIdx.y];
-  const int G8 = D.L_pad / 8;
-  const int64_t total = (int64_t)(D.K_alloc / 32) * 2 * G8 * 64;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int lane = (int)(idx % 64);
-  int64_t rest = idx / 64;
-  const int g = (int)(rest % G8);
-  rest /= G8;
-  const int ri = (int)(rest % 2);
-  const int kb = (int)(rest / 2);
-  const int k = kb * 32 + (lane & 31);
-  const int h = lane >> 5;
-  const int src = D.perm[k];
-  bf16x8 hi, lo;
-  for (int a = 0; a < 4; ++a) {
-    const int l = 8 * g + 4 * h + a;
-    float wr = 0.0f, wi = 0.0f;
-    if (src >= 0 && l < D.L) load_w(D, l, D.wcol ? D.wcol[src] : src, wr, wi);
-    const float v0 = ri == 0 ? wr : -wi;  // multiplies Br
-    const float v1 = ri == 0 ? wi : wr;   // multiplies Bi
-    const __bf16 h0 = (__bf16)v0, h1 = (__bf16)v1;
-    hi[2 * a] = h0;
-    hi[2 * a + 1] = h1;
-    lo[2 * a] = (__bf16)(v0 - (float)h0);
-    lo[2 * a + 1] = (__bf16)(v1 - (float)h1);
-  }
-  const int64_t base = (((int64_t)(kb * 2 + ri) * G8 + g) * 2) * 64 + lane;
-  ((bf16x8*)D.apack)[base] = hi;
-  ((bf16x8*)D.apack)[base + 64] = lo;
-}
-
-// Staging, part 2, FP32 with three real products per complex product (Gauss):
-// conj(W) B = (k1 - k3) + j (k1 + k2) with k1 = (Wr - Wi) Br, k2 = Wr (Bi - Br),
-// k3 = -Wi (Br + Bi).  Three planes (Wr - Wi, Wr, -Wi), 12 bytes per
-// (eigenpair, antenna) in either operand order:
-//  - 32-row blocks (32x32x2 operands, the two contraction rows of an MFMA step
-//    being two antennas): lane = row + 32 * (antenna parity), float4 = 4 steps
-//    = 8 antennas, vectors ordered (32-block, plane, 8-antenna group, lane);
-//  - 16-row blocks (16x16x4 operands, four antennas per step): lane = row +
-//    16 * (antenna mod 4), float2 = 2 steps = 8 antennas, vectors ordered
-//    (16-block, 8-antenna group, plane, lane).
-__global__ __launch_bounds__(256) void stage_pack_f32g_kernel(const InstDesc* __restrict__ descs) {
-  const InstDesc D = descs[blockIdx.y];
-  const int64_t total = (int64_t)D.K_alloc * 3 * D.L_pad / 4;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int lane = (int)(idx % 64);
-  int64_t rest = idx / 64;
-  if (D.rows16) {  // two float2 vectors: 8-antenna groups 2 gg and 2 gg + 1
-    const int q = (int)(rest % 3);
-    rest /= 3;
-    const int G16 = D.L_pad / 16;
-    const int gg = (int)(rest % G16);
-    const int blk = (int)(rest / G16);
-    const int k = blk * 16 + (lane & 15);
-    const int src = D.perm[k];
-    for (int h = 0; h < 2; ++h) {
-      const int g8 = 2 * gg + h;
-      f32x2 out;
-      for (int s = 0; s < 2; ++s) {
-        const int l = 8 * g8 + 4 * s + (lane >> 4);
-        float wr = 0.0f, wi = 0.0f;
-        if (src >= 0 && l < D.L) load_w(D, l, D.wcol ? D.wcol[src] : src, wr, wi);
-        out[s] = q == 0 ? wr - wi : (q == 1 ? wr : -wi);
+  const int col = src < 0 ? -1 : (D.wcol ? D.wcol[src] : src);
+  const int part = (tid >> 4) & 15;
+  int ex = 0;
+  if (kScaled) {
+    float m = 0.0f;
+    if (col >= 0)
+      for (int l = part; l < D.L; l += 16) {
+        float wr, wi;
+        load_w(D, l, col, wr, wi);
+        const float a = fmaxf(fabsf(wr), fabsf(wi));
+        if (a <= 3.4028235e38f) m = fmaxf(m, a);  // the largest finite component
       }
-      ((f32x2*)D.apack)[(((int64_t)blk * (D.L_pad / 8) + g8) * 3 + q) * 64 + lane] = out;
+    s_max[part][col32] = m;
+    __syncthreads();
+    for (int i = 0; i < 16; ++i) m = fmaxf(m, s_max[i][col32]);
+    if (m > 0.0f) {
+      (void)frexpf(m, &ex);  // m < 2^ex
+      ex = 14 - ex;
     }
-    return;
   }
-  const int G8 = D.L_pad / 8;
-  const int g = (int)(rest % G8);
-  rest /= G8;
-  const int q = (int)(rest % 3);
-  const int kb = (int)(rest / 3);
-  const int k = kb * 32 + (lane & 31);
-  const int src = D.perm[k];
-  f32x4 out;
-  for (int s = 0; s < 4; ++s) {
-    const int l = 8 * g + 2 * s + (lane >> 5);
-    float wr = 0.0f, wi = 0.0f;
-    if (src >= 0 && l < D.L) load_w(D, l, D.wcol ? D.wcol[src] : src, wr, wi);
-    out[s] = q == 0 ? wr - wi : (q == 1 ? wr : -wi);
+  if (part == 0) D.wexp[k] = -ex;
+  const int steps = D.L_pad / 32;
+  const int lane = tid & 63;
+  h8* const out = (h8*)D.apack + (int64_t)(k >> 4) * steps * NPL * 128;
+  for (int st = (tid >> 6) & 3; st < steps; st += 4) {
+    h8 hi[NPL], lo[NPL];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int l = 32 * st + 8 * (lane >> 4) + e;
+      float wr = 0.0f, wi = 0.0f;
+      if (col >= 0 && l < D.L) load_w(D, l, col, wr, wi);
+      if (kScaled) {
+        wr = ldexpf(wr, ex);
+        wi = ldexpf(wi, ex);
+      }
+#pragma unroll
+      for (int q = 0; q < NPL; ++q) {
+        const float v = NPL == 2 ? (q == 0 ? wr : wi) : (q == 0 ? wr - wi : (q == 1 ? wr : -wi));
+        const H vh = (H)v;
+        hi[q][e] = vh;
+        lo[q][e] = (H)(v - (float)vh);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < NPL; ++q) {
+      out[(st * NPL + q) * 128 + lane] = hi[q];
+      out[(st * NPL + q) * 128 + 64 + lane] = lo[q];
+    }
   }
-  ((f32x4*)D.apack)[idx] = out;
 }
 
-// Staging, part 2, BF16 x3 with three real products per complex product: the
-// three planes of the FP32 three-product form, each split hi = bf16(a),
-// lo = bf16(a - hi); 32x32x16 operand order with the 16 contraction rows of an
-// MFMA step being 16 antennas: lane = row + 32 * (antenna / 8), 8 antennas per lane.
-__global__ __launch_bounds__(256) void stage_pack_bf16g_kernel(const InstDesc* __restrict__ descs) {
-  const InstDesc D = descs[blockIdx.y];
-  const int G16 = D.L_pad / 16;
-  const int64_t total = (int64_t)(D.K_alloc / 32) * 3 * G16 * 64;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int lane = (int)(idx % 64);
-  int64_t rest = idx / 64;
-  const int g = (int)(rest % G16);
-  rest /= G16;
-  const int q = (int)(rest % 3);
-  const int kb = (int)(rest / 3);
-  const int k = kb * 32 + (lane & 31);
-  const int h = lane >> 5;
-  const int src = D.perm[k];
-  bf16x8 hi, lo;
-  for (int e = 0; e < 8; ++e) {
-    const int l = 16 * g + 8 * h + e;
-    float wr = 0.0f, wi = 0.0f;
-    if (src >= 0 && l < D.L) load_w(D, l, D.wcol ? D.wcol[src] : src, wr, wi);
-    const float v = q == 0 ? wr - wi : (q == 1 ? wr : -wi);
-    const __bf16 vh = (__bf16)v;
-    hi[e] = vh;
-    lo[e] = (__bf16)(v - (float)vh);
-  }
-  const int64_t base = (((int64_t)(kb * 3 + q) * G16 + g) * 2) * 64 + lane;
-  ((bf16x8*)D.apack)[base] = hi;
-  ((bf16x8*)D.apack)[base + 64] = lo;
-}
-
-hipError_t launch_stage(const InstDesc* d_descs, InstDyn* d_dyn, int n_inst, int max_K_alloc, int max_L_pad,
-                        int n_levels, int precision, int* d_err, hipStream_t s) {
+hipError_t launch_stage_meta(const InstDesc* d_descs, InstDyn* d_dyn, int n_inst, int n_levels, bool relative,
+                             int* d_err, hipStream_t s) {
   if (n_inst <= 0) return hipSuccess;
-  hipLaunchKernelGGL(stage_meta_kernel, dim3(n_inst), dim3(256), 0, s, d_descs, d_dyn, n_levels, d_err);
-  hipError_t e = hipGetLastError();
+  hipLaunchKernelGGL(stage_meta_kernel, dim3(n_inst), dim3(256), 0, s, d_descs, d_dyn, n_levels, relative, d_err);
+  return hipGetLastError();
+}
+
+hipError_t launch_stage(const InstDesc* d_descs, InstDyn* d_dyn, int n_inst, int max_K_alloc, int n_levels,
+                        int precision, int* d_err, hipStream_t s) {
+  if (n_inst <= 0) return hipSuccess;
+  const hipError_t e = launch_stage_meta(d_descs, d_dyn, n_inst, n_levels, true, d_err, s);
   if (e != hipSuccess) return e;
-  int64_t per = (int64_t)(max_K_alloc / 32) * 2 * (max_L_pad / 4) * 64;
-  if (precision == 1) per = (int64_t)(max_K_alloc / 32) * 2 * (max_L_pad / 8) * 64;
-  if (precision == 2) per = (int64_t)(max_K_alloc / 32) * 3 * (max_L_pad / 8) * 64;
-  if (precision == 3) per = (int64_t)(max_K_alloc / 32) * 3 * (max_L_pad / 16) * 64;
-  const unsigned gx = (unsigned)((per + 255) / 256);
-  if (precision == 3)
-    hipLaunchKernelGGL(stage_pack_bf16g_kernel, dim3(gx, n_inst), dim3(256), 0, s, d_descs);
-  else if (precision == 1)
-    hipLaunchKernelGGL(stage_pack_bf16_kernel, dim3(gx, n_inst), dim3(256), 0, s, d_descs);
-  else if (precision == 2)
-    hipLaunchKernelGGL(stage_pack_f32g_kernel, dim3(gx, n_inst), dim3(256), 0, s, d_descs);
-  else
-    hipLaunchKernelGGL(stage_pack_f32_kernel, dim3(gx, n_inst), dim3(256), 0, s, d_descs);
+  const dim3 grid(max_K_alloc / 32, n_inst), block(512);
+  switch (precision) {
+    case 1: hipLaunchKernelGGL((stage_pack_kernel<__bf16, 2>), grid, block, 0, s, d_descs); break;
+    case 2: hipLaunchKernelGGL((stage_pack_kernel<_Float16, 3>), grid, block, 0, s, d_descs); break;
+    case 3: hipLaunchKernelGGL((stage_pack_kernel<__bf16, 3>), grid, block, 0, s, d_descs); break;
+    default: hipLaunchKernelGGL((stage_pack_kernel<_Float16, 2>), grid, block, 0, s, d_descs); break;
+  }
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
 // Synthesis kernel.
-//   PREC:    0 = FP32, four real products per complex product (accumulators Er, Ei)
-//            1 = BF16 x3 (hi/lo split, three bf16 MFMAs per real product; Er, Ei)
-//            2 = FP32, three real products (Gauss; accumulators k1, k2, k3)
-//            3 = BF16 x3 of the three-product form (k1, k2, k3)
-//   MB x NB: 32x32 output blocks per wave (k-blocks x pixel blocks);
-//   WK x WN: waves along k and along pixels.
-template <int MB, int NB, int WK, int WN>
-struct TileCfg {
-  static constexpr int ROWS = 32;
+//   H, NPL: 16-bit type of the split operands and planes of the complex product
+//           (2: four real products, accumulators Er, Ei; 3: Gauss, k1, k2, k3)
+//   MR x NP: 16x16 output blocks per wave (eigenpair blocks x pixel blocks);
+//   WK x WN: waves along eigenpairs and along pixels.
+template <int MR_, int NP_, int WK_, int WN_, int OCC_ = 2>
+struct Tile {
+  static constexpr int MR = MR_, NP = NP_, WK = WK_, WN = WN_;
+  static constexpr int OCC = OCC_;             // waves per SIMD the register budget allows (512 / OCC registers each)
   static constexpr int WAVES = WK * WN;
   static constexpr int THREADS = 64 * WAVES;
-  static constexpr int KC = 32 * MB * WK;      // eigenpairs per pass
-  static constexpr int NT = 32 * NB * WN;      // pixels per tile
-  static constexpr int NCB = NT / 32;
-  static constexpr int LCH = NT <= 128 ? 32 : 16;  // antennas per LDS chunk
-  static constexpr int G4 = LCH / 4;
-  static constexpr int G8 = LCH / 8;
-  static constexpr int G16 = LCH / 16;
-  static constexpr int CHUNK_VEC = LCH * NT / 2;   // 16-byte vectors per chunk buffer
-  static constexpr int TASKS = NT * G4;           // (pixel, 4-antenna) phase tasks per chunk
-  static constexpr int JT = (TASKS + THREADS - 1) / THREADS;
+  static constexpr int KC = 16 * MR * WK;      // eigenpairs per pass
+  static constexpr int NT = 16 * NP * WN;      // pixels per tile
+  static constexpr int NPB = NT / 16;          // 16-pixel blocks per tile
+  static constexpr int LCH = 32;               // antennas per LDS chunk: one MFMA step
+  static constexpr int JT = NT * 8 / THREADS;  // (pixel, 4-antenna) phase tasks per thread and chunk
   static_assert(THREADS % NT == 0, "a thread keeps one pixel");
-  static_assert(TASKS % THREADS == 0, "task split");
+  static_assert(NT % 64 == 0, "a wave keeps one antenna group per task");
+  static_assert(JT >= 1 && NT * 8 % THREADS == 0, "whole tasks per thread");
   static_assert(kAntChunk % LCH == 0, "antenna padding covers the chunk");
-};
-
-template <int PREC>
-struct Acc {
-  static constexpr int N = PREC >= 2 ? 3 : 2;  // accumulator tiles per output block
-};
-
-template <class C, int PREC>
-struct ChunkVec {  // 16-byte vectors per LDS phase chunk
-  static constexpr int N = PREC >= 2 ? 3 * C::LCH * C::NT / 4 : C::CHUNK_VEC;
-};
-
-// A thread's share of a phase chunk: JT tasks of 4 (antenna, pixel) pairs, one
-// pixel per task.  The pairs of a task are laid out so that each task fills
-// whole 16-byte vectors of the chunk's MFMA operand layout.
-template <class C>
-__device__ __forceinline__ int gen_group(int tid, int j) {  // antenna group of task j
-  const int t = tid + j * C::THREADS;
-  // wave-uniform when a wave's 64 lanes share one antenna group
-  return C::NT % 64 == 0 ? __builtin_amdgcn_readfirstlane(t / C::NT) : t / C::NT;
-}
-
-// Antenna (within the chunk) of pair s of a task in antenna group g4.
-template <int PREC>
-__device__ __forceinline__ int gen_antenna(int g4, int s) {
-  if (PREC == 3) {
-    // lane (h, jj) of a plane holds antennas 16 g16 + 8 h + e, e = 0..7; a task
-    // fills e = 4 half .. 4 half + 3 (8 bytes of each 16-byte operand)
-    const int g16 = g4 >> 2, h = (g4 >> 1) & 1, half = g4 & 1;
-    return 16 * g16 + 8 * h + 4 * half + s;
+  // LDS of a workgroup: two phase chunks, the positions of the largest instance
+  // and each k-wave's level partials, sized by the launch so that small problems
+  // leave room for a second workgroup on the CU.
+  static constexpr size_t buf_bytes(int npl) { return (size_t)npl * NPB * 256 * sizeof(uint2); }
+  static size_t lds_bytes(int npl, int max_L_pad, int n_part_levels) {
+    return 2 * buf_bytes(npl) + (size_t)max_L_pad * 32 + (size_t)WK * n_part_levels * NT * sizeof(float);
   }
-  if (PREC == 2) return 8 * (g4 >> 1) + 2 * s + (g4 & 1);  // one lane of each of the three B planes
-  return 4 * g4 + s;
+};
+
+template <class H>
+struct Mma;
+template <>
+struct Mma<_Float16> {
+  typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+  static __device__ __forceinline__ f32x4 op(h8 a, h8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+  }
+};
+template <>
+struct Mma<__bf16> {
+  typedef __bf16 h8 __attribute__((ext_vector_type(8)));
+  static __device__ __forceinline__ f32x4 op(h8 a, h8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+  }
+};
+
+// Task j of a thread: its pixel and the antennas 4 Q .. 4 Q + 3 of the chunk
+// (Q wave-uniform: a wave's 64 lanes share one group).
+template <class C>
+__device__ __forceinline__ int gen_group(int tid, int j) {
+  return __builtin_amdgcn_readfirstlane((tid + j * C::THREADS) / C::NT);
 }
 
-// Phase pairs first .. first + count - 1 (pair q = pair q % 4 of task q / 4) of
-// this thread's share of a chunk, into registers.
-template <class C, int PREC>
-__device__ __forceinline__ void gen_pairs(float (&cr)[4 * C::JT], float (&ci)[4 * C::JT],
-                                          const BB_LDS double* __restrict__ xs_chunk, double px, double py,
-                                          double pz, int tid, int first, int count) {
+// A thread's phases of one chunk: P pairs (pair q = antenna q % 4 of task q / 4),
+// the positions read from LDS ahead of each pair's arithmetic.
+template <class C>
+struct Phases {
+  static constexpr int P = 4 * C::JT;
+  float cr[P], ci[P];
+  double x[P][3];
+  __device__ __forceinline__ void read(const BB_LDS double* __restrict__ xs_chunk, int tid, int q) {
+    const BB_LDS double* const at = xs_chunk + 4 * (4 * gen_group<C>(tid, q >> 2) + (q & 3));
 #pragma unroll
-  for (int q = 0; q < 4 * C::JT; ++q)
-    if (q >= first && q < first + count)
-      phase_pair(xs_chunk + 4 * gen_antenna<PREC>(gen_group<C>(tid, q >> 2), q & 3), px, py, pz, cr[q], ci[q]);
+    for (int a = 0; a < 3; ++a) x[q][a] = at[a];
+  }
+  template <bool FAST>
+  __device__ __forceinline__ void pair(double px, double py, double pz, double bias, int q) {
+    phase_pair<FAST>(x[q][0], x[q][1], x[q][2], px, py, pz, bias, cr[q], ci[q]);
+  }
+  template <bool FAST>
+  __device__ __forceinline__ void all(const BB_LDS double* __restrict__ xs_chunk, double px, double py, double pz,
+                                      double bias, int tid) {
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+      read(xs_chunk, tid, q);
+      pair<FAST>(px, py, pz, bias, q);
+    }
+  }
+};
+
+// hi = H(v), lo = H(v - hi) of two values, packed; fp16's lo words in one
+// instruction each (v_fma_mix: v * 1 - hi in FP32, rounded to fp16).
+template <class H>
+__device__ __forceinline__ void split2(float v0, float v1, uint32_t& hi, uint32_t& lo) {
+  typedef H h2 __attribute__((ext_vector_type(2)));
+  const f32x2 v = {v0, v1};
+  const h2 h = __builtin_convertvector(v, h2);
+  hi = __builtin_bit_cast(uint32_t, h);
+  if constexpr (std::is_same<H, _Float16>::value) {
+    uint32_t r;
+    asm("v_fma_mixlo_f16 %0, %1, 1.0, -%2 op_sel_hi:[0,0,1]" : "=v"(r) : "v"(v0), "v"(hi));
+    asm("v_fma_mixhi_f16 %0, %1, 1.0, -%2 op_sel:[0,0,1] op_sel_hi:[0,0,1]"
+        : "+v"(r)
+        : "v"(v1), "v"(hi));
+    lo = r;
+  } else {
+    const f32x2 d = {v0 - (float)h[0], v1 - (float)h[1]};
+    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(d, h2));
+  }
 }
 
-// This thread's share of a chunk from its phase pairs into the LDS operand
-// layout of the precision: (Br, Bi) vectors (FP32), interleaved BF16 hi / lo
-// vectors (BF16 x3), or the three planes Br, Bi - Br, Br + Bi (three products).
-template <class C, int PREC>
-__device__ __forceinline__ void gen_store(f32x4* __restrict__ buf, const float (&pr)[4 * C::JT],
-                                          const float (&pi)[4 * C::JT], int tid) {
-  static_assert(C::TASKS % C::THREADS == 0, "whole tasks per thread");
+// Plane q of the thread's tasks into the chunk buffer: Br, Bi (NPL = 2) or Br,
+// Bi - Br, Br + Bi (NPL = 3).  An MFMA operand is 16 bytes a lane (8 antennas,
+// lane = pixel + 16 kk), kept as two 8-byte halves of 4 antennas, ordered
+// (plane, pixel block, hi / lo, half, lane): a task writes one half, and
+// consecutive lanes write consecutive 8 bytes, without bank conflicts.
+template <class C, class H, int NPL>
+__device__ __forceinline__ void gen_store(uint2* __restrict__ buf, const Phases<C>& ph, int tid, int q) {
 #pragma unroll
   for (int j = 0; j < C::JT; ++j) {
-    const int pl = (tid + j * C::THREADS) % C::NT;
-    const int g4 = gen_group<C>(tid, j);
-    const int cb = pl >> 5, jj = pl & 31;
-    const float* cr = pr + 4 * j;
-    const float* ci = pi + 4 * j;
-    if (PREC == 3) {
-      const int g16 = g4 >> 2, h = (g4 >> 1) & 1, half = g4 & 1;
-      bf16x4* b4 = (bf16x4*)buf;
+    const int pl = tid % C::NT;
+    const int Q = gen_group<C>(tid, j);
+    const int at = ((q * C::NPB + (pl >> 4)) * 4 + (Q & 1)) * 64 + (Q >> 1) * 16 + (pl & 15);
+    uint2 hi, lo;
+    float v[4];
 #pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        bf16x4 hi, lo;
+    for (int e = 0; e < 4; ++e) {
+      const float r = ph.cr[4 * j + e], i = ph.ci[4 * j + e];
+      v[e] = NPL == 2 ? (q == 0 ? r : i) : (q == 0 ? r : (q == 1 ? i - r : r + i));
+    }
+    split2<H>(v[0], v[1], hi.x, lo.x);
+    split2<H>(v[2], v[3], hi.y, lo.y);
+    buf[at] = hi;
+    buf[at + 128] = lo;
+  }
+}
+
+// One plane of the W^H operand of a step: hi and lo words of the wave's NV blocks.
+template <class H, int NV>
+struct AFrag {
+  typename Mma<H>::h8 v[NV][2];
+};
+template <class H, int NV>
+__device__ __forceinline__ void load_a(AFrag<H, NV>& a, const BB_GLOBAL typename Mma<H>::h8* A, int64_t m_step,
+                                       int unit, int lane) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const float v = q == 0 ? cr[s] : (q == 1 ? ci[s] - cr[s] : cr[s] + ci[s]);
-          const __bf16 vh = (__bf16)v;
-          hi[s] = vh;
-          lo[s] = (__bf16)(v - (float)vh);
-        }
-        const int o = ((((g16 * 3 + q) * C::NCB + cb) * 2) * 64 + h * 32 + jj) * 2 + half;
-        b4[o] = hi;
-        b4[o + 128] = lo;
-      }
-    } else if (PREC == 2) {
-      const int g8 = g4 >> 1, h = g4 & 1;
-      f32x4 vr = {cr[0], cr[1], cr[2], cr[3]};
-      f32x4 vd = {ci[0] - cr[0], ci[1] - cr[1], ci[2] - cr[2], ci[3] - cr[3]};
-      f32x4 vs = {cr[0] + ci[0], cr[1] + ci[1], cr[2] + ci[2], cr[3] + ci[3]};
-      buf[((g8 * 3 + 0) * C::NCB + cb) * 64 + h * 32 + jj] = vr;
-      buf[((g8 * 3 + 1) * C::NCB + cb) * 64 + h * 32 + jj] = vd;
-      buf[((g8 * 3 + 2) * C::NCB + cb) * 64 + h * 32 + jj] = vs;
-    } else if (PREC == 0) {
-      f32x4 vr = {cr[0], cr[1], cr[2], cr[3]};
-      f32x4 vi = {ci[0], ci[1], ci[2], ci[3]};
-      buf[(g4 * C::NCB + cb) * 64 + jj] = vr;
-      buf[(g4 * C::NCB + cb) * 64 + 32 + jj] = vi;
-    } else {
-      bf16x8 hi, lo;
+  for (int m = 0; m < NV; ++m) {
+    const BB_GLOBAL typename Mma<H>::h8* const blk = A + (m * m_step + (int64_t)unit * 128);  // wave-uniform
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const __bf16 hr = (__bf16)cr[s], hiv = (__bf16)ci[s];
-        hi[2 * s] = hr;
-        hi[2 * s + 1] = hiv;
-        lo[2 * s] = (__bf16)(cr[s] - (float)hr);
-        lo[2 * s + 1] = (__bf16)(ci[s] - (float)hiv);
-      }
-      const int g8 = g4 >> 1, h = g4 & 1;
-      bf16x8* b16 = (bf16x8*)buf;
-      b16[((g8 * C::NCB + cb) * 2 + 0) * 64 + h * 32 + jj] = hi;
-      b16[((g8 * C::NCB + cb) * 2 + 1) * 64 + h * 32 + jj] = lo;
+    for (int t = 0; t < 2; ++t) a.v[m][t] = blk[lane + t * 64];
+  }
+}
+
+// x with every 16-bit word negated.
+template <class V>
+__device__ __forceinline__ V negated(V x) {
+  typedef unsigned u4 __attribute__((ext_vector_type(4)));
+  return __builtin_bit_cast(V, __builtin_bit_cast(u4, x) ^ (u4)0x80008000u);
+}
+
+// B operand of one step (pixel block n of the wave, plane u of the W operand):
+// hi and lo words of plane u of the phases, with NPL = 2 of both planes.
+template <class H, int NPL>
+struct BFrag {
+  typename Mma<H>::h8 v[NPL == 2 ? 2 : 1][2];
+};
+template <class C, class H, int NPL>
+__device__ __forceinline__ void load_b(BFrag<H, NPL>& b, const uint2* __restrict__ buf, int u, int pb, int lane) {
+#pragma unroll
+  for (int i = 0; i < (NPL == 2 ? 2 : 1); ++i) {
+    const uint2* const at = buf + ((NPL == 2 ? i : u) * C::NPB + pb) * 256 + lane;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      typedef unsigned u4 __attribute__((ext_vector_type(4)));
+      const uint2 x = at[t * 128], y = at[t * 128 + 64];
+      b.v[i][t] = __builtin_bit_cast(typename Mma<H>::h8, u4{x.x, x.y, y.x, y.y});
     }
   }
 }
 
-template <class C, int PREC>
-__device__ __forceinline__ void gen_chunk(f32x4* __restrict__ buf, const BB_LDS double* __restrict__ xs_chunk,
-                                          double px, double py, double pz, int tid) {
-  float cr[4 * C::JT], ci[4 * C::JT];
-  gen_pairs<C, PREC>(cr, ci, xs_chunk, px, py, pz, tid, 0, 4 * C::JT);
-  gen_store<C, PREC>(buf, cr, ci, tid);
+// acc[m][n] += a b (or -a b) of the split operands: lo hi + hi lo + hi hi.
+template <class H, int NV, int MR, int NP, bool NEG>
+__device__ __forceinline__ void mma3(f32x4 (&acc)[MR][NP], int n, const AFrag<H, NV>& a,
+                                     const typename Mma<H>::h8 (&b)[2]) {
+#pragma unroll
+  for (int t = 0; t < 3; ++t)
+#pragma unroll
+    for (int m = 0; m < NV; ++m) {
+      const typename Mma<H>::h8 av = a.v[m][t == 0 ? 1 : 0];
+      acc[m][n] = Mma<H>::op(NEG ? negated(av) : av, b[t == 1 ? 1 : 0], acc[m][n]);
+    }
 }
 
-// A operand (the W^H side) of one MFMA group: 4 contraction steps of the
-// wave's k-block.  It is loaded from L2 / HBM one group ahead of its use, so
-// the load latency is covered by the previous group's MFMAs.
-template <int PREC>
-struct AFrag;
-template <>
-struct AFrag<0> {  // Er / Ei rows, 4 antennas
-  f32x4 v[2];
-};
-template <>
-struct AFrag<1> {  // Er / Ei rows, hi / lo, 8 antennas
-  bf16x8 h[2], l[2];
-};
-template <>
-struct AFrag<2> {  // three planes, 8 antennas
-  f32x4 v[3];
-};
-template <>
-struct AFrag<3> {  // three planes, hi / lo, 16 antennas
-  bf16x8 h[3], l[3];
-};
-
-template <class C, int PREC>
-struct NGroups {  // MFMA groups per LDS chunk
-  static constexpr int N = PREC == 0 ? C::G4 : (PREC == 3 ? C::G16 : C::G8);
-};
-
-// base: first vector of this wave's k-block; stride: vectors per row tile (PREC 0/1)
-// or per plane (PREC 2/3); group g of chunk c.
-template <class C, int PREC>
-__device__ __forceinline__ void load_a(AFrag<PREC>& a, const void* apack, int64_t base, int64_t stride,
-                                       int c, int g, int lane) {
-  if constexpr (PREC == 0) {
-    const BB_GLOBAL f32x4* __restrict__ A = as_global<f32x4>(apack);
-    const int64_t o = base + (int64_t)(c * C::G4 + g) * 64 + lane;
-    a.v[0] = A[o];
-    a.v[1] = A[o + stride];
-  } else if constexpr (PREC == 1) {
-    const BB_GLOBAL bf16x8* __restrict__ A = as_global<bf16x8>(apack);
-    const int64_t o = base + (int64_t)(c * C::G8 + g) * 128 + lane;
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-      a.h[rt] = A[o + rt * stride];
-      a.l[rt] = A[o + rt * stride + 64];
-    }
-  } else if constexpr (PREC == 2) {
-    const BB_GLOBAL f32x4* __restrict__ A = as_global<f32x4>(apack);
-    const int64_t o = base + (int64_t)(c * C::G8 + g) * 64 + lane;
-#pragma unroll
-    for (int q = 0; q < 3; ++q) a.v[q] = A[o + q * stride];
+// MFMAs of one step.  NPL = 3: accumulators k1, k2, k3; NPL = 2: Er = Wr Br + Wi Bi, Ei = Wr Bi - Wi Br.
+template <class C, class H, int NPL, int NV>
+__device__ __forceinline__ void mma_step(f32x4 (&acc)[NPL][C::MR][C::NP], const AFrag<H, NV>& a,
+                                         const BFrag<H, NPL>& b, int u, int n) {
+  if constexpr (NPL == 3) {
+    mma3<H, NV, C::MR, C::NP, false>(acc[u], n, a, b.v[0]);
+  } else if (u == 0) {
+    mma3<H, NV, C::MR, C::NP, false>(acc[0], n, a, b.v[0]);
+    mma3<H, NV, C::MR, C::NP, false>(acc[1], n, a, b.v[1]);
   } else {
-    const BB_GLOBAL bf16x8* __restrict__ A = as_global<bf16x8>(apack);
-    const int64_t o = base + (int64_t)(c * C::G16 + g) * 128 + lane;
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      a.h[q] = A[o + q * stride];
-      a.l[q] = A[o + q * stride + 64];
-    }
+    mma3<H, NV, C::MR, C::NP, false>(acc[0], n, a, b.v[1]);
+    mma3<H, NV, C::MR, C::NP, true>(acc[1], n, a, b.v[0]);
   }
 }
 
-// MFMAs of group g of an LDS chunk for this wave's k-block and NB pixel blocks.
-template <class C, int PREC, int NB>
-__device__ __forceinline__ void mma_group(f32x16 (&acc)[Acc<PREC>::N][NB], const AFrag<PREC>& a,
-                                          const f32x4* __restrict__ buf, int g, int cb0, int lane) {
-  if constexpr (PREC == 0) {
-    f32x4 b[NB];
-#pragma unroll
-    for (int n = 0; n < NB; ++n) b[n] = buf[(g * C::NCB + cb0 + n) * 64 + lane];
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-        for (int n = 0; n < NB; ++n)
-          acc[rt][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[rt][s], b[n][s], acc[rt][n], 0, 0, 0);
-  } else if constexpr (PREC == 1) {
-    const bf16x8* Bb = (const bf16x8*)buf;
-    bf16x8 bh[NB], bl[NB];
-#pragma unroll
-    for (int n = 0; n < NB; ++n) {
-      const int o = ((g * C::NCB + cb0 + n) * 2) * 64 + lane;
-      bh[n] = Bb[o];
-      bl[n] = Bb[o + 64];
-    }
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-      for (int n = 0; n < NB; ++n) {
-        acc[rt][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l[rt], bh[n], acc[rt][n], 0, 0, 0);
-        acc[rt][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h[rt], bl[n], acc[rt][n], 0, 0, 0);
-        acc[rt][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h[rt], bh[n], acc[rt][n], 0, 0, 0);
-      }
-  } else if constexpr (PREC == 2) {
-    // planes q = 0, 1, 2 pair with Br, Bi - Br, Br + Bi
-    f32x4 b[3 * NB];
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-#pragma unroll
-      for (int n = 0; n < NB; ++n) b[3 * n + q] = buf[((g * 3 + q) * C::NCB + cb0 + n) * 64 + lane];
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int n = 0; n < NB; ++n)
-#pragma unroll
-        for (int q = 0; q < 3; ++q)
-          acc[q][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[q][s], b[3 * n + q][s], acc[q][n], 0, 0, 0);
-  } else {
-    const bf16x8* Bb = (const bf16x8*)buf;
-    bf16x8 bh[3 * NB], bl[3 * NB];
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-#pragma unroll
-      for (int n = 0; n < NB; ++n) {
-        const int o = (((g * 3 + q) * C::NCB + cb0 + n) * 2) * 64 + lane;
-        bh[3 * n + q] = Bb[o];
-        bl[3 * n + q] = Bb[o + 64];
-      }
-#pragma unroll
-    for (int n = 0; n < NB; ++n)
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        f32x16& c = acc[q][n];
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l[q], bh[3 * n + q], c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h[q], bl[3 * n + q], c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h[q], bh[3 * n + q], c, 0, 0, 0);
-      }
-  }
-}
-
-// (Er, Ei) of accumulator register r of pixel block n.
-template <int PREC, int NB>
-__device__ __forceinline__ void fields(const f32x16 (&acc)[Acc<PREC>::N][NB], int n, int r, float& er, float& ei) {
-  if constexpr (PREC >= 2) {
-    er = acc[0][n][r] - acc[2][n][r];
-    ei = acc[0][n][r] + acc[1][n][r];
-  } else {
-    er = acc[0][n][r];
-    ei = acc[1][n][r];
-  }
-}
-
-// MODE 0: level images (the product).  MODE 1: write E itself (two planes,
-// re and im, [K_alloc][n_pix] each) for the backward pass; one instance only.
-template <int MB, int NB, int WK, int WN, int PREC, int MODE>
-__global__ __launch_bounds__(64 * WK * WN) void synth_fwd_kernel(const FwdParams P) {
-  static_assert(MB == 1, "one k-block of 32 eigenpairs per wave");
-  using C = TileCfg<MB, NB, WK, WN>;
-  __shared__ f32x4 s_buf[2][ChunkVec<C, PREC>::N];
-  constexpr int NA = Acc<PREC>::N;
-  constexpr int NG = NGroups<C, PREC>::N;
-  __shared__ float s_part[WK][kMaxLevels][C::NT];
+template <class C, class H, int NPL>
+__global__ __launch_bounds__(C::THREADS, C::OCC) void synth_fwd_kernel(const FwdParams P) {
+  typedef typename Mma<H>::h8 h8;
+  constexpr int MR = C::MR, NP = C::NP, WK = C::WK, WN = C::WN;
+  extern __shared__ __align__(16) char s_mem[];
+  constexpr int kBuf = NPL * C::NPB * 256;
+  uint2* const s_buf = (uint2*)s_mem;  // two chunk buffers
   // scaled positions of the current instance, (x, y, z, 0) per antenna: every
   // phase chunk reads them from here (a broadcast LDS read per antenna) rather
   // than through L2, whose latency would otherwise open each chunk
-  __shared__ __align__(16) double s_xs[4 * kMaxAnt];
+  double* const s_xs = (double*)(s_mem + 2 * C::buf_bytes(NPL));
   const BB_LDS double* const xs = (const BB_LDS double*)s_xs;
+  float* const s_part = (float*)(s_xs + 4 * P.max_L_pad);  // [WK][n_levels][NT]
+  auto part = [&](int q, int l, int pl) -> float& { return s_part[(q * P.n_levels + l) * C::NT + pl]; };
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  // k-block of a wave = wave / WN: the waves of one SIMD (wave mod 4) cover the
-  // k-blocks evenly, so an instance whose K fills only part of the tile leaves
-  // no SIMD idle
-  const int wk = wave / WN;
-  const int wn = wave % WN;
-  const int cb0 = wn * NB;
+  // Block m of a wave in pass p is block p MR WK + m WK + wk, wk = wave / WN: the
+  // blocks that exist at a given K fall evenly on the waves of each SIMD.
+  const int wk = __builtin_amdgcn_readfirstlane(wave / WN);
+  const int pb0 = __builtin_amdgcn_readfirstlane((wave % WN) * NP);
   const int n_levels = P.n_levels;
-  // Phases of the next chunk are spread over the MFMA groups of the current
-  // one.  A SIMD issues few vector instructions while another of its waves
-  // streams MFMAs, so phases generated in one burst per chunk left the matrix
-  // pipe idle at the chunk's barrier; in slices, each wave's phase work sits
-  // between its own MFMA groups while the other wave keeps multiplying.
-  constexpr int PPG = 4 * C::JT / NG;  // phase pairs per MFMA group
-  static_assert(PPG * NG == 4 * C::JT, "pairs split evenly over the groups");
+
+  // the fast phase form needs pixels of at most unit length (up to rounding):
+  // checked once, over every pixel this wave will generate phases for
+  bool unit_pixels = true;
+  for (int64_t tile = blockIdx.x; tile < P.n_tiles; tile += gridDim.x) {
+    int64_t pg = tile * C::NT + (tid % C::NT);
+    if (pg >= P.n_pix) pg = P.n_pix - 1;
+    for (int a = 0; a < 3; ++a) unit_pixels = unit_pixels && fabs(P.pix[pg + a * P.pix_ld]) <= 1.001;
+  }
+  unit_pixels = __all(unit_pixels);
 
   // Persistent grid: workgroup b owns pixel tiles b, b + gridDim.x, ...; every
   // workgroup walks the groups (slots) and their instances in the same order,
@@ -669,462 +556,248 @@ __global__ __launch_bounds__(64 * WK * WN) void synth_fwd_kernel(const FwdParams
       // store, which the compiler cannot prove does not alias them.
       const int inst = __builtin_amdgcn_readfirstlane(P.inst_list[ii]);
       const InstDesc& Dg = P.descs[inst];
-      const void* const apack = Dg.apack;
+      const BB_GLOBAL h8* const apack = as_global<h8>(Dg.apack);
       const BB_GLOBAL double* const xs_g = as_global<double>(Dg.xs);
       const BB_GLOBAL float* const wts = as_global<float>(Dg.wts);
+      const BB_GLOBAL int* const wexp = as_global<int>(Dg.wexp);
       const BB_GLOBAL int* const levs = as_global<int>(Dg.levs);
-      const BB_GLOBAL int* const kbr = as_global<int>(Dg.kbr);  // (lo, hi) pairs
-      const int K_pad = __builtin_amdgcn_readfirstlane(P.dyn[inst].K_pad);
+      const BB_GLOBAL int* const kbr =
+          as_global<int>(Dg.kbr) + 2 * (__builtin_amdgcn_readfirstlane(Dg.K_alloc) / 32);  // (lo, hi) of each 16-block
+      const int nkb = __builtin_amdgcn_readfirstlane(P.dyn[inst].K_eff + 15) / 16;
       const int L_pad = __builtin_amdgcn_readfirstlane(Dg.L_pad);
       const int n_chunks = L_pad / C::LCH;
-      const int n_pass = (K_pad + C::KC - 1) / C::KC;
-      // 16-byte vectors per A row tile (PREC 0/1) or per plane (PREC 2/3)
-      const int64_t a_stride = PREC >= 2 ? (int64_t)(L_pad / 8) * 64 : (int64_t)(L_pad / 4) * 64;
-      if (blockIdx.x < P.n_tiles) {  // workgroup-uniform: this workgroup owns a tile
-        __syncthreads();  // the previous instance's phase chunks are done with s_xs
-        for (int i = tid; i < 2 * L_pad; i += C::THREADS)
-          ((f64x2*)s_xs)[i] = ((const BB_GLOBAL f64x2*)xs_g)[i];
-        __syncthreads();
+      const int n_pass = (nkb * 16 + C::KC - 1) / C::KC;
+      const int64_t kb_vec = (int64_t)n_chunks * NPL * 128;  // 16-byte vectors per 16-eigenpair block
+      const bool near = __builtin_amdgcn_readfirstlane(P.dyn[inst].fast_phase) != 0;
+      if (blockIdx.x >= P.n_tiles || n_pass == 0) continue;  // workgroup-uniform
+      __syncthreads();  // the previous instance's phases are done with s_xs
+      for (int i = tid; i < 2 * L_pad; i += C::THREADS) ((f64x2*)s_xs)[i] = ((const BB_GLOBAL f64x2*)xs_g)[i];
+      for (int i = tid; i < WK * n_levels * C::NT; i += C::THREADS) s_part[i] = 0.0f;
+      __syncthreads();
+
+      // this thread's pixel (phase generation); clamp the ragged tail
+      double px, py, pz;
+      auto load_pixel = [&](int64_t tile) {
+        int64_t pg = tile * C::NT + (tid % C::NT);
+        if (pg >= P.n_pix) pg = P.n_pix - 1;
+        px = P.pix[pg];
+        py = P.pix[pg + P.pix_ld];
+        pz = P.pix[pg + 2 * P.pix_ld];
+      };
+      double bias = kPhaseBias;
+      asm("" : "+v"(bias));  // kept in registers: the multiply-add then takes it as an operand
+      load_pixel(blockIdx.x);
+      const bool fast = near && unit_pixels;  // wave-uniform
+      int par = 0;  // chunk buffer holding the current chunk
+      {
+        Phases<C> ph;
+        if (fast)
+          ph.template all<true>(xs, px, py, pz, bias, tid);
+        else
+          ph.template all<false>(xs, px, py, pz, bias, tid);
+#pragma unroll
+        for (int q = 0; q < NPL; ++q) gen_store<C, H, NPL>(s_buf, ph, tid, q);
       }
+      __syncthreads();
       for (int64_t tile = blockIdx.x; tile < P.n_tiles; tile += gridDim.x) {
         const int64_t p0 = tile * C::NT;
-        for (int i = tid; i < WK * kMaxLevels * C::NT; i += C::THREADS) (&s_part[0][0][0])[i] = 0.0f;
-        // this thread's pixel (phase generation); clamp the ragged tail
-        int64_t pg = p0 + (tid % C::NT);
-        if (pg >= P.n_pix) pg = P.n_pix - 1;
-        const double px = P.pix[pg], py = P.pix[pg + P.pix_ld], pz = P.pix[pg + 2 * P.pix_ld];
-        for (int pass = 0; pass < n_pass; ++pass) {
-          const int kb = pass * (C::KC / 32) + wk;   // this wave's k-block
-          const bool active = kb < K_pad / 32;        // wave-uniform
-          const int64_t a_base = (int64_t)kb * (PREC >= 2 ? 3 : 2) * a_stride;
-          f32x16 acc[NA][NB];
-#pragma unroll
-          for (int t = 0; t < NA; ++t)
-#pragma unroll
-            for (int n = 0; n < NB; ++n)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) acc[t][n][r] = 0.0f;
-          AFrag<PREC> a_cur;
-          if (active) load_a<C, PREC>(a_cur, apack, a_base, a_stride, 0, 0, lane);
-
-          __syncthreads();  // previous users of s_buf are done
-          gen_chunk<C, PREC>(s_buf[0], xs, px, py, pz, tid);
-          __syncthreads();
-          for (int c = 0; c < n_chunks; ++c) {
-            // the last chunk regenerates itself into the idle buffer (read by
-            // nobody), so that no branch splits the MFMA stream
-            const int c_next = min(c + 1, n_chunks - 1);
-            const BB_LDS double* const xs_next = xs + 4 * c_next * C::LCH;
-            float cr[4 * C::JT], ci[4 * C::JT];
-            if (active) {
-              // FP32 three products: the second wave of each SIMD multiplies at a
-              // higher priority, which staggers the two waves' phase slices
-              if (PREC == 2 && wave >= C::WAVES / 2) __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-              for (int g = 0; g < NG; ++g) {
-                AFrag<PREC> a_nxt;  // next group's operand (past the end: reloads the last chunk's)
-                load_a<C, PREC>(a_nxt, apack, a_base, a_stride, g + 1 < NG ? c : c_next, g + 1 < NG ? g + 1 : 0,
-                                lane);
-                gen_pairs<C, PREC>(cr, ci, xs_next, px, py, pz, tid, g * PPG, PPG);
-                mma_group<C, PREC, NB>(acc, a_cur, s_buf[c & 1], g, cb0, lane);
-                a_cur = a_nxt;
-                // keep each group's phase pairs among its own MFMAs (left to
-                // itself the scheduler sinks them all behind the last group)
-                __builtin_amdgcn_sched_barrier(0);
-              }
-              if (PREC == 2 && wave >= C::WAVES / 2) __builtin_amdgcn_s_setprio(0);
-            } else {
-              gen_pairs<C, PREC>(cr, ci, xs_next, px, py, pz, tid, 0, 4 * C::JT);
-            }
-            gen_store<C, PREC>(s_buf[(c + 1) & 1], cr, ci, tid);
-            __syncthreads();
-          }
-          if (!active) continue;
-
-          if (MODE == 1) {
-#pragma unroll
-            for (int n = 0; n < NB; ++n) {
-              const int64_t p = p0 + (cb0 + n) * 32 + (lane & 31);
-              if (p < P.n_pix) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                  const int k = kb * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                  float er, ei;
-                  fields<PREC, NB>(acc, n, r, er, ei);
-                  P.e_out[(int64_t)k * P.e_ld + p] = er;
-                  P.e_out[(int64_t)(P.e_rows + k) * P.e_ld + p] = ei;
-                }
-              }
-            }
-            continue;
-          }
-          // epilogue: weighted |E|^2 into per-level partial sums
-          const int lev_lo = kbr[2 * kb], lev_hi = kbr[2 * kb + 1];
-          if (lev_lo > lev_hi) continue;  // no kept eigenvalue in this k-block
-          float w[16];
-          int lv[16];
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int k = kb * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-            w[r] = wts[k];
-            lv[r] = levs[k];
-          }
-#pragma unroll
-          for (int n = 0; n < NB; ++n) {
-            float e2[16];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              float er, ei;
-              fields<PREC, NB>(acc, n, r, er, ei);
-              e2[r] = w[r] * fmaf(er, er, ei * ei);
-            }
-            for (int l = lev_lo; l <= lev_hi; ++l) {
-              float sum = 0.0f;
-#pragma unroll
-              for (int r = 0; r < 16; ++r) sum += (lv[r] == l) ? e2[r] : 0.0f;
-              sum += __shfl_xor(sum, 32);
-              if (lane < 32) s_part[wk][l][(cb0 + n) * 32 + lane] += sum;
-            }
-          }
-        }
-        __syncthreads();
-        if (MODE == 1) continue;
-        for (int i = tid; i < n_levels * C::NT; i += C::THREADS) {
-          const int l = i / C::NT, pl = i % C::NT;
-          const int64_t p = p0 + pl;
-          if (p < P.n_pix) {
-            float sum = 0.0f;
-#pragma unroll
-            for (int q = 0; q < WK; ++q) sum += s_part[q][l][pl];
-            float* dst = P.img + ((int64_t)slot * n_levels + l) * P.img_ld + p;
-            *dst += sum;
-          }
-        }
-        __syncthreads();
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Tiles of 16-row eigenpair blocks for the three-product FP32 form, on
-// v_mfma_f32_16x16x4f32 (the same matrix rate as 32x32x2): kept eigenpairs are
-// padded to 16 rather than 32, which is what small K loses most to.
-//   MR x NP: 16x16 output blocks per wave (eigenpair blocks x pixel blocks);
-//   WK x WN: waves along eigenpairs and along pixels.  Eigenpair block m of
-//   k-group wk in pass p is block p * MR * WK + m * WK + wk (interleaved), so the
-//   blocks that exist at a given K fall evenly on the k-groups, and with WN a
-//   multiple of 4 each SIMD holds one wave of every k-group.
-// MFMA operand order (64 lanes): A lane l = row l % 16 of antenna l / 16 of the
-// step, B lane l = pixel l % 16 of antenna l / 16; result register r of lane l
-// = row 4 (l / 16) + r, pixel l % 16.  Operand vectors are float2 (two steps,
-// 8 antennas): a group of MFMAs covers 8 antennas, which keeps the A operand
-// and its prefetch within the register budget (256 VGPRs at two waves per
-// SIMD, 128 at four).
-template <int MR, int NP, int WK, int WN>
-struct Tile16 {
-  static constexpr int ROWS = 16;
-  static constexpr int WAVES = WK * WN;
-  static constexpr int THREADS = 64 * WAVES;
-  static constexpr int KC = 16 * MR * WK;       // eigenpairs per pass
-  static constexpr int NT = 16 * NP * WN;       // pixels per tile
-  static constexpr int NPB = NT / 16;           // 16-pixel blocks per tile
-  static constexpr int LCH = 32;                // antennas per LDS chunk
-  static constexpr int NG = LCH / 8;            // MFMA groups (2 steps of 4 antennas) per chunk
-  static constexpr int TASKS = NT * (LCH / 4);  // (pixel, 4-antenna) phase tasks per chunk
-  static constexpr int JT = TASKS / THREADS;
-  static constexpr int CHUNK_VEC = 3 * LCH * NT / 2;  // float2 vectors per chunk buffer
-  static constexpr int PPG = 4 * JT / NG;       // phase pairs per MFMA group
-  static_assert(WN % 4 == 0, "every SIMD holds one wave of each k-group");
-  static_assert(THREADS % NT == 0, "a thread keeps one pixel");
-  static_assert(JT >= 1 && TASKS % THREADS == 0, "whole tasks per thread");
-  static_assert(PPG * NG == 4 * JT, "pairs split evenly over the groups");
-  static_assert(kAntChunk % LCH == 0, "antenna padding covers the chunk");
-};
-
-// Task j of a thread: pixel (tid + j THREADS) mod NT and antenna group
-// gk = t / NT = 2 g8 + h; its four pairs are antennas 8 g8 + 4 s + kk for
-// s = 0, 1 and kk = 2 h, 2 h + 1: two float2 operand vectors.
-template <class C>
-__device__ __forceinline__ int gen_antenna16(int gk, int q) {
-  return 8 * (gk >> 1) + 4 * (q & 1) + 2 * (gk & 1) + ((q >> 1) & 1);
-}
-
-template <class C>
-__device__ __forceinline__ void gen_pairs16(float (&cr)[4 * C::JT], float (&ci)[4 * C::JT],
-                                            const BB_LDS double* __restrict__ xs_chunk, double px, double py,
-                                            double pz, int tid, int first, int count) {
-#pragma unroll
-  for (int q = 0; q < 4 * C::JT; ++q)
-    if (q >= first && q < first + count)
-      phase_pair(xs_chunk + 4 * gen_antenna16<C>(gen_group<C>(tid, q >> 2), q & 3), px, py, pz, cr[q], ci[q]);
-}
-
-// B planes Br, Bi - Br, Br + Bi of this thread's tasks into the chunk buffer,
-// float2 vectors ordered (8-antenna group, plane, pixel block, lane).
-template <class C>
-__device__ __forceinline__ void gen_store16(f32x2* __restrict__ buf, const float (&pr)[4 * C::JT],
-                                            const float (&pi)[4 * C::JT], int tid) {
-#pragma unroll
-  for (int j = 0; j < C::JT; ++j) {
-    const int pl = (tid + j * C::THREADS) % C::NT;
-    const int gk = gen_group<C>(tid, j);
-    const int g8 = gk >> 1, h = gk & 1;
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {  // kk = 2 h + e: pairs 2 e (s = 0) and 2 e + 1 (s = 1)
-      const int o = (g8 * 3 * C::NPB + (pl >> 4)) * 64 + (2 * h + e) * 16 + (pl & 15);
-      const float r0 = pr[4 * j + 2 * e], r1 = pr[4 * j + 2 * e + 1];
-      const float i0 = pi[4 * j + 2 * e], i1 = pi[4 * j + 2 * e + 1];
-      buf[o] = f32x2{r0, r1};
-      buf[o + C::NPB * 64] = f32x2{i0 - r0, i1 - r1};
-      buf[o + 2 * C::NPB * 64] = f32x2{r0 + i0, r1 + i1};
-    }
-  }
-}
-
-template <int NV>
-struct AFrag16 {  // three planes of NV eigenpair blocks, 8 antennas
-  f32x2 v[3][NV];
-};
-
-// A operand of group g of chunk c for NV blocks: block m's vectors start at
-// a_base + m * a_mstep (wave-uniform, so the address stays scalar and each
-// lane adds only its own offset), 8-antenna groups 3 x 64 vectors apart.
-template <class C, int NV>
-__device__ __forceinline__ void load_a16(AFrag16<NV>& a, const BB_GLOBAL f32x2* a_base, int64_t a_mstep, int c,
-                                         int g, int lane) {
-#pragma unroll
-  for (int m = 0; m < NV; ++m) {
-    const BB_GLOBAL f32x2* const blk = a_base + (m * a_mstep + (int64_t)(c * C::NG + g) * 3 * 64);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) a.v[q][m] = blk[lane + q * 64];
-  }
-}
-
-template <class C, int MR, int NP, int NV>
-__device__ __forceinline__ void mma_group16(f32x4 (&acc)[3][MR][NP], const AFrag16<NV>& a,
-                                            const f32x2* __restrict__ buf, int g, int pb0, int lane) {
-  f32x2 b[3][NP];
-#pragma unroll
-  for (int q = 0; q < 3; ++q)
-#pragma unroll
-    for (int n = 0; n < NP; ++n) b[q][n] = buf[((g * 3 + q) * C::NPB + pb0 + n) * 64 + lane];
-#pragma unroll
-  for (int s = 0; s < 2; ++s)
-#pragma unroll
-    for (int m = 0; m < NV; ++m)
-#pragma unroll
-      for (int n = 0; n < NP; ++n)
-#pragma unroll
-        for (int q = 0; q < 3; ++q)
-          acc[q][m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[q][m][s], b[q][n][s], acc[q][m][n], 0, 0, 0);
-}
-
-template <int MR, int NP, int WK, int WN>
-__global__ __launch_bounds__(64 * WK * WN) void synth_fwd16_kernel(const FwdParams P) {
-  using C = Tile16<MR, NP, WK, WN>;
-  __shared__ f32x2 s_buf[2][C::CHUNK_VEC];
-  __shared__ float s_part[WK][kMaxLevels][C::NT];
-  __shared__ __align__(16) double s_xs[4 * kMaxAnt];
-  const BB_LDS double* const xs = (const BB_LDS double*)s_xs;
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wk = __builtin_amdgcn_readfirstlane(wave / WN);
-  const int pb0 = __builtin_amdgcn_readfirstlane((wave % WN) * NP);
-  const int n_levels = P.n_levels;
-
-  // persistent grid over pixel tiles; groups and instances in the same order
-  // in every workgroup; one writer per image tile (as synth_fwd_kernel)
-  for (int grp = 0; grp < P.n_groups; ++grp) {
-    const int slot = __builtin_amdgcn_readfirstlane(P.group_slot[grp]);
-    for (int ii = P.group_begin[grp]; ii < P.group_begin[grp + 1]; ++ii) {
-      const int inst = __builtin_amdgcn_readfirstlane(P.inst_list[ii]);
-      const InstDesc& Dg = P.descs[inst];
-      const void* const apack = Dg.apack;
-      const BB_GLOBAL double* const xs_g = as_global<double>(Dg.xs);
-      const BB_GLOBAL float* const wts = as_global<float>(Dg.wts);
-      const BB_GLOBAL int* const levs = as_global<int>(Dg.levs);
-      const int K_alloc = __builtin_amdgcn_readfirstlane(Dg.K_alloc);
-      const BB_GLOBAL int* const kbr16 = as_global<int>(Dg.kbr) + 2 * (K_alloc / 32);
-      const int nb16 = __builtin_amdgcn_readfirstlane((P.dyn[inst].K_eff + 15) / 16);
-      const int L_pad = __builtin_amdgcn_readfirstlane(Dg.L_pad);
-      const int n_chunks = L_pad / C::LCH;
-      const int n_pass = (nb16 * 16 + C::KC - 1) / C::KC;
-      const int64_t a_blk_vec = (int64_t)(L_pad / 8) * 3 * 64;  // float2 vectors per 16-block
-      if (blockIdx.x < P.n_tiles) {
-        __syncthreads();
-        for (int i = tid; i < 2 * L_pad; i += C::THREADS) ((f64x2*)s_xs)[i] = ((const BB_GLOBAL f64x2*)xs_g)[i];
-        __syncthreads();
-      }
-      for (int64_t tile = blockIdx.x; tile < P.n_tiles; tile += gridDim.x) {
-        const int64_t p0 = tile * C::NT;
-        for (int i = tid; i < WK * kMaxLevels * C::NT; i += C::THREADS) (&s_part[0][0][0])[i] = 0.0f;
-        int64_t pg = p0 + (tid % C::NT);
-        if (pg >= P.n_pix) pg = P.n_pix - 1;
-        const double px = P.pix[pg], py = P.pix[pg + P.pix_ld], pz = P.pix[pg + 2 * P.pix_ld];
         for (int pass = 0; pass < n_pass; ++pass) {
           const int b0 = pass * MR * WK + wk;  // this wave's first block; block m is b0 + m WK
-          int nv = nb16 > b0 ? (nb16 - b0 + WK - 1) / WK : 0;
+          int nv = nkb > b0 ? (nkb - b0 + WK - 1) / WK : 0;
           nv = __builtin_amdgcn_readfirstlane(nv < MR ? nv : MR);
-          f32x4 acc[3][MR][NP];
+          f32x4 acc[NPL][MR][NP];
 #pragma unroll
-          for (int q = 0; q < 3; ++q)
+          for (int t = 0; t < NPL; ++t)
 #pragma unroll
             for (int m = 0; m < MR; ++m)
 #pragma unroll
-              for (int n = 0; n < NP; ++n) acc[q][m][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+              for (int n = 0; n < NP; ++n) acc[t][m][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-          // the chunk loop for NV existing blocks of this wave (NV = 0: phases only)
-          auto chunks = [&](auto nv_c) {
+          // The chunks of this pass, for NV existing blocks of this wave (NV = 0:
+          // phases only).  A chunk is S steps (plane u, pixel block n) of 3 NV MFMAs
+          // (6 NV with two planes); each step reads the next one's B operand, and the
+          // first of a plane the next plane's A operand, so that neither is waited
+          // for.  Beside the MFMAs the steps generate and store the phases of the
+          // next chunk, in slices, since a burst of them would leave the matrix pipe
+          // idle; the last chunk of a pass prepares the first chunk of the next pass
+          // or of the workgroup's next tile.  The chunk's one barrier comes before
+          // its last step: by then every wave has stored its phases and read its last
+          // B operand of this chunk, and the last step can read the next chunk's first.
+          auto chunks = [&](auto nv_c, auto fast_c) {
             constexpr int NV = decltype(nv_c)::value;
-            const BB_GLOBAL f32x2* const a_base = as_global<f32x2>(apack) + (int64_t)b0 * a_blk_vec;
-            const int64_t a_mstep = (int64_t)WK * a_blk_vec;
-            AFrag16<NV> a_cur;
-            if constexpr (NV > 0) load_a16<C, NV>(a_cur, a_base, a_mstep, 0, 0, lane);
-            __syncthreads();  // previous users of s_buf are done
-            {
-              float cr[4 * C::JT], ci[4 * C::JT];
-              gen_pairs16<C>(cr, ci, xs, px, py, pz, tid, 0, 4 * C::JT);
-              gen_store16<C>(s_buf[0], cr, ci, tid);
+            constexpr int NVA = NV > 0 ? NV : 1;
+            constexpr bool FAST = decltype(fast_c)::value;
+            constexpr int S = NPL * NP;
+            constexpr int PH = Phases<C>::P;
+            constexpr int PS = S - 1 - NPL;  // the pairs go to the first PS steps, the stores to the next NPL
+            static_assert(S % 2 == 0 && PS >= 1, "double-buffered B operand; steps for phases and stores");
+            const BB_GLOBAL h8* const A = apack + (int64_t)b0 * kb_vec;
+            const int64_t m_step = (int64_t)WK * kb_vec;
+            AFrag<H, NVA> a_cur, a_nxt;
+            BFrag<H, NPL> b[2];
+            if constexpr (NV > 0) {
+              load_a<H, NVA>(a_cur, A, m_step, 0, lane);
+              load_b<C, H, NPL>(b[0], s_buf + par * kBuf, 0, pb0, lane);
             }
-            __syncthreads();
             for (int c = 0; c < n_chunks; ++c) {
-              const int c_next = min(c + 1, n_chunks - 1);
-              const BB_LDS double* const xs_next = xs + 4 * c_next * C::LCH;
-              float cr[4 * C::JT], ci[4 * C::JT];
+              const bool last = c == n_chunks - 1;
+              if (last && pass == n_pass - 1) load_pixel(tile + gridDim.x);
+              const BB_LDS double* const xs_next = xs + (last ? 0 : 4 * (c + 1) * C::LCH);
+              Phases<C> ph;
               if constexpr (NV > 0) {
-                // waves of odd k-groups multiply at a higher priority, which
-                // staggers the phase slices of the waves sharing a SIMD
-                if (wk & 1) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-                for (int g = 0; g < C::NG; ++g) {
-                  AFrag16<NV> a_nxt;
-                  load_a16<C, NV>(a_nxt, a_base, a_mstep, g + 1 < C::NG ? c : c_next, g + 1 < C::NG ? g + 1 : 0,
-                                  lane);
-                  gen_pairs16<C>(cr, ci, xs_next, px, py, pz, tid, g * C::PPG, C::PPG);
-                  mma_group16<C, MR, NP, NV>(acc, a_cur, s_buf[c & 1], g, pb0, lane);
-                  a_cur = a_nxt;
+                for (int st = 0; st < S; ++st) {
+                  const int u = st / NP, n = st % NP;
+                  if (n == 0)  // next plane's operand (past the pass's end: its first again)
+                    load_a<H, NVA>(a_nxt, A, m_step, u + 1 < NPL ? c * NPL + u + 1 : (last ? 0 : (c + 1) * NPL), lane);
+                  if (st + 1 < S)
+                    load_b<C, H, NPL>(b[(st + 1) & 1], s_buf + par * kBuf, (st + 1) / NP, pb0 + (st + 1) % NP, lane);
+                  else
+                    load_b<C, H, NPL>(b[0], s_buf + (par ^ 1) * kBuf, 0, pb0, lane);
+#pragma unroll
+                  for (int q = 0; q < PH; ++q) {
+                    const int at = q * PS / PH + (PS >= 2 * PH ? 1 : 0);  // step of pair q; its position is read a step before
+                    if ((at > 0 ? at - 1 : 0) == st) ph.read(xs_next, tid, q);
+                  }
+                  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                  for (int q = 0; q < PH; ++q)
+                    if (q * PS / PH + (PS >= 2 * PH ? 1 : 0) == st) ph.template pair<FAST>(px, py, pz, bias, q);
+                  if (st >= PS && st < PS + NPL) gen_store<C, H, NPL>(s_buf + (par ^ 1) * kBuf, ph, tid, st - PS);
+                  mma_step<C, H, NPL, NVA>(acc, a_cur, b[st & 1], u, n);
+                  if (n == NP - 1) a_cur = a_nxt;
+                  if (st == S - 2) __syncthreads();
                   __builtin_amdgcn_sched_barrier(0);
                 }
-                if (wk & 1) __builtin_amdgcn_s_setprio(0);
               } else {
-                gen_pairs16<C>(cr, ci, xs_next, px, py, pz, tid, 0, 4 * C::JT);
+                ph.template all<FAST>(xs_next, px, py, pz, bias, tid);
+#pragma unroll
+                for (int q = 0; q < NPL; ++q) gen_store<C, H, NPL>(s_buf + (par ^ 1) * kBuf, ph, tid, q);
+                __syncthreads();
               }
-              gen_store16<C>(s_buf[(c + 1) & 1], cr, ci, tid);
-              __syncthreads();
+              par ^= 1;
             }
           };
+          auto by_form = [&](auto nv_c) {
+            if (fast)
+              chunks(nv_c, std::true_type{});
+            else
+              chunks(nv_c, std::false_type{});
+          };
           if (nv == MR)
-            chunks(std::integral_constant<int, MR>{});
-          else if (MR > 3 && nv == 3)
-            chunks(std::integral_constant<int, (MR > 3 ? 3 : 1)>{});
-          else if (MR > 2 && nv == 2)
-            chunks(std::integral_constant<int, (MR > 2 ? 2 : 1)>{});
+            by_form(std::integral_constant<int, MR>{});
           else if (MR > 1 && nv == 1)
-            chunks(std::integral_constant<int, 1>{});
+            by_form(std::integral_constant<int, 1>{});
           else
-            chunks(std::integral_constant<int, 0>{});
+            by_form(std::integral_constant<int, 0>{});
+          static_assert(MR <= 2, "block counts covered above");
 
-          // epilogue: weighted |E|^2 of each existing block into per-level sums
 #pragma unroll
           for (int m = 0; m < MR; ++m) {
             if (m >= nv) continue;
-            const int b = b0 + m * WK;
-            const int lev_lo = kbr16[2 * b], lev_hi = kbr16[2 * b + 1];
-            if (lev_lo > lev_hi) continue;
+            const int kb = b0 + m * WK;
+            const int lev_lo = kbr[2 * kb], lev_hi = kbr[2 * kb + 1];
+            if (lev_lo > lev_hi) continue;  // no kept eigenpair in this block
             float w[4];
-            int lv[4];
+            int lv[4], ex[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              const int k = b * 16 + 4 * (lane >> 4) + r;
+              const int k = kb * 16 + 4 * (lane >> 4) + r;
               w[r] = wts[k];
               lv[r] = levs[k];
+              ex[r] = wexp[k];
             }
 #pragma unroll
             for (int n = 0; n < NP; ++n) {
               float e2[4];
 #pragma unroll
               for (int r = 0; r < 4; ++r) {
-                const float er = acc[0][m][n][r] - acc[2][m][n][r];
-                const float ei = acc[0][m][n][r] + acc[1][m][n][r];
+                // fields (Er, Ei) of the accumulators, the columns' power-of-two scale undone
+                float er = NPL == 3 ? acc[0][m][n][r] - acc[NPL - 1][m][n][r] : acc[0][m][n][r];
+                float ei = NPL == 3 ? acc[0][m][n][r] + acc[1][m][n][r] : acc[1][m][n][r];
+                if (std::is_same<H, _Float16>::value) {
+                  er = ldexpf(er, ex[r]);
+                  ei = ldexpf(ei, ex[r]);
+                }
                 e2[r] = w[r] * fmaf(er, er, ei * ei);
               }
+              // weighted |E|^2 into per-level partial sums
               for (int l = lev_lo; l <= lev_hi; ++l) {
                 float sum = 0.0f;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) sum += (lv[r] == l) ? e2[r] : 0.0f;
                 sum += __shfl_xor(sum, 16);
                 sum += __shfl_xor(sum, 32);
-                if (lane < 16) s_part[wk][l][(pb0 + n) * 16 + lane] += sum;
+                if (lane < 16) part(wk, l, (pb0 + n) * 16 + lane) += sum;
               }
             }
           }
         }
+        // sum over the waves in a fixed order; the partials are cleared for the next tile
         __syncthreads();
         for (int i = tid; i < n_levels * C::NT; i += C::THREADS) {
           const int l = i / C::NT, pl = i % C::NT;
           const int64_t p = p0 + pl;
-          if (p < P.n_pix) {
-            float sum = 0.0f;
+          float sum = 0.0f;
 #pragma unroll
-            for (int q = 0; q < WK; ++q) sum += s_part[q][l][pl];
+          for (int q = 0; q < WK; ++q) {
+            float& x = part(q, l, pl);
+            sum += x;
+            x = 0.0f;
+          }
+          if (p < P.n_pix) {
             float* dst = P.img + ((int64_t)slot * n_levels + l) * P.img_ld + p;
             *dst += sum;
           }
         }
-        __syncthreads();
       }
     }
   }
 }
 
-// Resident workgroups of a kernel on the current device (persistent grid size).
-template <class K>
-static int resident_blocks(K kernel, int threads) {
-  int dev = 0, ncu = 0, per_cu = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess) return 0;
-  return ncu * (per_cu > 0 ? per_cu : 1);
+// Compute units of the current device (one device type per process).
+static int compute_units() {
+  static const int n = [] {
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    return ncu;
+  }();
+  return n;
 }
 
-template <int MB, int NB, int WK, int WN, int PREC, int MODE = 0>
+int resident_blocks(const void* kernel, int threads) {
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu < 1) per_cu = 1;
+  const int n = compute_units();
+  return (n > 0 ? n : 256) * per_cu;
+}
+
+template <class C, class H, int NPL>
 static hipError_t launch_cfg(const FwdParams& p, hipStream_t s) {
-  using C = TileCfg<MB, NB, WK, WN>;
   if (p.n_tiles <= 0 || p.n_groups <= 0) return hipSuccess;
-  auto kern = synth_fwd_kernel<MB, NB, WK, WN, PREC, MODE>;
-  static int resident = 0;  // per instantiation; one device type per process
-  if (resident <= 0) resident = resident_blocks(kern, C::THREADS);
-  int64_t grid = resident > 0 ? resident : 1024;
+  auto kern = synth_fwd_kernel<C, H, NPL>;
+  const size_t lds = C::lds_bytes(NPL, p.max_L_pad, p.n_levels);
+  static const hipError_t attr =
+      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
+  if (attr != hipSuccess) return attr;
+  if (lds > kMaxLds) return hipErrorInvalidValue;
+  // persistent grid: as many workgroups as are resident (registers and LDS)
+  const int by_regs = 4 * C::OCC / C::WAVES > 0 ? 4 * C::OCC / C::WAVES : 1;
+  const int by_lds = (int)(kMaxLds / lds);
+  int64_t grid = (int64_t)compute_units() * (by_regs < by_lds ? by_regs : by_lds);
+  if (grid <= 0) grid = 256;
   if (grid > p.n_tiles) grid = p.n_tiles;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(C::THREADS), 0, s, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(C::THREADS), lds, s, p);
   return hipGetLastError();
 }
 
-template <int PREC, int MODE, int MB, int NB, int WK, int WN>
-static hipError_t launch_tc(const FwdParams& p, TileCfg<MB, NB, WK, WN>, hipStream_t s) {
-  return launch_cfg<MB, NB, WK, WN, PREC, MODE>(p, s);
-}
-
-// 16-row tiles: the three-product FP32 form's level images only.
-template <int PREC, int MODE, int MR, int NP, int WK, int WN>
-static hipError_t launch_tc(const FwdParams& p, Tile16<MR, NP, WK, WN>, hipStream_t s) {
-  using C = Tile16<MR, NP, WK, WN>;
-  if constexpr (PREC != 2 || MODE != 0) {
-    return hipErrorInvalidValue;
-  } else {
-    if (p.n_tiles <= 0 || p.n_groups <= 0) return hipSuccess;
-    auto kern = synth_fwd16_kernel<MR, NP, WK, WN>;
-    static int resident = 0;  // per instantiation; one device type per process
-    if (resident <= 0) resident = resident_blocks(kern, C::THREADS);
-    int64_t grid = resident > 0 ? resident : 1024;
-    if (grid > p.n_tiles) grid = p.n_tiles;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(C::THREADS), 0, s, p);
-    return hipGetLastError();
-  }
-}
+// Contraction of a precision: the words of its split operands and its planes.
+template <int PREC>
+struct Form {
+  using H = typename std::conditional<PREC == 1 || PREC == 3, __bf16, _Float16>::type;
+  static constexpr int NPL = PREC >= 2 ? 3 : 2;
+};
 
 // ---------------------------------------------------------------------------
 // Tile candidates.  Each precision has a list of tile shapes (kernel
@@ -1133,58 +806,87 @@ static hipError_t launch_tc(const FwdParams& p, Tile16<MR, NP, WK, WN>, hipStrea
 // 128, or more.  Each class has a default shape (the measured best on this
 // GPU) and may use every shape of the list whose eigenpairs per pass do not
 // exceed the class's largest K (so that no wave of a tile is idle at that K).
-// Register budget: 8-wave tiles run two waves per SIMD (<= 256 VGPRs each),
-// 16-wave tiles four (<= 128).
+// Register budget: 512 / OCC VGPRs a wave at OCC waves per SIMD.
 template <class... T>
 struct TileList {};
 
 template <int PREC>
 struct Cands;
 template <>
-struct Cands<0> {  // 4 products: Er/Ei accumulators, 32 regs per output block
-  using L = TileList<TileCfg<1, 4, 8, 1>,   // 0: 256 x 128  (2 x 2 blocks per wave measured slower)
-                     TileCfg<1, 4, 4, 2>,   // 1: 128 x 256
-                     TileCfg<1, 2, 2, 4>,   // 2: 64 x 256
-                     TileCfg<1, 2, 1, 4>,   // 3: 32 x 256, 4 waves
-                     TileCfg<1, 2, 4, 2>>;  // 4: 128 x 128
+struct Cands<0> {  // 4 products: Er / Ei accumulators, half as many as three planes need, so twice the pixels a wave
+  using L = TileList<Tile<2, 8, 8, 1>,      // 0: 256 x 128
+                     Tile<2, 4, 4, 2>,      // 1: 128 x 128
+                     Tile<1, 2, 4, 4, 4>,   // 2: 64 x 128, 16 waves
+                     Tile<1, 2, 2, 2, 4>,   // 3: 32 x 64, 4 waves
+                     Tile<2, 4, 4, 1>>;     // 4: 128 x 64, 4 waves
   static constexpr int dflt[4] = {3, 2, 1, 0};
 };
 template <>
-struct Cands<1> {  // BF16 x3, 4 products: the shapes of the FP32 form, and narrower pixel tiles
-  using L = TileList<TileCfg<1, 4, 8, 1>,   // 0: 256 x 128
-                     TileCfg<1, 4, 4, 2>,   // 1: 128 x 256
-                     TileCfg<1, 2, 2, 4>,   // 2: 64 x 256
-                     TileCfg<1, 2, 1, 4>,   // 3: 32 x 256, 4 waves
-                     TileCfg<1, 2, 4, 2>,   // 4: 128 x 128
-                     TileCfg<1, 2, 8, 1>>;  // 5: 256 x 64
+struct Cands<1> {
+  using L = TileList<Tile<2, 8, 8, 1>,      // 0: 256 x 128
+                     Tile<2, 4, 4, 2>,      // 1: 128 x 128
+                     Tile<1, 2, 4, 4, 4>,   // 2: 64 x 128, 16 waves
+                     Tile<1, 2, 2, 2, 4>,   // 3: 32 x 64, 4 waves
+                     Tile<2, 4, 4, 1>,      // 4: 128 x 64, 4 waves
+                     Tile<2, 4, 8, 1>>;     // 5: 256 x 64
   static constexpr int dflt[4] = {3, 2, 1, 0};
 };
 template <>
-struct Cands<2> {  // 3 products: k1/k2/k3 accumulators, 48 regs per 32x32 output block
-  using L = TileList<TileCfg<1, 2, 8, 1>,    // 0: 256 x 64
-                     TileCfg<1, 1, 4, 4>,    // 1: 128 x 128, 16 waves: 3 active k-blocks (K <= 96) still
-                                             //    spread evenly over the four SIMDs
-                     TileCfg<1, 2, 2, 4>,    // 2: 64 x 256
-                     TileCfg<1, 1, 1, 8>,    // 3: 32 x 256, one pixel block per wave, two waves per SIMD
-                     TileCfg<1, 2, 4, 2>,    // 4: 128 x 128
-                     TileCfg<1, 1, 2, 8>,    // 5: 64 x 256, 16 waves
-                     Tile16<4, 2, 2, 4>,     // 6: 128 x 128 in 16-row blocks, 8 waves
-                     Tile16<2, 2, 2, 4>,     // 7: 64 x 128 in 16-row blocks
-                     Tile16<1, 1, 2, 8>,     // 8: 32 x 128 in 16-row blocks, 16 waves
-                     Tile16<2, 1, 2, 8>,     // 9: 64 x 128 in 16-row blocks, 16 waves
-                     Tile16<1, 2, 4, 4>,     // 10: 64 x 128 in 16-row blocks, 16 waves
-                     Tile16<2, 2, 4, 4>>;    // 11: 128 x 128 in 16-row blocks, 16 waves
+struct Cands<2> {  // 3 products: k1, k2, k3 accumulators
+  using L = TileList<Tile<2, 4, 8, 1>,      // 0: 256 x 64
+                     Tile<2, 4, 4, 1>,      // 1: 128 x 64, 4 waves
+                     Tile<2, 2, 2, 4>,      // 2: 64 x 128
+                     Tile<1, 2, 2, 2, 4>,   // 3: 32 x 64, 4 waves, up to four workgroups a CU
+                     Tile<2, 2, 4, 2>,      // 4: 128 x 64
+                     Tile<1, 4, 4, 2>,      // 5: 64 x 128
+                     Tile<1, 4, 8, 2, 4>,   // 6: 128 x 128, 16 waves
+                     Tile<2, 2, 2, 2>,      // 7: 64 x 64, 4 waves
+                     Tile<1, 2, 2, 4, 4>,   // 8: 32 x 128
+                     Tile<1, 2, 4, 4, 4>,   // 9: 64 x 128, 16 waves
+                     Tile<1, 2, 4, 2, 4>,   // 10: 64 x 64
+                     Tile<2, 4, 4, 2>>;     // 11: 128 x 128
   static constexpr int dflt[4] = {3, 9, 11, 0};
 };
 template <>
-struct Cands<3> {  // BF16 three products: in 16 waves its operand fragments would spill
-  using L = TileList<TileCfg<1, 2, 8, 1>,   // 0: 256 x 64
-                     TileCfg<1, 2, 4, 2>,   // 1: 128 x 128
-                     TileCfg<1, 2, 2, 4>,   // 2: 64 x 256
-                     TileCfg<1, 1, 1, 8>,   // 3: 32 x 256
-                     TileCfg<1, 1, 4, 2>>;  // 4: 128 x 64
+struct Cands<3> {
+  using L = TileList<Tile<2, 4, 8, 1>,      // 0: 256 x 64
+                     Tile<2, 4, 4, 2>,      // 1: 128 x 128
+                     Tile<1, 2, 4, 4, 4>,   // 2: 64 x 128, 16 waves
+                     Tile<1, 2, 2, 2, 4>,   // 3: 32 x 64, 4 waves
+                     Tile<2, 4, 4, 1>>;     // 4: 128 x 64, 4 waves
   static constexpr int dflt[4] = {3, 2, 1, 0};
 };
+
+// The shape that takes a tile's place for an image with fewer tiles than
+// compute units: half the pixels, the same eigenpairs per pass.
+template <class C>
+struct Narrow {
+  using T = C;
+};
+template <>
+struct Narrow<Tile<2, 8, 8, 1>> {
+  using T = Tile<2, 4, 8, 1>;
+};
+template <>
+struct Narrow<Tile<2, 4, 4, 2>> {
+  using T = Tile<2, 4, 4, 1>;
+};
+template <>
+struct Narrow<Tile<1, 2, 4, 4, 4>> {
+  using T = Tile<1, 2, 4, 2, 4>;
+};
+
+template <class C, class H, int NPL>
+static hipError_t launch_shape(FwdParams p, hipStream_t s) {
+  using N = typename Narrow<C>::T;
+  if constexpr (!std::is_same<N, C>::value) {
+    if (p.n_tiles < compute_units()) {
+      p.n_tiles = (p.n_pix + N::NT - 1) / N::NT;
+      return launch_cfg<N, H, NPL>(p, s);
+    }
+  }
+  return launch_cfg<C, H, NPL>(p, s);
+}
 
 template <int I, class F, class T0, class... Ts>
 static hipError_t tile_at(int id, F&& f, TileList<T0, Ts...>) {
@@ -1248,15 +950,6 @@ bool synth_tile_info(int precision, int id, int* kc, int* nt, int* waves) {
   return true;
 }
 
-int synth_tile_rows(int precision, int id) {
-  int rows = 32;
-  (void)with_tile(precision, id, [&](auto cfg) {
-    rows = decltype(cfg)::ROWS;
-    return hipSuccess;
-  });
-  return rows;
-}
-
 bool synth_tile_allowed(int precision, int id, int k_class) {
   static const int kmax[4] = {32, 64, 128, kMaxEig};
   int kc = 0;
@@ -1266,7 +959,9 @@ bool synth_tile_allowed(int precision, int id, int k_class) {
 
 template <int PREC>
 static hipError_t launch_prec_tile(const FwdParams& p, int id, hipStream_t s) {
-  return tile_at<0>(id, [&](auto cfg) { return launch_tc<PREC, 0>(p, cfg, s); }, typename Cands<PREC>::L{});
+  using F = Form<PREC>;
+  return tile_at<0>(id, [&](auto cfg) { return launch_shape<decltype(cfg), typename F::H, F::NPL>(p, s); },
+                    typename Cands<PREC>::L{});
 }
 
 hipError_t launch_synth_tile(const FwdParams& p, int precision, int id, hipStream_t s) {
@@ -1290,23 +985,6 @@ hipError_t launch_synth(const FwdParams& p, int max_K_alloc, int precision, int 
   return launch_synth_tile(p, precision, synth_default_tile(precision, synth_k_class(max_K_alloc)), s);
 }
 
-// FP32 recompute of E for the backward pass, in the three-product form
-// whatever the handle's precision (the instance is staged as three planes), on
-// 32-row tiles (the 16-row kernel writes no E), one per K class so that no
-// k-block wave idles: K <= 32: 32 x 256, <= 64: 64 x 256, <= 128: 128 x 128,
-// above: 256 x 64.
-using FieldsL = TileList<TileCfg<1, 1, 1, 8>, TileCfg<1, 2, 2, 4>, TileCfg<1, 2, 4, 2>, TileCfg<1, 2, 8, 1>>;
-
-int fields_tile_pixels(int K_alloc) {
-  int nt = 0;
-  tile_at<0>(synth_k_class(K_alloc), [&](auto cfg) { nt = decltype(cfg)::NT; return hipSuccess; }, FieldsL{});
-  return nt;
-}
-
-hipError_t launch_fields(const FwdParams& p, int K_alloc, hipStream_t s) {
-  return tile_at<0>(synth_k_class(K_alloc), [&](auto cfg) { return launch_tc<2, 1>(p, cfg, s); }, FieldsL{});
-}
-
 // Phase-generation throughput probe (measurement only): every thread takes one
 // pixel and evaluates the phases of all antennas `reps` times with the
 // synthesis kernel's own arithmetic (positions from LDS, FP64 argument and
@@ -1325,15 +1003,27 @@ __global__ __launch_bounds__(256) void phase_probe_kernel(const double* __restri
   }
   __syncthreads();
   const BB_LDS double* const xs = (const BB_LDS double*)s_xs;
+  bool near = true;
+  for (int l = threadIdx.x; l < n_ant; l += blockDim.x)
+    near = near && fabs(xs[4 * l]) + fabs(xs[4 * l + 1]) + fabs(xs[4 * l + 2]) < 0.999 * kPhaseFastMax;
+  near = __syncthreads_and(near);
+  double bias = kPhaseBias;
+  asm("" : "+v"(bias));
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n_pix; p += (int64_t)gridDim.x * blockDim.x) {
     const double px = pix[p], py = pix[p + n_pix], pz = pix[p + 2 * n_pix];
     float acc = 0.0f;
-    for (int r = 0; r < reps; ++r)
-      for (int l = 0; l < n_ant; ++l) {
-        float c, sn;
-        phase_pair(xs + 4 * l, px, py, pz, c, sn);
-        acc += c + sn;
-      }
+    auto all = [&](auto fast_c) {
+      for (int r = 0; r < reps; ++r)
+        for (int l = 0; l < n_ant; ++l) {
+          float c, sn;
+          phase_pair<decltype(fast_c)::value>(xs[4 * l], xs[4 * l + 1], xs[4 * l + 2], px, py, pz, bias, c, sn);
+          acc += c + sn;
+        }
+    };
+    if (near && fabs(px) <= 1.001 && fabs(py) <= 1.001 && fabs(pz) <= 1.001)
+      all(std::true_type{});
+    else
+      all(std::false_type{});
     out[p] = acc;
   }
 }
