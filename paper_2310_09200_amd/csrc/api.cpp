@@ -1,6 +1,6 @@
 // Host side of the C ABI declared in include/bluebild.h: argument validation,
-// workspace carving, stream-ordered launches, the rocSOLVER eigensolve of the
-// FP64 pre-step, status codes.  No exception crosses the ABI.
+// workspace carving, stream-ordered launches, the eigensolve of the FP64
+// pre-step, status codes.  No exception crosses the ABI.
 
 #include <hip/hip_runtime.h>
 #include <rocblas/rocblas.h>
@@ -43,6 +43,7 @@ struct SingleMeta {
 struct Layout {  // byte offsets into a handle's workspace
   size_t meta, err, apack, xs, wts, levs, kbr, perm;
   size_t A, G, T, U, evals, E, info, dsel, lsel, wcol, solver, solver_bytes;
+  size_t tau, pub, status;
   size_t total;
 };
 
@@ -103,6 +104,12 @@ Layout make_layout(const bb_options& o, size_t solver_bytes) {
   p += align_up(4 * Lm);
   l.wcol = p;
   p += align_up(4 * Lm);
+  l.tau = p;
+  p += align_up(16 * Lm);
+  l.pub = p;
+  p += align_up(bb::eig_pub_bytes());
+  l.status = p;
+  p += align_up(sizeof(bb::EigStatus));
   l.solver = p;
   l.solver_bytes = solver_bytes;
   p += align_up(solver_bytes);
@@ -160,7 +167,12 @@ size_t solver_query(bb_context ctx, int n) {
   rocsolver_zhegvd(ctx->rb, rocblas_eform_ax, rocblas_evect_original, rocblas_fill_lower, n, nullptr, n, nullptr, n,
                    nullptr, nullptr, nullptr);
   if (rocblas_stop_device_memory_size_query(ctx->rb, &sz) != rocblas_status_success) return 0;
-  return sz;
+  // the tridiagonal solver alone (the library's part of the solve up to kEigMaxN antennas)
+  size_t tri = 0;
+  if (rocblas_start_device_memory_size_query(ctx->rb) != rocblas_status_success) return 0;
+  rocsolver_dstedc(ctx->rb, rocblas_evect_tridiagonal, n, nullptr, nullptr, nullptr, n, nullptr);
+  if (rocblas_stop_device_memory_size_query(ctx->rb, &tri) != rocblas_status_success) return 0;
+  return std::max(sz, tri);
 }
 
 __global__ void write_meta_kernel(SingleMeta* dst, InstDesc d, int slot) {
@@ -499,33 +511,79 @@ static bb_status parse_intervals(bb_context ctx, const double* intervals, int nl
   return BB_OK;
 }
 
-// FP64 pre-step shared by bb_synth_collect and bb_synth_prestep: Gram,
-// generalized eigensolve, selection; leaves weights / level ids / column map
-// in the workspace.  Waits for the eigensolver status.
-// With energy_fraction > 0, n_eig is chosen from the eigenvalues (fewest
-// leading eigenpairs reaching that fraction of the positive eigenvalues' sum,
-// at most k_max) and returned through n_eig_used.
-// With a beamforming matrix W_bf (n_ant x n_beam), the eigenproblem is the
-// beamformed one (V^W, W_bf^H G W_bf) of size n_beam and the eigenvectors
+// ||V - V^H||_F <= 1e-12 ||V||_F, squared; NaN fails too.
+static bb_status check_hermitian(bb_context ctx, double diff2, double norm2) {
+  if (diff2 <= 1e-24 * norm2) return BB_OK;
+  return fail(ctx, BB_ERR_INVALID_ARG, "visibility matrix is not Hermitian (||V - V^H|| / ||V|| = %.3g)",
+              std::sqrt(diff2 / norm2));
+}
+
+// The eigenproblem of one instance with the library's kernels (eigen.hip) and
+// rocSOLVER's tridiagonal solver: eigenvalues ascending in the evals region,
+// eigenvectors in the A region.  Waits for the status.  `late` (with BB_OK) when
+// the workgroups of the tridiagonalisation could not run together in time:
+// nothing is computed then, and the caller takes the other solver.
+static bb_status solve_eigen(bb_synth h, int n, double wavelength_m, const double* ant_xyz, const double* vis,
+                             std::vector<double>* evals_host, bool& late) {
+  bb_context ctx = h->ctx;
+  hipStream_t s = ctx->stream;
+  const Layout& L = h->lay;
+  const bool identity = h->opt.gram == BB_GRAM_IDENTITY;
+  bb::EigBuffers b{};
+  b.A = at<double>(h, L.A);
+  b.G = at<double>(h, L.G);
+  b.Y = b.G + (size_t)n * n;
+  b.T = at<double>(h, L.T);
+  b.U = at<double>(h, L.U);
+  b.D = at<double>(h, L.evals);
+  b.E = at<double>(h, L.E);
+  b.tau = at<double>(h, L.tau);
+  b.pub = at<uint64_t>(h, L.pub);
+  b.status = at<bb::EigStatus>(h, L.status);
+  BB_HIP(ctx, bb::launch_eig_reduce(b, ant_xyz, vis, n, wavelength_m, identity, s));
+  rocblas_set_stream(ctx->rb, s);
+  if (L.solver_bytes > 0 && rocblas_set_workspace(ctx->rb, h->ws + L.solver, L.solver_bytes) != rocblas_status_success)
+    return fail(ctx, BB_ERR_DEVICE, "rocblas_set_workspace failed");
+  const rocblas_status rs = rocsolver_dstedc(ctx->rb, rocblas_evect_tridiagonal, n, b.D, b.E, b.T, n, &b.status->stedc);
+  if (L.solver_bytes > 0) rocblas_set_workspace(ctx->rb, nullptr, 0);
+  if (rs == rocblas_status_memory_error) return fail(ctx, BB_ERR_WORKSPACE, "rocSOLVER workspace too small");
+  if (rs != rocblas_status_success) return fail(ctx, BB_ERR_DEVICE, "rocsolver_dstedc status %d", (int)rs);
+  BB_HIP(ctx, bb::launch_eig_vectors(b, n, identity, s));
+  BB_HIP(ctx, hipEventRecord(h->ev[1], s));
+  bb::EigStatus st{};
+  BB_HIP(ctx, hipMemcpyAsync(&st, b.status, sizeof st, hipMemcpyDeviceToHost, s));
+  if (evals_host) {
+    evals_host->resize(n);
+    BB_HIP(ctx, hipMemcpyAsync(evals_host->data(), b.D, sizeof(double) * n, hipMemcpyDeviceToHost, s));
+  }
+  BB_HIP(ctx, hipStreamSynchronize(s));
+  double diff2 = 0.0, norm2 = 0.0;
+  for (int i = 0; i < bb::kHermParts; ++i) {
+    diff2 += st.herm[2 * i];
+    norm2 += st.herm[2 * i + 1];
+  }
+  const bb_status hs = check_hermitian(ctx, diff2, norm2);
+  if (hs != BB_OK) return hs;
+  if (st.chol != 0) return fail(ctx, BB_ERR_NOT_POSDEF, "Gram matrix not positive definite (leading minor %d)", st.chol);
+  late = (st.trd & bb::kTrdLate) != 0;
+  if (late) return BB_OK;
+  if (st.trd & bb::kTrdNotFinite) return fail(ctx, BB_ERR_EIGEN, "tridiagonal matrix not finite");
+  if (st.stedc != 0) return fail(ctx, BB_ERR_EIGEN, "eigensolver did not converge (info %d)", st.stedc);
+  return BB_OK;
+}
+
+// The same by rocSOLVER's zhegvd alone: matrices beyond kEigMaxN, and the
+// beamformed problem (V^W, W_bf^H G W_bf) of size n_beam, whose eigenvectors
 // are mapped back to antennas, U = W_bf alpha (left in the U region).
-static bb_status run_prestep(bb_synth h, int32_t n_ant, double wavelength_m, const double* ant_xyz,
-                             const double* vis, int32_t n_eig, const double* intervals,
-                             double energy_fraction = 0.0, int32_t* n_eig_used = nullptr,
-                             const double* W_bf = nullptr, int32_t n_beam = 0) {
+static bb_status solve_eigen_library(bb_synth h, int32_t n_ant, double wavelength_m, const double* ant_xyz,
+                                     const double* vis, std::vector<double>* evals_host, const double* W_bf,
+                                     int32_t n_beam) {
   bb_context ctx = h->ctx;
   const int n_sys = W_bf ? n_beam : n_ant;  // size of the eigenproblem
-  if (energy_fraction <= 0.0 && n_eig > n_ant) return fail(ctx, BB_ERR_INVALID_ARG, "n_eig %d > n_ant %d", n_eig, n_ant);
-  if (!ant_xyz || !vis || !intervals) return fail(ctx, BB_ERR_INVALID_ARG, "null pointer");
-  const int nl = h->opt.n_levels;
-  bb::Intervals iv{};
-  bb_status ist = parse_intervals(ctx, intervals, nl, iv);
-  if (ist != BB_OK) return ist;
-  BB_HIP(ctx, hipSetDevice(ctx->device));
   hipStream_t s = ctx->stream;
   const Layout& L = h->lay;
   double* A = at<double>(h, L.A);
   double* G = at<double>(h, L.G);
-  BB_HIP(ctx, hipEventRecord(h->ev[0], s));
   BB_HIP(ctx, bb::launch_gram(ant_xyz, n_ant, n_ant, wavelength_m, G, n_ant, h->opt.gram == BB_GRAM_IDENTITY, s));
   BB_HIP(ctx, bb::launch_copy_c128(vis, n_sys, A, n_sys, s));
   double* herm = reinterpret_cast<double*>(h->ws + L.info + 16);  // two doubles beside the solver status
@@ -563,20 +621,56 @@ static bb_status run_prestep(bb_synth h, int32_t n_ant, double wavelength_m, con
   BB_HIP(ctx, hipEventRecord(h->ev[1], s));
   rocblas_int info = 0;
   double herm_host[2] = {0.0, 0.0};
-  std::vector<double> ev;
   BB_HIP(ctx, hipMemcpyAsync(&info, at<rocblas_int>(h, L.info), sizeof info, hipMemcpyDeviceToHost, s));
   BB_HIP(ctx, hipMemcpyAsync(herm_host, herm, sizeof herm_host, hipMemcpyDeviceToHost, s));
-  if (energy_fraction > 0.0) {
-    ev.resize(n_sys);
-    BB_HIP(ctx, hipMemcpyAsync(ev.data(), at<double>(h, L.evals), sizeof(double) * n_sys, hipMemcpyDeviceToHost, s));
+  if (evals_host) {
+    evals_host->resize(n_sys);
+    BB_HIP(ctx, hipMemcpyAsync(evals_host->data(), at<double>(h, L.evals), sizeof(double) * n_sys,
+                               hipMemcpyDeviceToHost, s));
   }
   BB_HIP(ctx, hipStreamSynchronize(s));
-  // ||V - V^H||_F <= 1e-12 ||V||_F, squared; NaN fails too
-  if (!(herm_host[0] <= 1e-24 * herm_host[1]))
-    return fail(ctx, BB_ERR_INVALID_ARG, "visibility matrix is not Hermitian (||V - V^H|| / ||V|| = %.3g)",
-                std::sqrt(herm_host[0] / herm_host[1]));
+  const bb_status hs = check_hermitian(ctx, herm_host[0], herm_host[1]);
+  if (hs != BB_OK) return hs;
   if (info > n_sys) return fail(ctx, BB_ERR_NOT_POSDEF, "Gram matrix not positive definite (leading minor %d)", info - n_sys);
   if (info != 0) return fail(ctx, BB_ERR_EIGEN, "eigensolver did not converge (info %d)", info);
+  return BB_OK;
+}
+
+// FP64 pre-step shared by bb_synth_collect and bb_synth_prestep: Gram,
+// generalized eigensolve, selection; leaves weights / level ids / column map
+// in the workspace.  Waits for the eigensolver status.
+// With energy_fraction > 0, n_eig is chosen from the eigenvalues (fewest
+// leading eigenpairs reaching that fraction of the positive eigenvalues' sum,
+// at most k_max) and returned through n_eig_used.
+// With a beamforming matrix W_bf (n_ant x n_beam), the eigenproblem is the
+// beamformed one of size n_beam.
+static bb_status run_prestep(bb_synth h, int32_t n_ant, double wavelength_m, const double* ant_xyz,
+                             const double* vis, int32_t n_eig, const double* intervals,
+                             double energy_fraction = 0.0, int32_t* n_eig_used = nullptr,
+                             const double* W_bf = nullptr, int32_t n_beam = 0) {
+  bb_context ctx = h->ctx;
+  const int n_sys = W_bf ? n_beam : n_ant;  // size of the eigenproblem
+  if (energy_fraction <= 0.0 && n_eig > n_ant) return fail(ctx, BB_ERR_INVALID_ARG, "n_eig %d > n_ant %d", n_eig, n_ant);
+  if (!ant_xyz || !vis || !intervals) return fail(ctx, BB_ERR_INVALID_ARG, "null pointer");
+  const int nl = h->opt.n_levels;
+  bb::Intervals iv{};
+  bb_status ist = parse_intervals(ctx, intervals, nl, iv);
+  if (ist != BB_OK) return ist;
+  BB_HIP(ctx, hipSetDevice(ctx->device));
+  hipStream_t s = ctx->stream;
+  const Layout& L = h->lay;
+  BB_HIP(ctx, hipEventRecord(h->ev[0], s));
+  std::vector<double> ev;
+  std::vector<double>* const evp = energy_fraction > 0.0 ? &ev : nullptr;
+  bool library = W_bf || n_sys < 2 || n_sys > bb::kEigMaxN;
+  if (!library) {
+    ist = solve_eigen(h, n_sys, wavelength_m, ant_xyz, vis, evp, library);
+    if (ist != BB_OK) return ist;
+  }
+  if (library) {
+    ist = solve_eigen_library(h, n_ant, wavelength_m, ant_xyz, vis, evp, W_bf, n_beam);
+    if (ist != BB_OK) return ist;
+  }
   if (energy_fraction > 0.0) {
     // eigenvalues ascending: walk from the largest (Section 2.6 truncation by energy)
     double total = 0.0;

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace bb {
@@ -140,6 +141,37 @@ hipError_t launch_select_export_batched(const double* A, const double* evals, in
 hipError_t launch_export_eig(const double* A_c128, const double* evals, int L, int K, const int* wcol,
                              const float* dsel, const int* lsel, float* W_out_c64, double* lam_out, float* d_out,
                              int* lev_out, hipStream_t s);
+
+// Generalized eigenproblem of one instance (eigen.hip), 2 <= n <= kEigMaxN.
+constexpr int kEigMaxN = 512;
+constexpr int kHermParts = 64;       // workgroups (partial sums) of the Hermiticity check
+constexpr int kTrdLate = 1;          // EigStatus::trd: a wait between workgroups ran out (nothing computed)
+constexpr int kTrdNotFinite = 2;     // the tridiagonal matrix is not finite
+struct EigStatus {
+  int chol;                          // 0, or the first leading minor of G that is not positive
+  int trd;
+  int stedc;                         // the tridiagonal solver's info
+  int pad;
+  double herm[2 * kHermParts];       // sums of ||V - V^H||_F^2 and ||V||_F^2, to be added in order
+};
+struct EigBuffers {
+  double* A;       // n x n complex128: V, C, the reflectors, at last the eigenvectors
+  double* G;       // n x n: Gram matrix, then its factor below the diagonal blocks
+  double* Y;       // n x n: inverse factor
+  double* T;       // n x n complex128 scratch; n x n float64 eigenvectors of the tridiagonal matrix
+  double* U;       // n x n complex128 scratch
+  double* D;       // n diagonal
+  double* E;       // n off-diagonal
+  double* tau;     // n complex128
+  uint64_t* pub;   // eig_pub_bytes()
+  EigStatus* status;
+};
+size_t eig_pub_bytes();
+// Inputs (ant n x 3 column-major, vis n x n complex128) to the tridiagonal matrix (D, E).
+hipError_t launch_eig_reduce(const EigBuffers& b, const double* ant, const double* vis, int n, double wl,
+                             bool identity, hipStream_t s);
+// Eigenvectors in A from those of the tridiagonal matrix in T.
+hipError_t launch_eig_vectors(const EigBuffers& b, int n, bool identity, hipStream_t s);
 
 // Level determination and weighting (levels_weighting.hip).
 hipError_t launch_kmeans_levels(const double* lam, int n, int k, int negative_level, double* intervals,

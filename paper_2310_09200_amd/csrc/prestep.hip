@@ -1,7 +1,7 @@
-// FP64 pre-step of one instance (Algorithm 1 up to the synthesis call):
-// Gram matrix, copy of V for the in-place eigensolver, and selection of the
-// kept eigenpairs with their filter weights and level ids.  The generalized
-// eigensolve itself is rocSOLVER's zhegvd, called from the host API.
+// FP64 pre-step (Algorithm 1 up to the synthesis call): inputs of rocSOLVER's
+// zhegvd, called from the host API for batches, beamforming and matrices beyond
+// the reach of eigen.hip (Gram matrix, copy of V for the in-place solver), and
+// selection of the kept eigenpairs with their filter weights and level ids.
 
 #include <hip/hip_runtime.h>
 #include <math.h>
