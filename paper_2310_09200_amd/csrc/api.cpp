@@ -947,8 +947,9 @@ bb_status bb_synth_levels_kmeans(bb_synth h, int32_t n, const double* lam, int32
   if (k < 1) return fail(ctx, BB_ERR_INVALID_ARG, "no positive level left (n_levels %d)", h->opt.n_levels);
   if (!lam || !intervals || !level_of) return fail(ctx, BB_ERR_INVALID_ARG, "null device pointer");
   BB_HIP(ctx, hipSetDevice(ctx->device));
+  // the run costs go to the pre-step matrices' region (free between calls) where they fit
   BB_HIP(ctx, bb::launch_kmeans_levels(lam, n, k, negative_level, intervals, level_of, at<int>(h, h->lay.err),
-                                       ctx->stream));
+                                       h->ws + h->lay.A, h->lay.evals - h->lay.A, ctx->stream));
   return BB_OK;
 }
 

@@ -174,8 +174,9 @@ hipError_t launch_eig_reduce(const EigBuffers& b, const double* ant, const doubl
 hipError_t launch_eig_vectors(const EigBuffers& b, int n, bool identity, hipStream_t s);
 
 // Level determination and weighting (levels_weighting.hip).
+// scratch: n x n doubles make it faster (may be smaller, or null with 0 bytes).
 hipError_t launch_kmeans_levels(const double* lam, int n, int k, int negative_level, double* intervals,
-                                int* level_of, int* err, hipStream_t s);
+                                int* level_of, int* err, void* scratch, size_t scratch_bytes, hipStream_t s);
 struct UvFrame {
   double eu[3], ev[3];  // image-plane axes at the phase centre
   double scale;         // FoV / wavelength: cells per metre of baseline
