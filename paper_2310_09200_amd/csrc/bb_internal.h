@@ -305,7 +305,7 @@ constexpr int kGatherRecBytes = 128;  // per sorted baseline
 hipError_t launch_nufft_spread_gather(const NufftGeom& g, const NufftInst* insts, int64_t max_src, const double* ant,
                                       int64_t ld, const void* vp, const int* offset, const uint64_t* list,
                                       int n_levels, void* rec, void* cv, int* nparts, int* part_off, int* scan_tmp,
-                                      float* grid, int64_t n_cell, hipStream_t s);
+                                      bool fresh, float* grid, int64_t n_cell, hipStream_t s);
 // nch, choff: n_tiles and n_tiles + 1 ints of scratch (chunks per tile and their offsets).
 hipError_t launch_nufft_spread_tiles(const NufftGeom& g, const NufftInst* insts, const double* ant, int64_t ld,
                                      const void* vp, const int* offset, const uint64_t* list, int bin, int n_levels,

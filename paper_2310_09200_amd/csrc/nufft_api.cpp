@@ -335,6 +335,7 @@ struct bb_nufft_ {
   FftPlans plans;
   rocfft_execution_info info = nullptr;
   int64_t count = 0;  // instances spread since the last emit
+  bool dirty = false;  // a spread was launched since the grid was cleared
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   bool spread_timed = false, emit_timed = false;
 };
@@ -904,14 +905,16 @@ bb_status bb_nufft_collect_eig_batched(bb_nufft h, int32_t n_inst, const bb_inst
     BB_HIP(ctx, bb::launch_nufft_bin(h->g, d_inst, n_inst, max_ant, ant_xyz_packed, n_ant_rows, cl.bin, count, offset,
                                      cursor, list, pnat<int>(h, h->lay.err), scan_tmp, s));
   }
+  const bool was_dirty = h->dirty;
+  h->dirty = true;
   if (cl.mode == 2) {
     BB_HIP(ctx, bb::launch_nufft_spread_gather(h->g, d_inst, cl.pairs, ant_xyz_packed, n_ant_rows, ws + cl.vp,
                                                reinterpret_cast<int*>(ws + cl.offset),
                                                reinterpret_cast<uint64_t*>(ws + cl.list), n_levels, ws + cl.rec,
                                                ws + cl.cv, reinterpret_cast<int*>(ws + cl.nparts),
                                                reinterpret_cast<int*>(ws + cl.part_off),
-                                               reinterpret_cast<int*>(ws + cl.scan_tmp), tnat<float>(h, h->lay.grid),
-                                               n_cell, s));
+                                               reinterpret_cast<int*>(ws + cl.scan_tmp), !was_dirty,
+                                               tnat<float>(h, h->lay.grid), n_cell, s));
   } else if (cl.mode == 1) {
     const int* offset = reinterpret_cast<int*>(ws + cl.offset);
     const uint64_t* list = reinterpret_cast<uint64_t*>(ws + cl.list);
@@ -990,6 +993,7 @@ bb_status bb_nufft_emit(bb_nufft h) {
                                         h->images + (int64_t)lv * h->n_pix, s));
   }
   BB_HIP(ctx, bb::launch_fill_zero(tnat<float>(h, h->lay.grid), 2 * n_cell * h->opt.n_levels, s));
+  h->dirty = false;
   BB_HIP(ctx, bb::launch_fill_zero_f64(pnat<double>(h, h->lay.diag), bb::kMaxLevels, s));
   BB_HIP(ctx, hipEventRecord(h->ev[3], s));
   h->emit_timed = true;
