@@ -256,6 +256,7 @@ struct LineFft {
   int64_t t_inner;       // out_mode 1: line = outer * t_inner + inner, stored at [outer][w][inner]
   int out_mode;          // 0: out[line * out_stride + w]
   int direct;            // 1: a direct pruned DFT per line (L <= kLineDftMax) from a table
+  int reg;               // plan of the transform in registers (-1: none for this length)
 };
 // Fills L, n_pass, radix_codes and nl; -1 if L is not 2,3,5-smooth or exceeds kLineFftMax.
 int line_fft_plan(int L, LineFft& p);
@@ -263,7 +264,8 @@ size_t line_fft_lds_bytes(const LineFft& p);  // dynamic LDS of a launch
 // Load position of each input index of a planned length (p.L ints): the digit
 // reversal the in-place passes need.
 void line_fft_perm(const LineFft& p, int* perm);
-// The passes' twiddles of a planned length (2 (p.L - 1) floats, complex64).
+// The passes' twiddles of a planned line (complex64, at most line_fft_twiddle_points(p.L)).
+size_t line_fft_twiddle_points(int L);
 void line_fft_twiddles(const LineFft& p, float* tw);
 hipError_t launch_line_fft(const LineFft& p, const void* in, const float* inv_psi, const int* perm, const float2* tw,
                            void* out, hipStream_t s);

@@ -278,7 +278,7 @@ NufftLayout nufft_layout(const bb::NufftGeom& g, int n_levels, int64_t n_pix, si
       l.perm[d] = p;
       p += align_up(4 * (size_t)g.M[d]);
       l.tw[d] = p;
-      p += align_up(8 * (size_t)g.M[d]);
+      p += align_up(8 * bb::line_fft_twiddle_points(g.M[d]));
       l.dft[d] = p;
       if (g.M[d] <= bb::kLineDftMax) p += align_up(8 * (size_t)g.N[d] * g.win_len[d]);
     }
@@ -636,7 +636,7 @@ bb_status create_one(bb_context ctx, const bb_nufft_options* opt, int64_t n_pix,
     for (int d = 0; d < 3; ++d) {
       perm[d].resize(g.M[d]);
       bb::line_fft_perm(h->lf[2 - d], perm[d].data());
-      tw[d].assign(2 * (size_t)g.M[d], 0.0f);
+      tw[d].assign(2 * bb::line_fft_twiddle_points(g.M[d]), 0.0f);
       bb::line_fft_twiddles(h->lf[2 - d], tw[d].data());
       if (h->lf[2 - d].direct) {
         dft[d].assign(2 * (size_t)g.N[d] * g.win_len[d], 0.0f);

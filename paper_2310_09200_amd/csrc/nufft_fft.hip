@@ -1,20 +1,25 @@
-// Line FFTs of the NUFFT's pruned type-2 transform (gfx950).  Lines of at
-// most 64 points (the thin axis of a grid) are instead a direct pruned DFT on
-// MFMA (line_dft_kernel, at the end of this file).
+// Line FFTs of the NUFFT's pruned type-2 transform (gfx950): of a line's L = M
+// points N <= M are stored (index i holds frequency i for i < N/2, else i - N;
+// the others are zero), each is divided by the axis's kernel transform on load,
+// and of the inverse DFT X[m] = sum_n x[n] exp(+2 pi i n m / M) (unnormalised)
+// only the window (lo + w) mod M, w < len, is kept.  Three kernels:
 //
+//   line_reg_kernel   lengths that are products of two or three radices up to 20
+//                     (most 2,3,5-smooth lengths up to 8000): a butterfly per
+//                     thread and pass, in registers;
+//   line_fft_kernel   any other 2,3,5-smooth length up to 16384, in place in LDS;
+//   line_dft_kernel   at most 64 points (the thin axis of a grid): a direct
+//                     pruned DFT on MFMA.
+//
+// line_fft_kernel:
 // Each workgroup transforms one or more lines of L = M points held in LDS
-// (L 2,3,5-smooth, at most 16384).  A line's N stored inputs are placed at
-// their frequencies' positions (index i holds frequency i for i < N/2, else
-// i - N) and divided by the axis's kernel transform on load; the other M - N
-// positions are zero.  The inverse DFT X[m] = sum_n x[n] exp(+2 pi i n m / M)
-// (unnormalised) is done in place by mixed-radix decimation in time (radix 8,
+// (L 2,3,5-smooth, at most 16384), in place by mixed-radix decimation in time (radix 8,
 // 4, 2, 3, 5 in the order R_0, R_1, ...): pass s combines R_s transforms of
 // length Ns = R_0 ... R_{s-1} that sit Ns apart into one of length P = Ns R_s,
 // each butterfly reading and writing the same R_s points (twiddles
 // exp(2 pi i k r / P)).  For that the load puts input n at the digit-reversed
 // position sum_s r_s Ns_s, where n = r_{S-1} + R_{S-1} (r_{S-2} + R_{S-2} (...)),
-// from a table made on the host.  Only a window of outputs, positions
-// (lo + w) mod M for w < len, is stored.  One LDS buffer of L x 8 bytes per
+// from a table made on the host.  One LDS buffer of L x 8 bytes per
 // line.  Twiddles come from a table made in FP64 on the host: pass s keeps
 // its Ns (R_s - 1) values exp(2 pi i k r / P), k < Ns, 1 <= r < R_s, at
 // offset Ns - 1 (the earlier passes hold sum (P - Ns) = Ns - 1 of them), so
@@ -27,6 +32,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <utility>
 
 #include "bb_internal.h"
 
@@ -113,6 +119,91 @@ __device__ __forceinline__ void small_dft<5>(float2 (&v)[5]) {
   v[2] = cadd(r2, j2);
   v[3] = csub(r2, j2);
 }
+
+// Composite sizes R = A B with A, B coprime (no twiddles): with inputs
+// n = B n1 + A n2 and outputs k = k1 mod A = k2 mod B (both mod R),
+// exp(2 pi i n k / R) = exp(2 pi i n1 k1 / A) exp(2 pi i n2 k2 / B).
+template <int A, int B>
+__device__ __forceinline__ void coprime_dft(float2 (&v)[A * B]) {
+  constexpr int R = A * B;
+  float2 y[A][B];
+#pragma unroll
+  for (int n2 = 0; n2 < B; ++n2) {
+    float2 x[A];
+#pragma unroll
+    for (int n1 = 0; n1 < A; ++n1) x[n1] = v[(B * n1 + A * n2) % R];
+    small_dft<A>(x);
+#pragma unroll
+    for (int k1 = 0; k1 < A; ++k1) y[k1][n2] = x[k1];
+  }
+#pragma unroll
+  for (int k1 = 0; k1 < A; ++k1) {
+    small_dft<B>(y[k1]);
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+      if (k % A == k1) v[k] = y[k1][k % B];
+  }
+}
+
+template <>
+__device__ __forceinline__ void small_dft<9>(float2 (&v)[9]) {
+  // exp(2 pi i p / 9) for p = 1, 2, 4
+  constexpr float2 w1 = {0.76604444311897803520f, 0.64278760968653932632f};
+  constexpr float2 w2 = {0.17364817766693034885f, 0.98480775301220805937f};
+  constexpr float2 w4 = {-0.93969262078590838405f, 0.34202014332566873304f};
+  float2 y[3][3];  // [k1][n2]
+#pragma unroll
+  for (int n2 = 0; n2 < 3; ++n2) {
+    float2 x[3] = {v[n2], v[3 + n2], v[6 + n2]};
+    small_dft<3>(x);
+#pragma unroll
+    for (int k1 = 0; k1 < 3; ++k1) y[k1][n2] = x[k1];
+  }
+  y[1][1] = cmul(y[1][1], w1);
+  y[2][1] = cmul(y[2][1], w2);
+  y[1][2] = cmul(y[1][2], w2);
+  y[2][2] = cmul(y[2][2], w4);
+#pragma unroll
+  for (int k1 = 0; k1 < 3; ++k1) {
+    small_dft<3>(y[k1]);
+#pragma unroll
+    for (int k2 = 0; k2 < 3; ++k2) v[k1 + 3 * k2] = y[k1][k2];
+  }
+}
+
+template <>
+__device__ __forceinline__ void small_dft<16>(float2 (&v)[16]) {
+  constexpr float c = 0.92387953251128675613f, s = 0.38268343236508977173f;  // cos, sin of pi / 8
+  constexpr float h = 0.70710678118654752440f;
+  constexpr float2 w[10] = {{1, 0}, {c, s}, {h, h}, {s, c}, {0, 1}, {-s, c}, {-h, h}, {-c, s}, {-1, 0}, {-c, -s}};
+  float2 y[4][4];  // [k1][n2]
+#pragma unroll
+  for (int n2 = 0; n2 < 4; ++n2) {
+    float2 x[4] = {v[n2], v[4 + n2], v[8 + n2], v[12 + n2]};
+    small_dft<4>(x);
+#pragma unroll
+    for (int k1 = 0; k1 < 4; ++k1) y[k1][n2] = n2 * k1 == 0 ? x[k1] : n2 * k1 == 4 ? mul_i(x[k1]) : cmul(x[k1], w[n2 * k1]);
+  }
+#pragma unroll
+  for (int k1 = 0; k1 < 4; ++k1) {
+    small_dft<4>(y[k1]);
+#pragma unroll
+    for (int k2 = 0; k2 < 4; ++k2) v[k1 + 4 * k2] = y[k1][k2];
+  }
+}
+
+template <>
+__device__ __forceinline__ void small_dft<6>(float2 (&v)[6]) { coprime_dft<2, 3>(v); }
+template <>
+__device__ __forceinline__ void small_dft<10>(float2 (&v)[10]) { coprime_dft<2, 5>(v); }
+template <>
+__device__ __forceinline__ void small_dft<12>(float2 (&v)[12]) { coprime_dft<4, 3>(v); }
+template <>
+__device__ __forceinline__ void small_dft<15>(float2 (&v)[15]) { coprime_dft<3, 5>(v); }
+template <>
+__device__ __forceinline__ void small_dft<18>(float2 (&v)[18]) { coprime_dft<2, 9>(v); }
+template <>
+__device__ __forceinline__ void small_dft<20>(float2 (&v)[20]) { coprime_dft<4, 5>(v); }
 
 // floor(j / d) for 0 <= j, 1 <= d <= 16384, given inv_d = 1 / d in FP32.
 __device__ __forceinline__ int quot(int j, float inv_d) { return (int)(((float)j + 0.5f) * inv_d); }
@@ -215,6 +306,198 @@ __global__ __launch_bounds__(T) void line_fft_kernel(LineFft p, const float2* __
     }
     __syncthreads();  // the lines are reused by the next group
   }
+}
+
+// L = R1 R2 R3 (R2 = 1: two passes), self-sorting: the pass of radix R after
+// passes of product Ns takes the points j + r L / R of butterfly j < L / R, times
+// exp(2 pi i r (j mod Ns) / (Ns R)), and leaves output q at (j div Ns) Ns R +
+// j mod Ns + q Ns.  The first pass reads the line from memory (a butterfly's
+// points at a stride of L / R1: whole cache lines over the threads) and the last
+// one writes the window to memory, so LDS sees each point once per pass between
+// them and nothing is zeroed, placed or copied out.  There it is held in rows of
+// R1 points P1 apart, and after the second pass of R1 R2 points P2 apart: P1 odd,
+// and P2 = R1 modulo 32, which spreads the strided writes over the banks and
+// leaves every read a constant stride.  A butterfly of every pass per thread; the
+// last pass's twiddles are requested before the barrier that it waits at.  The
+// radices are constants: with a switch over them addresses and windows took as
+// many instructions as the butterflies (360 us).
+//
+// 32 k lines of 3200 or 3240 points, half of them stored and half kept (0.83 GB,
+// 0.17 ms): 250 us, the vector units 70 % busy; 440 and 540 us in line_fft_kernel
+// (six or seven passes through LDS with bank conflicts in the early ones).  A
+// workgroup takes one set of lines: as a loop over lines with the twiddles kept
+// (in LDS or registers) fewer workgroups fit a CU and it took 500 us.
+template <int R1, int R2, int R3>
+struct RegGeom {
+  static constexpr int L = R1 * R2 * R3;
+  static constexpr int S1 = L / R1, S2 = L / R2, S3 = R1 * R2;  // butterflies of the passes
+  static constexpr int T = std::max(std::max(S1, S3), R2 > 1 ? S2 : 0);
+  static constexpr int NL = std::max(1, 256 / T);  // lines per workgroup
+  static constexpr int TPB = (NL * T + 63) / 64 * 64;
+  // waves per SIMD: a radix above 16 needs more than the 96 registers of five
+  static constexpr int WAVES = std::max(std::max(R1, R2), R3) > 16 ? 4 : 5;
+  static constexpr int P1 = R1 | 1;
+  static constexpr int P2 = R2 == 1 ? P1 : S3 + ((R1 - S3) % 32 + 32) % 32;
+  static constexpr int POINTS = std::max(S1 * P1, R2 == 1 ? 0 : R3 * P2);  // of LDS per line
+  static constexpr size_t LDS = ((size_t)NL * POINTS + (R2 > 1 ? S3 : 0)) * sizeof(float2);
+};
+
+template <int R1, int R2, int R3>
+__global__ __launch_bounds__((RegGeom<R1, R2, R3>::TPB), (RegGeom<R1, R2, R3>::WAVES)) void line_reg_kernel(LineFft p,
+                                                                                 const float2* __restrict__ in,
+                                                                                 const float* __restrict__ inv_psi,
+                                                                                 const float2* __restrict__ tw,
+                                                                                 float2* __restrict__ out) {
+  using G = RegGeom<R1, R2, R3>;
+  constexpr int L = G::L, S1 = G::S1, S2 = G::S2, S3 = G::S3, P1 = G::P1, P2 = G::P2, NL = G::NL;
+  extern __shared__ float2 s_line[];  // NL lines, then the second pass's twiddles
+  float2* const s_tw = s_line + NL * G::POINTS;
+  const int n_in = p.n_in, half = n_in / 2, gap = L - n_in, lo = p.win_lo;
+  const unsigned wl = p.win_len;
+  const int line_t = NL == 1 ? 0 : (int)threadIdx.x / G::T;
+  const int j = threadIdx.x - line_t * G::T;
+  float2* const s = s_line + line_t * G::POINTS;
+  const unsigned in_off = line_t * (unsigned)p.in_stride, out_off = line_t * (unsigned)p.out_stride;
+  if constexpr (R2 > 1) {
+    for (int i = threadIdx.x; i < S3; i += G::TPB) s_tw[i] = tw[i];
+    tw += S3;
+  }
+  const int64_t line0 = (int64_t)blockIdx.x * NL;
+  const bool live = j < G::T && line_t < min((int64_t)NL, p.n_lines - line0);
+  const float2* const src = in + line0 * p.in_stride;
+  float2* const dst = out + line0 * p.out_stride;
+  {
+    const bool act = live && j < S1;
+    float2 v[R1];
+    if (act) {
+      float sc[R1];
+#pragma unroll
+      for (int r = 0; r < R1; ++r) {  // all requested before the first is used; input 0 where none is stored
+        const int m = j + r * S1;
+        const bool stored = m < half || m >= L - half;
+        const unsigned i = !stored ? 0 : m < half ? m : m - gap;
+        v[r] = src[in_off + i];
+        sc[r] = inv_psi[i];
+        if (!stored) sc[r] = 0.0f;
+      }
+#pragma unroll
+      for (int r = 0; r < R1; ++r) v[r] = make_float2(v[r].x * sc[r], v[r].y * sc[r]);
+      small_dft<R1>(v);
+    }
+    if (act)
+#pragma unroll
+      for (int q = 0; q < R1; ++q) s[j * P1 + q] = v[q];
+  }
+  if constexpr (R2 > 1) {
+    __syncthreads();
+    const bool act = live && j < S2;
+    const int g = j / R1, k = j - g * R1;
+    float2 v[R2];
+    if (act) {
+#pragma unroll
+      for (int r = 0; r < R2; ++r) v[r] = s[g * P1 + k + r * (R3 * P1)];  // S2 = R1 R3 points: R3 rows
+#pragma unroll
+      for (int r = 1; r < R2; ++r) v[r] = cmul(v[r], s_tw[r * R1 + k]);
+      small_dft<R2>(v);
+    }
+    __syncthreads();
+    if (act)
+#pragma unroll
+      for (int q = 0; q < R2; ++q) s[g * P2 + k + q * R1] = v[q];
+  }
+  const bool act = live && j < S3;
+  float2 t[R3], v[R3];
+  if (act)
+#pragma unroll
+    for (int r = 1; r < R3; ++r) t[r] = tw[(unsigned)(r * S3 + j)];
+  __syncthreads();
+  if (act) {
+#pragma unroll
+    for (int r = 0; r < R3; ++r) v[r] = s[j + r * P2];
+#pragma unroll
+    for (int r = 1; r < R3; ++r) v[r] = cmul(v[r], t[r]);
+    small_dft<R3>(v);
+#pragma unroll
+    for (int q = 0; q < R3; ++q) {
+      const int m = j + q * S3 - lo;
+      const unsigned w = min((unsigned)m, (unsigned)(m + L));  // m mod L
+      if (w < wl) dst[out_off + w] = v[q];
+    }
+  }
+}
+
+// The lengths' radices: two if possible, then the fewest threads per line (the
+// largest count of butterflies of a pass) for the fewest idle ones, then an odd
+// first radix (no padding).  Radices up to 20 keep a pass within 96 registers.
+constexpr int kRegRadices[] = {4, 5, 6, 8, 9, 10, 12, 15, 16, 18, 20};
+constexpr int kRegMax = 8000;  // = 20^3
+struct RegPlan {
+  int L, r1, r2, r3, t;
+};
+constexpr RegPlan reg_plan(int L) {
+  RegPlan best{L, 0, 0, 0, 0};
+  int rest = L;
+  for (int f : {2, 3, 5})
+    while (rest % f == 0) rest /= f;
+  if (rest != 1) return best;
+  for (int r1 : kRegRadices)
+    for (int r3 : kRegRadices) {
+      if (L % (r1 * r3)) continue;
+      const int r2 = L / (r1 * r3);
+      bool known = r2 == 1;
+      for (int r : kRegRadices) known |= r2 == r;
+      const int t = std::max(std::max(L / r1, L / r3), r2 > 1 ? L / r2 : 0);
+      if (!known || t > 512) continue;
+      const bool first = best.t == 0, fewer = best.r2 > 1 && r2 == 1, more = best.r2 == 1 && r2 > 1;
+      if (first || fewer || (!more && (t < best.t || (t == best.t && r1 % 2 > best.r1 % 2))))
+        best = {L, r1, r2, r3, t};
+    }
+  return best;
+}
+constexpr int reg_plan_count() {
+  int n = 0;
+  for (int L = 16; L <= kRegMax; L += 4) n += reg_plan(L).t > 0;  // an axis has 2 N points, N even
+  return n;
+}
+constexpr int kRegPlanCount = reg_plan_count();
+struct RegPlans {
+  RegPlan p[kRegPlanCount];
+};
+constexpr RegPlans reg_plans() {
+  RegPlans t{};
+  int n = 0;
+  for (int L = 16; L <= kRegMax; L += 4)
+    if (const RegPlan q = reg_plan(L); q.t > 0) t.p[n++] = q;
+  return t;
+}
+constexpr RegPlans kRegPlans = reg_plans();
+
+int reg_find(int L) {
+  for (int i = 0; i < kRegPlanCount; ++i)
+    if (kRegPlans.p[i].L == L) return i;
+  return -1;
+}
+
+template <size_t I>
+hipError_t launch_reg(const LineFft& p, const float2* in, const float* inv_psi, const float2* tw, float2* out,
+                      hipStream_t s) {
+  constexpr RegPlan q = kRegPlans.p[I];
+  using G = RegGeom<q.r1, q.r2, q.r3>;
+  auto* const fn = &line_reg_kernel<q.r1, q.r2, q.r3>;
+  if (G::LDS > 65536) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::LDS);
+    if (e != hipSuccess) return e;
+  }
+  const int64_t groups = (p.n_lines + G::NL - 1) / G::NL;
+  hipLaunchKernelGGL(fn, dim3((unsigned)groups), dim3(G::TPB), G::LDS, s, p, in, inv_psi, tw, out);
+  return hipGetLastError();
+}
+template <size_t... I>
+hipError_t launch_reg_plan(int i, const LineFft& p, const float2* in, const float* inv_psi, const float2* tw, float2* out,
+                      hipStream_t s, std::index_sequence<I...>) {
+  static constexpr decltype(&launch_reg<0>) fn[] = {&launch_reg<I>...};
+  return fn[i](p, in, inv_psi, tw, out, s);
 }
 
 // out[c][r] = in[r][c] for an rows x cols matrix of complex64, 32 x 32 tiles.
@@ -404,6 +687,7 @@ int line_fft_plan(int L, LineFft& p) {
   p.radix_codes = 0;
   for (int i = 0; i < n; ++i) p.radix_codes |= (uint64_t)rad[i] << (4 * i);
   p.nl = std::max(1, 4096 / L);
+  p.reg = reg_find(L);
   return 0;
 }
 
@@ -416,7 +700,27 @@ size_t line_fft_lds_bytes(const LineFft& p) {
   return (fft_pad(p) ? n + (n >> 5) + 2 : n) * sizeof(float2);
 }
 
+// Whether line_reg_kernel transforms the planned lines.
+static bool reg_fits(const LineFft& p) { return p.reg >= 0 && p.out_mode == 0; }
+
+size_t line_fft_twiddle_points(int L) { return 2 * (size_t)L; }
+
 void line_fft_twiddles(const LineFft& p, float* tw) {
+  if (reg_fits(p)) {
+    const RegPlan& q = kRegPlans.p[p.reg];
+    const int r1 = q.r1, r2 = q.r2, r3 = q.r3;
+    auto fill = [&](int ns, int R) {  // [r][k], k < ns: exp(2 pi i r k / (ns R))
+      for (int r = 0; r < R; ++r)
+        for (int k = 0; k < ns; ++k) {
+          const double a = 2.0 * M_PI * (double)(r * k) / (ns * R);
+          *tw++ = (float)std::cos(a);
+          *tw++ = (float)std::sin(a);
+        }
+    };
+    if (r2 > 1) fill(r1, r2);
+    fill(r1 * r2, r3);
+    return;
+  }
   int ns = 1;
   for (int s = 0; s < p.n_pass; ++s) {
     const int R = (int)((p.radix_codes >> (4 * s)) & 15), P = ns * R;
@@ -452,6 +756,9 @@ void line_fft_perm(const LineFft& p, int* perm) {
 hipError_t launch_line_fft(const LineFft& p, const void* in, const float* inv_psi, const int* perm, const float2* tw,
                            void* out, hipStream_t s) {
   if (p.n_lines <= 0) return hipSuccess;
+  if (reg_fits(p))
+    return launch_reg_plan(p.reg, p, static_cast<const float2*>(in), inv_psi, tw, static_cast<float2*>(out), s,
+                      std::make_index_sequence<kRegPlanCount>{});
   const int64_t groups = (p.n_lines + p.nl - 1) / p.nl;
   const unsigned grid = (unsigned)std::min<int64_t>(groups, 1 << 16);
   const size_t lds = line_fft_lds_bytes(p);

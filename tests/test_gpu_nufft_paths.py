@@ -89,3 +89,27 @@ def test_spread_widths_and_wraps(ctx, eps, extent, calls):
     print(f"case nufft eps={eps} extent={extent} calls={calls}", flush=True)
     pix, items, frame, uvw = _case(3, extent, 8)
     _check(ctx, 3, items, pix, frame, uvw, eps, calls)
+
+
+_LENGTHS = sorted(m for m in (4 * 2 ** a * 3 ** b * 5 ** c for a in range(12) for b in range(8) for c in range(6))
+                  if 24 <= m <= 9000)
+
+
+# every transform length up to 9000: two and three passes of each radix in
+# registers, and the lengths left to the in-place transform
+@pytest.mark.parametrize("length", _LENGTHS)
+def test_line_lengths(ctx, length):
+    print(f"case nufft line length={length}", flush=True)
+    eps, w = 1e-5, 6
+    h = np.sin(np.deg2rad(10.0))
+    extent = (length / 2 - w - 0.5) / (8 * h) / 1.01
+    g = np.random.default_rng(length)
+    frame = np.array(sims.tangent_basis(40.0))
+    x = np.array([[0.0, 0, 0], [extent, 0, 0]] + [[e, 0, 0] for e in extent * g.random(4)])
+    x[1:, 1:] = 0.3 * (g.random((5, 2)) - 0.5)
+    W = (g.normal(size=(6, 6)) + 1j * g.normal(size=(6, 6))).astype(np.complex64)
+    items = [(x @ frame, 1.0, W, np.ones(6, np.float32), np.zeros(6, np.int32))]
+    pix = _pixels(10, 20.0, frame)
+    uvw = np.array([extent * 1.01, 0.35, 0.35])
+    assert nf.plan_params(eps, uvw, nf.rotate(pix, frame))["M"][0] == length
+    _check(ctx, 1, items, pix, frame, uvw, eps, 1)
