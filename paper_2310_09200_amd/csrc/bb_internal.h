@@ -223,7 +223,7 @@ struct NufftInst {
   int64_t ord_off, ls_off;  // this instance's level-grouped order and level starts
   int64_t vp_off;           // this instance's V' block (n_levels x n_ant^2 complex64)
 };
-hipError_t launch_nufft_prep(const NufftInst* insts, int n_inst, const void* W, const float* d, const int* lev,
+hipError_t launch_nufft_prep(const NufftInst* insts, int n_inst, int max_eig, const void* W, const float* d, const int* lev,
                              int n_levels, int* order, int* lstart, double* diag, int* err, hipStream_t s);
 hipError_t launch_nufft_spread(const NufftGeom& g, const NufftInst* insts, int n_inst, int max_ant,
                                const double* ant, int64_t ant_ld, const void* Wmat, const float* d, const int* order,
@@ -237,12 +237,14 @@ hipError_t launch_nufft_gather(int axis, const NufftGeom& g, const void* src, co
 struct InterpLayout {
   int64_t s1, s2;
   int lo0, len0;
+  int64_t level_stride;  // points from one level's u to the next
+  int real;              // 1: u holds real parts only
 };
 // Adds 2 Re(exp(2 pi i <s, C>) interpolated value) * corr (+ diag[lv] when
-// g.use_diag) to each pixel's level image.
+// g.use_diag) to each pixel's image of levels lv0 .. lv0 + n_lv - 1 (images: level 0's).
 hipError_t launch_nufft_interp(const NufftGeom& g, const InterpLayout& lay, const double* pix, int64_t pix_ld,
-                               int64_t n_pix, const float* u, const double* corr, const double* diag, int lv,
-                               float* image, hipStream_t s);
+                               int64_t n_pix, const float* u, const double* corr, const double* diag, int lv0,
+                               int n_lv, float* images, hipStream_t s);
 // Line FFTs of the pruned transform (nufft_fft.hip).
 constexpr int kLineFftMax = 16384;  // longest line held in LDS (128 KB)
 constexpr int kLineDftMax = 64;     // lines up to this length may be a direct pruned DFT instead
@@ -256,6 +258,7 @@ struct LineFft {
   int64_t t_inner;       // out_mode 1: line = outer * t_inner + inner, stored at [outer][w][inner]
   int out_mode;          // 0: out[line * out_stride + w]
   int direct;            // 1: a direct pruned DFT per line (L <= kLineDftMax) from a table
+  int real;              // 1: only the outputs' real parts are stored (line_real_fits)
   int reg;               // plan of the transform in registers (-1: none for this length)
 };
 // Fills L, n_pass, radix_codes and nl; -1 if L is not 2,3,5-smooth or exceeds kLineFftMax.
@@ -269,11 +272,14 @@ size_t line_fft_twiddle_points(int L);
 void line_fft_twiddles(const LineFft& p, float* tw);
 hipError_t launch_line_fft(const LineFft& p, const void* in, const float* inv_psi, const int* perm, const float2* tw,
                            void* out, hipStream_t s);
-hipError_t launch_transpose_c64(const void* in, int64_t rows, int64_t cols, void* out, hipStream_t s);
+// n matrices, one after another
+hipError_t launch_transpose_c64(const void* in, int64_t rows, int64_t cols, int n, void* out, hipStream_t s);
 // Table of the direct pruned DFT of a line of p.L points from p.n_in stored
 // inputs to the p.win_len kept outputs (complex64 [n_in][win_len], host):
 // exp(+2 pi i f m / L) times inv_psi[i], f the input's frequency, m the output position.
 void line_dft_table(const LineFft& p, const float* inv_psi, float* tab);
+// Whether a line's transform can store real parts only.
+bool line_real_fits(const LineFft& p);
 // Whether a planned line (with n_in and the window set) fits the direct DFT kernel.
 bool line_dft_fits(const LineFft& p);
 hipError_t launch_line_dft(const LineFft& p, const void* in, const float2* tab, void* out, hipStream_t s);
@@ -290,7 +296,7 @@ hipError_t launch_nufft_vprime(const NufftInst* insts, int n_inst, int max_ant, 
                                const int* order, const int* lstart, int n_levels, void* vp, hipStream_t s);
 int nufft_tile_size(const NufftGeom& g);  // 16 or 8 grid points per tile side, 0 = no tiled path
 // Exclusive prefix sum of n ints into offset[0..n] (and cursor[0..n-1] unless
-// null); tmp: scan_tmp_ints(n) ints (may be null for n <= 65536).
+// null); tmp: scan_tmp_ints(n) ints (null: one workgroup).
 int scan_tmp_ints(int n);
 hipError_t launch_scan_i32(const int* count, int n, int* offset, int* cursor, int* tmp, hipStream_t s);
 hipError_t launch_nufft_bin(const NufftGeom& g, const NufftInst* insts, int n_inst, int max_ant, const double* ant,

@@ -39,56 +39,70 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // ---------------------------------------------------------------------------
 // Per instance: eigenpair order grouped by level (stable), level starts, and
-// the diagonal term sum_{k in l} d_k ||w_k||^2 added into diag[l].
+// the diagonal term sum_{k in l} d_k ||w_k||^2 added into diag[l].  Workgroup
+// (instance, y): the norms of kPrepCols eigenvectors, a wave along each; y = 0 also
+// orders (64 antennas and eigenpairs: 15 us; 25 us with one thread ordering and
+// one thread per vector).
+constexpr int kPrepCols = 64;
+
 __global__ __launch_bounds__(256) void nufft_prep_kernel(const NufftInst* __restrict__ insts, const float2* __restrict__ W,
                                                          const float* __restrict__ dw, const int* __restrict__ lev,
                                                          int n_levels, int* __restrict__ order, int* __restrict__ lstart,
                                                          double* __restrict__ diag, int* __restrict__ err) {
   const NufftInst I = insts[blockIdx.x];
-  __shared__ int s_count[kMaxLevels + 1];
   __shared__ double s_sum[kMaxLevels][256 / 64];
-  const int tid = threadIdx.x;
-  int* ord = order + I.ord_off;
-  int* ls = lstart + I.ls_off;
-  if (tid == 0) {
-    for (int l = 0; l <= n_levels; ++l) s_count[l] = 0;
-    for (int k = 0; k < I.n_eig; ++k) {
-      int lv = lev[I.eig_off + k];
-      if (lv < -1 || lv >= n_levels) {
+  __shared__ int s_base[kMaxLevels + 1], s_wave[kMaxLevels][256 / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int* const lv_of = lev + I.eig_off;
+  if (blockIdx.y == 0) {
+    // level of each eigenpair's, counts, starts, then places: a pass over 256 at a time each
+    for (int l = tid; l <= n_levels; l += 256) s_base[l] = 0;
+    __syncthreads();
+    for (int k = tid; k < I.n_eig; k += 256) {
+      const int lv = lv_of[k];
+      if (lv < -1 || lv >= n_levels)
         atomicOr(err, kErrLevelId);
-        lv = -1;
+      else if (lv >= 0)
+        atomicAdd(&s_base[lv + 1], 1);
+    }
+    __syncthreads();
+    if (tid == 0)
+      for (int l = 0; l < n_levels; ++l) s_base[l + 1] += s_base[l];
+    __syncthreads();
+    for (int l = tid; l <= n_levels; l += 256) lstart[I.ls_off + l] = s_base[l];
+    for (int k0 = 0; k0 < I.n_eig; k0 += 256) {
+      const int k = k0 + tid;
+      const int lv = k < I.n_eig ? lv_of[k] : -1;
+      int before = 0;  // eigenpairs of the level in the lanes below
+      for (int l = 0; l < n_levels; ++l) {
+        const uint64_t same = __ballot(lv == l);
+        if (lane == 0) s_wave[l][wave] = __popcll(same);
+        if (lv == l) before = __popcll(same & ((1ull << lane) - 1));
       }
-      if (lv >= 0) s_count[lv + 1] += 1;
-    }
-    for (int l = 0; l < n_levels; ++l) s_count[l + 1] += s_count[l];
-    for (int l = 0; l <= n_levels; ++l) ls[l] = s_count[l];
-    for (int k = 0; k < I.n_eig; ++k) {  // stable placement
-      const int lv = lev[I.eig_off + k];
-      if (lv >= 0 && lv < n_levels) ord[s_count[lv]++] = k;
+      __syncthreads();
+      if (lv >= 0 && lv < n_levels) {
+        int at = s_base[lv] + before;
+        for (int w = 0; w < wave; ++w) at += s_wave[lv][w];
+        order[I.ord_off + at] = k;
+      }
+      __syncthreads();
+      if (tid < n_levels) s_base[tid] += s_wave[tid][0] + s_wave[tid][1] + s_wave[tid][2] + s_wave[tid][3];
+      __syncthreads();
     }
   }
-  __syncthreads();
-  // diagonal term: thread t sums d_k ||w_k||^2 over the eigenpairs k = t, t + 256, ...
-  double part[kMaxLevels];
-#pragma unroll
-  for (int l = 0; l < kMaxLevels; ++l) part[l] = 0.0;
-  for (int k = tid; k < I.n_eig; k += 256) {
-    const int lv = lev[I.eig_off + k];
+  if (lane < kMaxLevels) s_sum[lane][wave] = 0.0;
+  const int k_end = min(I.n_eig, ((int)blockIdx.y + 1) * kPrepCols);
+  for (int k = blockIdx.y * kPrepCols + wave; k < k_end; k += 4) {
+    const int lv = lv_of[k];
     if (lv < 0 || lv >= n_levels) continue;
-    const float2* col = W + I.w_off + (int64_t)k * I.n_ant;
+    const float2* const col = W + I.w_off + (int64_t)k * I.n_ant;
     double nrm = 0.0;
-    for (int q = 0; q < I.n_ant; ++q) nrm += (double)col[q].x * col[q].x + (double)col[q].y * col[q].y;
-    const double v = (double)dw[I.eig_off + k] * nrm;
-#pragma unroll
-    for (int l = 0; l < kMaxLevels; ++l)
-      if (l == lv) part[l] += v;
-  }
-  const int lane = tid & 63, wave = tid >> 6;
-#pragma unroll
-  for (int l = 0; l < kMaxLevels; ++l) {
-    double v = part[l];
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-    if (lane == 0) s_sum[l][wave] = v;
+    for (int q = lane; q < I.n_ant; q += 64) {
+      const float2 w = col[q];
+      nrm += (double)w.x * w.x + (double)w.y * w.y;
+    }
+    for (int o = 32; o > 0; o >>= 1) nrm += __shfl_xor(nrm, o);
+    if (lane == 0) s_sum[lv][wave] += (double)dw[I.eig_off + k] * nrm;
   }
   __syncthreads();
   if (tid < n_levels) {
@@ -275,31 +289,42 @@ __global__ __launch_bounds__(256) void nufft_bin_kernel(NufftGeom g, const Nufft
   if (pass == 1) list[pos] = ((uint64_t)blockIdx.y << 32) | ((uint64_t)q << 16) | (uint64_t)r;
 }
 
-// Exclusive prefix sum of n counts into offset[0..n] and cursor[0..n-1] (one workgroup).
-__global__ __launch_bounds__(1024) void nufft_scan_kernel(const int* __restrict__ count, int n, int* __restrict__ offset,
-                                                          int* __restrict__ cursor) {
-  __shared__ int s[1024];
-  __shared__ int carry;
-  const int tid = threadIdx.x;
-  if (tid == 0) carry = 0;
-  __syncthreads();
-  for (int base = 0; base < n; base += 1024) {
-    const int v = base + tid < n ? count[base + tid] : 0;
-    s[tid] = v;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-      const int t = tid >= off ? s[tid - off] : 0;
-      __syncthreads();
-      s[tid] += t;
-      __syncthreads();
+// Exclusive prefix sum of n counts into offset[0..n] and cursor[0..n-1] (one
+// workgroup, 8 counts per thread and step).  cursor may alias count: a thread
+// reads its counts before it writes there.
+__global__ __launch_bounds__(1024) void nufft_scan_kernel(const int* count, int n, int* __restrict__ offset,
+                                                          int* cursor) {
+  __shared__ int s_wave[2][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int carry = 0;
+  for (int base = 0, step = 0; base < n; base += 8192, step ^= 1) {
+    const int i0 = base + 8 * tid;
+    int v[8], sum = 0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = i0 + u < n ? count[i0 + u] : 0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) sum += v[u];
+    int incl = sum;  // over the wave's threads up to this one
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(incl, o);
+      if (lane >= o) incl += t;
     }
-    if (base + tid < n) {
-      offset[base + tid] = carry + s[tid] - v;
-      if (cursor) cursor[base + tid] = carry + s[tid] - v;
+    if (lane == 63) s_wave[step][wave] = incl;
+    __syncthreads();
+    int run = carry + incl - sum;
+    for (int w = 0; w < 16; ++w) {
+      const int t = s_wave[step][w];
+      if (w < wave) run += t;
+      carry += t;
     }
-    __syncthreads();
-    if (tid == 1023) carry += s[1023];
-    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (i0 + u < n) {
+        offset[i0 + u] = run;
+        if (cursor) cursor[i0 + u] = run;
+      }
+      run += v[u];
+    }
   }
   if (tid == 0) offset[n] = carry;
 }
@@ -329,7 +354,7 @@ __global__ __launch_bounds__(1024) void scan_chunk_sums_kernel(const int* __rest
 // is read before the barrier that precedes the writes).
 __global__ __launch_bounds__(1024) void scan_chunks_kernel(const int* count, int n, const int* __restrict__ chunk_off,
                                                            int* __restrict__ offset, int* cursor) {
-  __shared__ int s[1024];
+  __shared__ int s_wave[16];
   const int base = blockIdx.x * kScanChunk, t = threadIdx.x;
   int v[4], sum = 0;
 #pragma unroll
@@ -338,15 +363,15 @@ __global__ __launch_bounds__(1024) void scan_chunks_kernel(const int* count, int
     v[i] = idx < n ? count[idx] : 0;
     sum += v[i];
   }
-  s[t] = sum;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int x = t >= off ? s[t - off] : 0;
-    __syncthreads();
-    s[t] += x;
-    __syncthreads();
+  int incl = sum;  // over the wave's threads up to this one
+  for (int o = 1; o < 64; o <<= 1) {
+    const int x = __shfl_up(incl, o);
+    if ((t & 63) >= o) incl += x;
   }
-  int run = chunk_off[blockIdx.x] + s[t] - sum;
+  if ((t & 63) == 63) s_wave[t >> 6] = incl;
+  __syncthreads();
+  int run = chunk_off[blockIdx.x] + incl - sum;
+  for (int w = 0; w < (t >> 6); ++w) run += s_wave[w];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int idx = base + 4 * t + i;
@@ -590,16 +615,24 @@ __global__ __launch_bounds__(256) void nufft_gather_c_kernel(NufftGeom g, const 
 }
 
 // ---------------------------------------------------------------------------
-// Interpolation at the pixels, correction and accumulation into one level's image.
-template <int W, bool SHIFT>
+// Interpolation at the pixels, correction and accumulation into the images of
+// levels lv0 + blockIdx.y.  REAL: u holds real parts only.  Points outside the
+// windows (pixels other than the ones planned for) get weight zero and some valid
+// address instead of a branch, so that a pixel's w^3 reads are in flight together:
+// 16 k pixels and 5 levels take 25 us in one launch (240 us with a launch per
+// level and the reads of one row at a time), 1 M pixels 125 us a level (190 us).
+template <int W, bool SHIFT, bool REAL>
 __global__ __launch_bounds__(256) void nufft_interp_kernel(NufftGeom g, InterpLayout lay,
                                                            const double* __restrict__ pix, int64_t pix_ld,
-                                                           int64_t n_pix, const float* __restrict__ u,
+                                                           int64_t n_pix, const float* __restrict__ u_levels,
                                                            const double* __restrict__ corr,
-                                                           const double* __restrict__ diag, int lv,
-                                                           float* __restrict__ image) {
+                                                           const double* __restrict__ diag, int lv0,
+                                                           float* __restrict__ images) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= n_pix) return;
+  const int lv = lv0 + blockIdx.y;
+  constexpr int NC = REAL ? 1 : 2;  // floats per point
+  const float* const u = u_levels + blockIdx.y * (NC * lay.level_stride);
   const double a0 = pix[p], a1 = pix[p + pix_ld], a2 = pix[p + 2 * pix_ld];
   const double s0 = frame_coord(g, 0, a0, a1, a2), s1 = frame_coord(g, 1, a0, a1, a2),
                s2 = frame_coord(g, 2, a0, a1, a2);
@@ -608,37 +641,37 @@ __global__ __launch_bounds__(256) void nufft_interp_kernel(NufftGeom g, InterpLa
   kernel_row<W>((s0 - g.D[0]) * g.hM[0], g.M[0], g.beta, k0, i0);
   kernel_row<W>((s1 - g.D[1]) * g.hM[1], g.M[1], g.beta, k1, i1);
   kernel_row<W>((s2 - g.D[2]) * g.hM[2], g.M[2], g.beta, k2, i2);
-  // window offsets; points outside the windows (pixels other than the ones
-  // planned for) contribute nothing
-  int w0[W], w1[W], w2[W];
+  int w0[W];
+  int64_t o1[W], o2[W];
 #pragma unroll
   for (int t = 0; t < W; ++t) {
     w0[t] = i0[t] - lay.lo0;
     if (w0[t] < 0) w0[t] += g.M[0];
-    w1[t] = i1[t] - g.win_lo[1];
-    if (w1[t] < 0) w1[t] += g.M[1];
-    w2[t] = i2[t] - g.win_lo[2];
-    if (w2[t] < 0) w2[t] += g.M[2];
+    int w1 = i1[t] - g.win_lo[1];
+    if (w1 < 0) w1 += g.M[1];
+    int w2 = i2[t] - g.win_lo[2];
+    if (w2 < 0) w2 += g.M[2];
+    if (w0[t] >= lay.len0) w0[t] = 0, k0[t] = 0.0f;
+    if (w1 >= g.win_len[1]) w1 = 0, k1[t] = 0.0f;
+    if (w2 >= g.win_len[2]) w2 = 0, k2[t] = 0.0f;
+    o1[t] = w1 * lay.s1;
+    o2[t] = w2 * lay.s2;
   }
   float fr = 0.0f, fi = 0.0f;
 #pragma unroll
-  for (int c = 0; c < W; ++c) {
-    if (w1[c] >= g.win_len[1]) continue;
+  for (int c = 0; c < W; ++c)
 #pragma unroll
     for (int e = 0; e < W; ++e) {
-      if (w2[e] >= g.win_len[2]) continue;
-      const int64_t base = (int64_t)w1[c] * lay.s1 + (int64_t)w2[e] * lay.s2;
+      const float* const row = u + NC * (o1[c] + o2[e]);
       float sr = 0.0f, si = 0.0f;
 #pragma unroll
-      for (int a = 0; a < W; ++a)
-        if (w0[a] < lay.len0) {
-          sr += u[2 * (base + w0[a])] * k0[a];
-          if (SHIFT) si += u[2 * (base + w0[a]) + 1] * k0[a];
-        }
+      for (int a = 0; a < W; ++a) {
+        sr += row[NC * w0[a]] * k0[a];
+        if (SHIFT) si += row[NC * w0[a] + 1] * k0[a];
+      }
       fr += sr * k1[c] * k2[e];
       if (SHIFT) fi += si * k1[c] * k2[e];
     }
-  }
   // the image is 2 Re(.); a uvw cell's sources were shifted by C, which the
   // factor exp(2 pi i <s, C>) restores (turns reduced exactly in FP64)
   double val = fr;
@@ -647,7 +680,7 @@ __global__ __launch_bounds__(256) void nufft_interp_kernel(NufftGeom g, InterpLa
     const float f = (float)(t - rint(t));
     val = (double)fr * (double)__builtin_amdgcn_cosf(f) - (double)fi * (double)__builtin_amdgcn_sinf(f);
   }
-  image[p] += (float)(2.0 * val * corr[p] + (g.use_diag ? diag[lv] : 0.0));
+  images[lv * n_pix + p] += (float)(2.0 * val * corr[p] + (g.use_diag ? diag[lv] : 0.0));
 }
 
 // Per-pixel correction 1 / prod_d (phi_hat_d(2 pi s_d) / h_d), by quadrature:
@@ -677,9 +710,10 @@ __global__ __launch_bounds__(256) void fill_zero_f64_kernel(double* __restrict__
 }
 
 // ---------------------------------------------------------------------------
-hipError_t launch_nufft_prep(const NufftInst* insts, int n_inst, const void* W, const float* d, const int* lev,
+hipError_t launch_nufft_prep(const NufftInst* insts, int n_inst, int max_eig, const void* W, const float* d, const int* lev,
                              int n_levels, int* order, int* lstart, double* diag, int* err, hipStream_t s) {
-  hipLaunchKernelGGL(nufft_prep_kernel, dim3(n_inst), dim3(256), 0, s, insts, (const float2*)W, d, lev, n_levels,
+  const dim3 grd((unsigned)n_inst, (unsigned)((max_eig + kPrepCols - 1) / kPrepCols));
+  hipLaunchKernelGGL(nufft_prep_kernel, grd, dim3(256), 0, s, insts, (const float2*)W, d, lev, n_levels,
                      order, lstart, diag, err);
   return hipGetLastError();
 }
@@ -717,7 +751,8 @@ int nufft_tile_size(const NufftGeom& g) {
 int scan_tmp_ints(int n) { return 2 * ((n + kScanChunk - 1) / kScanChunk) + 2; }
 
 hipError_t launch_scan_i32(const int* count, int n, int* offset, int* cursor, int* tmp, hipStream_t s) {
-  if (n <= 1 << 16 || !tmp) {
+  // up to a step of the one workgroup, else three launches (57,600 counts: 41 us against 11)
+  if (n <= 1 << 13 || !tmp) {
     hipLaunchKernelGGL(nufft_scan_kernel, dim3(1), dim3(1024), 0, s, count, n, offset, cursor);
     return hipGetLastError();
   }
@@ -827,17 +862,16 @@ hipError_t launch_nufft_gather(int axis, const NufftGeom& g, const void* src, co
 }
 
 hipError_t launch_nufft_interp(const NufftGeom& g, const InterpLayout& lay, const double* pix, int64_t pix_ld,
-                               int64_t n_pix, const float* u, const double* corr, const double* diag, int lv,
-                               float* image, hipStream_t s) {
-  const dim3 grd((unsigned)((n_pix + 255) / 256));
+                               int64_t n_pix, const float* u, const double* corr, const double* diag, int lv0,
+                               int n_lv, float* images, hipStream_t s) {
+  const dim3 grd((unsigned)((n_pix + 255) / 256), (unsigned)n_lv);
+  if (lay.real && g.cell_q > 1) return hipErrorInvalidValue;
   return with_width(g.w, [&](auto wc) {
     constexpr int KW = decltype(wc)::value;
-    if (g.cell_q > 1)
-      hipLaunchKernelGGL((nufft_interp_kernel<KW, true>), grd, dim3(256), 0, s, g, lay, pix, pix_ld, n_pix, u, corr,
-                         diag, lv, image);
-    else
-      hipLaunchKernelGGL((nufft_interp_kernel<KW, false>), grd, dim3(256), 0, s, g, lay, pix, pix_ld, n_pix, u, corr,
-                         diag, lv, image);
+    auto* const fn = g.cell_q > 1 ? &nufft_interp_kernel<KW, true, false>
+                     : lay.real   ? &nufft_interp_kernel<KW, false, true>
+                                  : &nufft_interp_kernel<KW, false, false>;
+    hipLaunchKernelGGL(fn, grd, dim3(256), 0, s, g, lay, pix, pix_ld, n_pix, u, corr, diag, lv0, images);
     return hipGetLastError();
   });
 }

@@ -25,6 +25,11 @@ namespace {
 
 constexpr int kSigma = 2;        // type-2 grid upsampling
 constexpr int kQuadNodes = 100;  // Gauss-Legendre nodes for kernel transforms
+// Stages of several levels at once, up to this size: a launch of one level of a
+// small grid leaves most of the chip idle (240 x 240 x 12 points, 18 MB of stages:
+// 5 levels' transforms and interpolations 120 us, 440 us one by one); a level
+// that fills the chip gains nothing.
+constexpr size_t kBatchBytes = (size_t)128 << 20;
 
 // Byte offsets of a plan's two regions.  The transient region (grid, the
 // pruned transform's stages, rocFFT's work area) holds data only from a spread
@@ -34,6 +39,7 @@ constexpr int kQuadNodes = 100;  // Gauss-Legendre nodes for kernel transforms
 // transient region followed by the persistent one.
 struct NufftLayout {
   size_t grid, stage_ac, stage_b, work, work_bytes, t_total;  // from the transient base
+  int batch;       // levels that the transform's stages hold
   size_t perm[3];  // line FFTs: digit-reversed load position per input index (int32, M_d)
   size_t tw[3];    // line FFTs: the passes' twiddles (complex64, M_d - 1)
   size_t dft[3];   // lines of at most kLineDftMax points: direct DFT table (complex64, N_d x window_d)
@@ -255,12 +261,18 @@ NufftLayout nufft_layout(const bb::NufftGeom& g, int n_levels, int64_t n_pix, si
   size_t p = 0;  // transient region
   l.grid = p;
   p += align_up(8 * n_cell * (size_t)n_levels);
+  l.batch = 1;
   if (line_fft) {
     const StageSizes st = line_stage_sizes(g);
+    const size_t ac = 8 * std::max(st.a, st.b), b = 8 * std::max(st.b, st.c);
+    // as many levels at once as kBatchBytes hold, the batches of one size
+    const size_t fit = std::min<size_t>(n_levels, std::max<size_t>(1, kBatchBytes / (ac + b)));
+    const size_t batches = (n_levels + fit - 1) / fit;
+    l.batch = (int)((n_levels + batches - 1) / batches);
     l.stage_ac = p;
-    p += align_up(8 * std::max(st.a, st.b));
+    p += align_up(ac * l.batch);
     l.stage_b = p;
-    p += align_up(8 * std::max(st.b, st.c));
+    p += align_up(b * l.batch);
   } else {
     const StageSizes st = stage_sizes(g);
     l.stage_ac = p;
@@ -593,6 +605,7 @@ bb_status create_one(bb_context ctx, const bb_nufft_options* opt, int64_t n_pix,
     h->lf[2].n_lines = w2 * w1;  // B' lines along axis 0 -> C[w2][w1][w0]
     h->lf[2].in_stride = g.N[0];
     h->lf[2].out_stride = w0;
+    h->lf[2].real = h->cells == 1 && cell.q == 1 && bb::line_real_fits(h->lf[2]);
   }
   auto bail = [&](const char* what) {
     if (h->info) rocfft_execution_info_destroy(h->info);
@@ -852,7 +865,7 @@ bb_status bb_nufft_collect_eig_batched(bb_nufft h, int32_t n_inst, const bb_inst
   const int n_levels = h->opt.n_levels;
   std::vector<bb::NufftInst> ni(n_inst);
   int64_t ord_off = 0, vp_off = 0;
-  int max_ant = 0;
+  int max_ant = 0, max_eig = 0;
   for (int i = 0; i < n_inst; ++i) {
     const bb_instance& b = inst[i];
     if (b.n_ant < 2 || b.n_ant > h->opt.n_ant_max)
@@ -878,6 +891,7 @@ bb_status bb_nufft_collect_eig_batched(bb_nufft h, int32_t n_inst, const bb_inst
     ord_off += b.n_eig;
     vp_off += (int64_t)n_levels * b.n_ant * b.n_ant;
     max_ant = std::max(max_ant, b.n_ant);
+    max_eig = std::max(max_eig, b.n_eig);
   }
   const CallLayout cl = call_layout(h, n_inst, inst);
   if (ws_bytes < cl.total) return fail(ctx, BB_ERR_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, cl.total);
@@ -891,7 +905,7 @@ bb_status bb_nufft_collect_eig_batched(bb_nufft h, int32_t n_inst, const bb_inst
   BB_HIP(ctx, hipEventRecord(h->ev[0], s));
   // pageable source: the copy is staged before the call returns
   BB_HIP(ctx, hipMemcpyAsync(d_inst, ni.data(), sizeof(bb::NufftInst) * n_inst, hipMemcpyHostToDevice, s));
-  BB_HIP(ctx, bb::launch_nufft_prep(d_inst, n_inst, W_packed, d_packed, level_packed, n_levels, d_order, d_lstart,
+  BB_HIP(ctx, bb::launch_nufft_prep(d_inst, n_inst, max_eig, W_packed, d_packed, level_packed, n_levels, d_order, d_lstart,
                                     pnat<double>(h, h->lay.diag), pnat<int>(h, h->lay.err), s));
   const int64_t n_cell = (int64_t)h->g.N[0] * h->g.N[1] * h->g.N[2];
   if (cl.mode > 0) {
@@ -955,25 +969,27 @@ bb_status bb_nufft_emit(bb_nufft h) {
   if (!h->line_fft && rocfft_execution_info_set_stream(h->info, s) != rocfft_status_success)
     return fail(ctx, BB_ERR_DEVICE, "rocfft_execution_info_set_stream failed");
   BB_HIP(ctx, hipEventRecord(h->ev[2], s));
-  for (int lv = 0; lv < h->opt.n_levels; ++lv) {
+  for (int lv = 0; lv < h->opt.n_levels; lv += h->lay.batch) {
+    const int nb = std::min(h->lay.batch, h->opt.n_levels - lv);
     const float* level_grid = tnat<float>(h, h->lay.grid) + 2 * (int64_t)lv * n_cell;
     bb::InterpLayout il;
     const void* u;
     if (h->line_fft) {
-      // axis 2: grid -> A'; axis 1: A' -> B; B -> B' (transpose); axis 0: B' -> C
+      // axis 2: grid -> A'; axis 1: A' -> B; B -> B' (transpose); axis 0: B' -> C, nb levels of each
       const int64_t w1 = g.win_len[1], w2 = g.win_len[2];
       auto line = [&](int st, const void* in, void* out) {
         const int d = 2 - st;
-        return h->lf[st].direct
-                   ? bb::launch_line_dft(h->lf[st], in, pnat<float2>(h, h->lay.dft[d]), out, s)
-                   : bb::launch_line_fft(h->lf[st], in, psi[d], pnat<int>(h, h->lay.perm[d]),
-                                         pnat<float2>(h, h->lay.tw[d]), out, s);
+        bb::LineFft p = h->lf[st];
+        p.n_lines *= nb;
+        return p.direct ? bb::launch_line_dft(p, in, pnat<float2>(h, h->lay.dft[d]), out, s)
+                        : bb::launch_line_fft(p, in, psi[d], pnat<int>(h, h->lay.perm[d]),
+                                              pnat<float2>(h, h->lay.tw[d]), out, s);
       };
       BB_HIP(ctx, line(0, level_grid, ac));
       BB_HIP(ctx, line(1, ac, b));
-      BB_HIP(ctx, bb::launch_transpose_c64(b, g.N[0], w2 * w1, ac, s));
+      BB_HIP(ctx, bb::launch_transpose_c64(b, g.N[0], w2 * w1, nb, ac, s));
       BB_HIP(ctx, line(2, ac, b));
-      il = {(int64_t)g.win_len[0], w1 * g.win_len[0], g.win_lo[0], g.win_len[0]};
+      il = {(int64_t)g.win_len[0], w1 * g.win_len[0], g.win_lo[0], g.win_len[0], w2 * w1 * g.win_len[0], h->lf[2].real};
       u = b;
     } else {
       // grid -> A (FFT along axis 2) -> B (axis 1) -> C (axis 0)
@@ -985,12 +1001,12 @@ bb_status bb_nufft_emit(bb_nufft h) {
         if (rocfft_execute(h->plans.p[st], buf, nullptr, h->info) != rocfft_status_success)
           return fail(ctx, BB_ERR_DEVICE, "rocfft_execute failed");
       }
-      il = {(int64_t)g.win_len[2] * g.M[0], (int64_t)g.M[0], 0, g.M[0]};
+      il = {(int64_t)g.win_len[2] * g.M[0], (int64_t)g.M[0], 0, g.M[0], 0, 0};
       u = ac;
     }
     BB_HIP(ctx, bb::launch_nufft_interp(g, il, h->pix, h->n_pix, h->n_pix, static_cast<const float*>(u),
-                                        pnat<double>(h, h->lay.corr), pnat<double>(h, h->lay.diag), lv,
-                                        h->images + (int64_t)lv * h->n_pix, s));
+                                        pnat<double>(h, h->lay.corr), pnat<double>(h, h->lay.diag), lv, nb,
+                                        h->images, s));
   }
   BB_HIP(ctx, bb::launch_fill_zero(tnat<float>(h, h->lay.grid), 2 * n_cell * h->opt.n_levels, s));
   h->dirty = false;

@@ -366,6 +366,7 @@ __global__ __launch_bounds__((RegGeom<R1, R2, R3>::TPB), (RegGeom<R1, R2, R3>::W
   const bool live = j < G::T && line_t < min((int64_t)NL, p.n_lines - line0);
   const float2* const src = in + line0 * p.in_stride;
   float2* const dst = out + line0 * p.out_stride;
+  float* const dst_re = reinterpret_cast<float*>(out) + line0 * p.out_stride;
   {
     const bool act = live && j < S1;
     float2 v[R1];
@@ -421,7 +422,12 @@ __global__ __launch_bounds__((RegGeom<R1, R2, R3>::TPB), (RegGeom<R1, R2, R3>::W
     for (int q = 0; q < R3; ++q) {
       const int m = j + q * S3 - lo;
       const unsigned w = min((unsigned)m, (unsigned)(m + L));  // m mod L
-      if (w < wl) dst[out_off + w] = v[q];
+      if (w < wl) {
+        if (p.real)
+          dst_re[out_off + w] = v[q].x;
+        else
+          dst[out_off + w] = v[q];
+      }
     }
   }
 }
@@ -504,6 +510,8 @@ hipError_t launch_reg_plan(int i, const LineFft& p, const float2* in, const floa
 __global__ __launch_bounds__(256) void transpose_c64_kernel(const float2* __restrict__ in, int64_t rows, int64_t cols,
                                                             float2* __restrict__ out) {
   __shared__ float2 tile[32][33];
+  in += (int64_t)blockIdx.z * rows * cols;
+  out += (int64_t)blockIdx.z * rows * cols;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
   const int64_t c0 = (int64_t)blockIdx.x * 32, r0 = (int64_t)blockIdx.y * 32;
 #pragma unroll
@@ -703,6 +711,8 @@ size_t line_fft_lds_bytes(const LineFft& p) {
 // Whether line_reg_kernel transforms the planned lines.
 static bool reg_fits(const LineFft& p) { return p.reg >= 0 && p.out_mode == 0; }
 
+bool line_real_fits(const LineFft& p) { return reg_fits(p) && !p.direct; }
+
 size_t line_fft_twiddle_points(int L) { return 2 * (size_t)L; }
 
 void line_fft_twiddles(const LineFft& p, float* tw) {
@@ -782,9 +792,9 @@ hipError_t launch_line_fft(const LineFft& p, const void* in, const float* inv_ps
   return hipGetLastError();
 }
 
-hipError_t launch_transpose_c64(const void* in, int64_t rows, int64_t cols, void* out, hipStream_t s) {
+hipError_t launch_transpose_c64(const void* in, int64_t rows, int64_t cols, int n, void* out, hipStream_t s) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((cols + 31) / 32), (unsigned)((rows + 31) / 32));
+  const dim3 grid((unsigned)((cols + 31) / 32), (unsigned)((rows + 31) / 32), (unsigned)n);
   hipLaunchKernelGGL(transpose_c64_kernel, grid, dim3(256), 0, s, static_cast<const float2*>(in), rows, cols,
                      static_cast<float2*>(out));
   return hipGetLastError();
