@@ -222,6 +222,7 @@ struct NufftInst {
   int64_t ant_off, w_off, eig_off;
   int64_t ord_off, ls_off;  // this instance's level-grouped order and level starts
   int64_t vp_off;           // this instance's V' block (n_levels x n_ant^2 complex64)
+  int64_t pair_off;         // this instance's first baseline (n_ant (n_ant - 1) / 2 each)
 };
 hipError_t launch_nufft_prep(const NufftInst* insts, int n_inst, int max_eig, const void* W, const float* d, const int* lev,
                              int n_levels, int* order, int* lstart, double* diag, int* err, hipStream_t s);
@@ -307,13 +308,15 @@ hipError_t launch_nufft_bin(const NufftGeom& g, const NufftInst* insts, int n_in
 int nufft_gather_z(const NufftGeom& g);
 void nufft_gather_blocks(const NufftGeom& g, int& nbx, int& nby);
 constexpr int kGatherRecBytes = 128;  // per sorted baseline
-// After launch_nufft_bin with bin 1: records (max_src x 128 bytes), level values
-// (max_src x ((n_levels + 1) & ~1) complex64), nparts and part_off (blocks,
-// blocks + 1 ints), scan_tmp (scan_tmp_ints(blocks)).
-hipError_t launch_nufft_spread_gather(const NufftGeom& g, const NufftInst* insts, int64_t max_src, const double* ant,
-                                      int64_t ld, const void* vp, const int* offset, const uint64_t* list,
-                                      int n_levels, void* rec, void* cv, int* nparts, int* part_off, int* scan_tmp,
-                                      bool fresh, float* grid, int64_t n_cell, hipStream_t s);
+// count (N0 N1 ints), offset (N0 N1 + 1), place (max_src x 8 bytes), records
+// (max_src x 128 bytes), level values (max_src x ((n_levels + 1) & ~1)
+// complex64), nparts and part_off (blocks, blocks + 1 ints), scan_tmp
+// (scan_tmp_ints of the larger count).  fresh: the grid is clear.
+hipError_t launch_nufft_spread_gather(const NufftGeom& g, const NufftInst* insts, int n_inst, int max_ant,
+                                      int64_t max_src, const double* ant, int64_t ld, const void* vp, int* count,
+                                      int* offset, void* place, int n_levels, void* rec, void* cv, int* nparts,
+                                      int* part_off, int* scan_tmp, bool fresh, float* grid, int64_t n_cell, int* err,
+                                      hipStream_t s);
 // nch, choff: n_tiles and n_tiles + 1 ints of scratch (chunks per tile and their offsets).
 hipError_t launch_nufft_spread_tiles(const NufftGeom& g, const NufftInst* insts, const double* ant, int64_t ld,
                                      const void* vp, const int* offset, const uint64_t* list, int bin, int n_levels,

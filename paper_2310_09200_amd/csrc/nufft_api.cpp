@@ -864,7 +864,7 @@ bb_status bb_nufft_collect_eig_batched(bb_nufft h, int32_t n_inst, const bb_inst
     return fail(ctx, BB_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
   const int n_levels = h->opt.n_levels;
   std::vector<bb::NufftInst> ni(n_inst);
-  int64_t ord_off = 0, vp_off = 0;
+  int64_t ord_off = 0, vp_off = 0, pair_off = 0;
   int max_ant = 0, max_eig = 0;
   for (int i = 0; i < n_inst; ++i) {
     const bb_instance& b = inst[i];
@@ -888,6 +888,8 @@ bb_status bb_nufft_collect_eig_batched(bb_nufft h, int32_t n_inst, const bb_inst
     d.ord_off = ord_off;
     d.ls_off = (int64_t)i * (n_levels + 1);
     d.vp_off = vp_off;
+    d.pair_off = pair_off;
+    pair_off += (int64_t)b.n_ant * (b.n_ant - 1) / 2;
     ord_off += b.n_eig;
     vp_off += (int64_t)n_levels * b.n_ant * b.n_ant;
     max_ant = std::max(max_ant, b.n_ant);
@@ -911,27 +913,23 @@ bb_status bb_nufft_collect_eig_batched(bb_nufft h, int32_t n_inst, const bb_inst
   if (cl.mode > 0) {
     BB_HIP(ctx, bb::launch_nufft_vprime(d_inst, n_inst, max_ant, W_packed, d_packed, d_order, d_lstart, n_levels,
                                         ws + cl.vp, s));
-    int* count = reinterpret_cast<int*>(ws + cl.count);
-    int* offset = reinterpret_cast<int*>(ws + cl.offset);
-    int* cursor = reinterpret_cast<int*>(ws + cl.cursor);
-    uint64_t* list = reinterpret_cast<uint64_t*>(ws + cl.list);
-    int* scan_tmp = reinterpret_cast<int*>(ws + cl.scan_tmp);
-    BB_HIP(ctx, bb::launch_nufft_bin(h->g, d_inst, n_inst, max_ant, ant_xyz_packed, n_ant_rows, cl.bin, count, offset,
-                                     cursor, list, pnat<int>(h, h->lay.err), scan_tmp, s));
   }
+  int* count = reinterpret_cast<int*>(ws + cl.count);
+  int* offset = reinterpret_cast<int*>(ws + cl.offset);
+  int* scan_tmp = reinterpret_cast<int*>(ws + cl.scan_tmp);
   const bool was_dirty = h->dirty;
   h->dirty = true;
   if (cl.mode == 2) {
-    BB_HIP(ctx, bb::launch_nufft_spread_gather(h->g, d_inst, cl.pairs, ant_xyz_packed, n_ant_rows, ws + cl.vp,
-                                               reinterpret_cast<int*>(ws + cl.offset),
-                                               reinterpret_cast<uint64_t*>(ws + cl.list), n_levels, ws + cl.rec,
+    BB_HIP(ctx, bb::launch_nufft_spread_gather(h->g, d_inst, n_inst, max_ant, cl.pairs, ant_xyz_packed, n_ant_rows,
+                                               ws + cl.vp, count, offset, ws + cl.list, n_levels, ws + cl.rec,
                                                ws + cl.cv, reinterpret_cast<int*>(ws + cl.nparts),
-                                               reinterpret_cast<int*>(ws + cl.part_off),
-                                               reinterpret_cast<int*>(ws + cl.scan_tmp), !was_dirty,
-                                               tnat<float>(h, h->lay.grid), n_cell, s));
+                                               reinterpret_cast<int*>(ws + cl.part_off), scan_tmp, !was_dirty,
+                                               tnat<float>(h, h->lay.grid), n_cell, pnat<int>(h, h->lay.err), s));
   } else if (cl.mode == 1) {
-    const int* offset = reinterpret_cast<int*>(ws + cl.offset);
-    const uint64_t* list = reinterpret_cast<uint64_t*>(ws + cl.list);
+    uint64_t* list = reinterpret_cast<uint64_t*>(ws + cl.list);
+    BB_HIP(ctx, bb::launch_nufft_bin(h->g, d_inst, n_inst, max_ant, ant_xyz_packed, n_ant_rows, cl.bin, count, offset,
+                                     reinterpret_cast<int*>(ws + cl.cursor), list, pnat<int>(h, h->lay.err), scan_tmp,
+                                     s));
     BB_HIP(ctx, bb::launch_nufft_spread_tiles(h->g, d_inst, ant_xyz_packed, n_ant_rows, ws + cl.vp, offset, list,
                                               cl.bin, n_levels, reinterpret_cast<int*>(ws + cl.nch),
                                               reinterpret_cast<int*>(ws + cl.choff), tnat<float>(h, h->lay.grid), n_cell,
