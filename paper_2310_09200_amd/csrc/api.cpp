@@ -1326,31 +1326,38 @@ bb_status bb_synth_autotune_batched(bb_synth h, int32_t n_inst, const bb_instanc
 namespace {
 
 struct BwdPlan {
-  int L_pad, K_alloc, n_split;
-  int64_t split_len;
-  size_t off_E, off_dd, off_dW, off_dx, total;
+  int L_pad, K_alloc, n_split, n_dw;
+  int64_t split_len, dw_len;
+  size_t off_E, off_dd, off_top, off_dW, off_dx, total;
 };
 
 BwdPlan plan_backward(int64_t n_pix, int n_ant, int n_eig) {
   BwdPlan b{};
   b.L_pad = bb::round_up(n_ant, bb::kAntChunk);
   b.K_alloc = bb::round_up(n_eig, 32);
-  // pixel splits: the fused and dx kernels run (L_pad / 32) x n_split
-  // workgroups, two of which fit a CU; 512 of them fill the 256 CUs
-  const int64_t lblocks = b.L_pad / 32;
-  int64_t want = (512 + lblocks - 1) / lblocks;
+  // pixel splits: the dx kernel runs (L_pad / 32) x n_split workgroups, two of
+  // which fit a CU, three of up to 64 eigenpairs: the 256 CUs are filled once
+  const int64_t lblocks = b.L_pad / 32, fill = b.K_alloc <= 64 ? 768 : 512;
+  int64_t want = (fill + lblocks - 1) / lblocks;
   const int64_t max_split = (n_pix + 63) / 64;
   if (want > max_split) want = max_split;
   if (want < 1) want = 1;
   b.split_len = ((n_pix + want - 1) / want + 63) / 64 * 64;
   b.n_split = (int)((n_pix + b.split_len - 1) / b.split_len);
+  // dW: blocks of 128 antennas x 64 or 128 eigenpairs, one per CU
+  const int64_t blocks = (int64_t)((b.L_pad + 127) / 128) * (b.K_alloc <= 64 ? 1 : (b.K_alloc + 127) / 128);
+  want = std::max<int64_t>(1, std::min<int64_t>((256 + blocks - 1) / blocks, max_split));
+  b.dw_len = ((n_pix + want - 1) / want + 63) / 64 * 64;
+  b.n_dw = (int)((n_pix + b.dw_len - 1) / b.dw_len);
   size_t p = 0;
   b.off_E = p;
   p += align_up((size_t)2 * b.K_alloc * n_pix * 4);
   b.off_dd = p;
   p += align_up((size_t)b.K_alloc * b.n_split * 8);
+  b.off_top = p;
+  p += align_up((size_t)b.K_alloc * b.n_split * 4);
   b.off_dW = p;
-  p += align_up((size_t)b.n_split * b.L_pad * b.K_alloc * 2 * 8);
+  p += align_up((size_t)b.n_dw * b.L_pad * b.K_alloc * 2 * 8);
   b.off_dx = p;
   p += align_up((size_t)b.n_split * b.L_pad * 3 * 8);
   b.total = p;
@@ -1435,6 +1442,9 @@ bb_status bb_synth_eig_backward(bb_synth h, int32_t n_ant, int32_t n_eig, double
   b.W = W;
   b.n_split = bp.n_split;
   b.split_len = bp.split_len;
+  b.n_dw = bp.n_dw;
+  b.dw_len = bp.dw_len;
+  b.m_top = reinterpret_cast<float*>(ws + bp.off_top);
   b.dd_part = reinterpret_cast<double*>(ws + bp.off_dd);
   b.dW_part = reinterpret_cast<double*>(ws + bp.off_dW);
   b.dx_part = reinterpret_cast<double*>(ws + bp.off_dx);

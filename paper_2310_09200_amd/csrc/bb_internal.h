@@ -337,7 +337,10 @@ struct BwdParams {
   int n_split;                          // pixel splits of the contractions over pixels
   int64_t split_len;                    // pixels per split (multiple of 64)
   double* dd_part;                      // [K_alloc][n_split]
-  double* dW_part;                      // [n_split][L_pad][K_alloc][2]
+  int n_dw;                             // pixel splits of dW, dw_len pixels each (multiple of 64)
+  int64_t dw_len;
+  float* m_top;                         // [K_alloc][n_split]: largest |Re M|, |Im M|
+  double* dW_part;                      // [n_dw][L_pad][K_alloc][2]
   double* dx_part;                      // [n_split][L_pad][3]
   double scale_x;                       // -(4 pi / wavelength)
 };

@@ -8,10 +8,9 @@
 //   dW_lk = 2 sum_p B_lp M_kp            (d/dRe W + j d/dIm W)
 //   H_lp  = sum_k conj(W_lk) M_kp
 //   dx_l  = -(4 pi / lambda_w) sum_p Im(H_lp B_lp) p
-// E is recomputed by the forward MFMA kernel (FP32, three products) into HBM; the
-// contractions dW and H run on FP32 MFMA (32x32x2), in one kernel sharing its
-// staged phases and M when every eigenpair fits one 64-wide slice, in two
-// otherwise.  The kernels work in level-sorted eigenpair order (the staging
+// E is recomputed on FP32 MFMA into HBM.  H runs on FP32 MFMA (32x32x2): dx is an
+// FP64 result whose sums show every rounding of H.  dW, a complex64 result, runs on
+// fp16 products of two-term splits.  The kernels work in level-sorted eigenpair order (the staging
 // permutation) and
 // the reduction writes results back in the caller's order.  Contractions over
 // pixels are split into fixed pixel ranges whose FP64 partials are summed in a
@@ -21,6 +20,7 @@
 #include <stdint.h>
 
 #include "bb_internal.h"
+#include "split.h"
 
 namespace bb {
 
@@ -47,9 +47,12 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
   return t;
 }
 
-// M = d c conj(E) in place, dd partial sums; grid (K_alloc, n_split), 256 threads.
+// M = d c conj(E) in place, dd partial sums, and the largest |Re M|, |Im M| of the
+// split; grid (K_alloc, n_split), 256 threads.
 __global__ __launch_bounds__(256) void bwd_m_kernel(const BwdParams P) {
   __shared__ double sh[4];
+  __shared__ float shm[4];
+  float top = 0.0f;
   const int k = blockIdx.x;
   const int s = blockIdx.y;
   const InstDesc& D = *P.desc;
@@ -72,26 +75,21 @@ __global__ __launch_bounds__(256) void bwd_m_kernel(const BwdParams P) {
       const float c = P.gimg[(int64_t)lev * P.gimg_ld + p];
       const float a = er[p], b = ei[p];
       acc += (double)(c * fmaf(a, a, b * b));
-      er[p] = w * c * a;
-      ei[p] = -w * c * b;
+      const float mr = w * c * a, mi = -w * c * b;
+      er[p] = mr;
+      ei[p] = mi;
+      top = fmaxf(top, fmaxf(fabsf(mr), fabsf(mi)));
     }
   }
+  for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+  if ((threadIdx.x & 63) == 0) shm[threadIdx.x >> 6] = top;
   const double t = block_sum<256>(acc, sh);
-  if (threadIdx.x == 0) P.dd_part[(int64_t)k * P.n_split + s] = t;
+  if (threadIdx.x == 0) {
+    P.dd_part[(int64_t)k * P.n_split + s] = t;
+    P.m_top[(int64_t)k * P.n_split + s] = fmaxf(fmaxf(shm[0], shm[1]), fmaxf(shm[2], shm[3]));
+  }
 }
 
-// dW partial: sum over the split's pixels of B_lp M_kp for a 32 x 64 (l, k)
-// tile of two 32-eigenpair blocks, on MFMA.  grid (L_pad/32,
-// ceil(K_alloc/64), n_split), 256 threads.  Each 64-pixel chunk stages
-// phases [64 px][32 l] and M [64 px][64 k] in LDS; wave w contracts pixels
-// 16 w .. 16 w + 15 of it as 8 steps of 32x32x2 MFMAs per block (A = B
-// phases, rows l; B = M, columns k):
-//   Re += Br Mr - Bi Mi,  Im += Br Mi + Bi Mr.
-// Two blocks per workgroup share each phase evaluation; the second is absent
-// (workgroup-uniform) when K_alloc is an odd multiple of 32.  The next
-// chunk's M and pixel coordinates are loaded into registers while the
-// current chunk is processed.  The four waves' partial tiles are summed in a
-// fixed order at the end.
 typedef float bwd_f32x16 __attribute__((ext_vector_type(16)));
 
 // One chunk's H block of a wave: H[l][p] += sum over 64 eigenpairs of
@@ -119,26 +117,6 @@ __device__ __forceinline__ void h_chunk(bwd_f32x16& h, const float2 (*sW)[65], c
   }
 }
 
-// h_chunk for a W that stays the same over the chunks: the real part takes
-// -Wi' from registers (wny[st] for this lane's row of step st), loaded once.
-template <int PART>
-__device__ __forceinline__ void h_chunk_w(bwd_f32x16& h, const float2 (*sW)[65], const float (&wny)[32],
-                                          const float2 (*sM)[65], int blk, int lane) {
-#pragma unroll
-  for (int st = 0; st < 32; ++st) {
-    const int kk = 2 * st + (lane >> 5);
-    const float2 m = sM[kk][32 * blk + (lane & 31)];
-    if (PART == 0) {
-      h = __builtin_amdgcn_mfma_f32_32x32x2f32(sW[lane & 31][kk].x, m.x, h, 0, 0, 0);
-      h = __builtin_amdgcn_mfma_f32_32x32x2f32(wny[st], m.y, h, 0, 0, 0);
-    } else {
-      const float2 w = sW[lane & 31][kk];
-      h = __builtin_amdgcn_mfma_f32_32x32x2f32(w.x, m.y, h, 0, 0, 0);
-      h = __builtin_amdgcn_mfma_f32_32x32x2f32(w.y, m.x, h, 0, 0, 0);
-    }
-  }
-}
-
 // h_chunk over conj(W) staged once for every eigenpair of the instance (rows
 // of WS, this slice's columns kc .. kc + 63); the real part negates Wi' per
 // step.
@@ -160,133 +138,232 @@ __device__ __forceinline__ void h_chunk_all(bwd_f32x16& h, const float2 (*sW)[WS
   }
 }
 
-// One chunk's dW block of a wave: dW[l][k] += sum over the chunk's 64 pixels
-// of B[p][l] M[k][p] for eigenpairs 32 blk .. 32 blk + 31, real part (PART 0:
-// Br Mr - Bi Mi) or imaginary part (PART 1: Br Mi + Bi Mr).
-// The real part takes -Bi from the staged plane sBn (no negation per step).
-template <int PART>
-__device__ __forceinline__ void dw_chunk(bwd_f32x16& dw, const float2 (*sB)[32], const float (*sBn)[32],
-                                         const float2 (*sM)[65], int blk, int lane) {
-#pragma unroll
-  for (int st = 0; st < 32; ++st) {
-    const int pp = 2 * st + (lane >> 5);
-    const float2 b = sB[pp][lane & 31];
-    const float2 m = sM[32 * blk + (lane & 31)][pp];
-    if (PART == 0) {
-      dw = __builtin_amdgcn_mfma_f32_32x32x2f32(b.x, m.x, dw, 0, 0, 0);
-      dw = __builtin_amdgcn_mfma_f32_32x32x2f32(sBn[pp][lane & 31], m.y, dw, 0, 0, 0);
-    } else {
-      dw = __builtin_amdgcn_mfma_f32_32x32x2f32(b.x, m.y, dw, 0, 0, 0);
-      dw = __builtin_amdgcn_mfma_f32_32x32x2f32(b.y, m.x, dw, 0, 0, 0);
-    }
-  }
+// dW partial: sum over a split's pixels of B_lp M_kp for 128 antennas x 16 NKT
+// eigenpairs.  512 threads: wave w takes antennas 32 (w / 2) .. + 31 of the block
+// and pixels 32 (w % 2) .. + 31 of every 64-pixel chunk, on
+// v_mfma_f32_16x16x32_f16 (A = phases, B = M; both operands hold 8 consecutive
+// pixels per lane):
+//   Re += Br Mr + Bi (-Mi),  Im += Br Mi + Bi Mr,
+// each factor as hi + lo halves and three of the four half products.  A wave
+// forms its phases where the matrix unit wants them, in registers; M is read
+// once per 128 antennas, scaled by a power of two per eigenpair (its largest
+// |M|, found when M was formed, becomes 2^14, so that a low half reaches 2^-38 of
+// it), split and staged as planes [re hi, re lo, im hi, im lo][half][k][32 px],
+// two chunks deep.
+//   Three products at the fp16 rate (16 times FP32's) against one: 250 antennas,
+// 121 eigenpairs, 500^2 pixels take 257 us against 693 on FP32 MFMA, and
+// against 64 bits the result is closer (one rounding per 32 pixels in the split's
+// sum: 5.5e-7 against 9.0e-7).
+// A tile of 32 antennas x all eigenpairs keeps phases (a wave's 1200 cycles a
+// chunk) below products (3072, NKT = 8).
+typedef _Float16 bwd_f16x8 __attribute__((ext_vector_type(8)));
+typedef float bwd_f32x4 __attribute__((ext_vector_type(4)));
+typedef float bwd_f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ bwd_f32x4 mfma_h(const uint4& a, const uint4& b, bwd_f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(bwd_f16x8, a), __builtin_bit_cast(bwd_f16x8, b), c,
+                                                0, 0, 0);
 }
 
-// One chunk's dW steps of a wave for both eigenpair blocks.
-__device__ __forceinline__ void dw2_chunk(bwd_f32x16 (&are)[2], bwd_f32x16 (&aim)[2], const float2 (*sB)[32],
-                                          const float2 (*sM)[65], int wave, int lane) {
-#pragma unroll
-  for (int st = 0; st < 8; ++st) {
-    const int pp = 16 * wave + 2 * st + (lane >> 5);  // this lane's contraction row (pixel)
-    const float2 b = sB[pp][lane & 31];               // A operand: row l = lane % 32
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const float2 m = sM[pp][32 * q + (lane & 31)];  // B operand: column k = lane % 32 of block q
-      are[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(b.x, m.x, are[q], 0, 0, 0);
-      are[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(-b.y, m.y, are[q], 0, 0, 0);
-      aim[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(b.x, m.y, aim[q], 0, 0, 0);
-      aim[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(b.y, m.x, aim[q], 0, 0, 0);
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void bwd_dw_kernel(const BwdParams P) {
-  __shared__ float2 sB[64][32];
-  __shared__ float2 sM[64][65];  // [pixel][eigenpair] (+1 pad: the staging writes run along pixels)
-  __shared__ double sP[3][64];   // the chunk's pixel coordinates
-  __shared__ double sX[32][4];   // the tile's scaled antenna positions
+template <int NKT>
+__global__ __launch_bounds__(512, 2) void bwd_dw_kernel(const BwdParams P) {
+  constexpr int K = 16 * NKT;       // eigenpairs of the block
+  constexpr int PLANE = 2 * K * 4;  // 16-byte words of a plane: [half][k][4]
+  constexpr int Q = NKT / 2;        // rows of M per thread and chunk, every 32nd
+  extern __shared__ uint4 s_m[];    // [2][4][PLANE]; then the halves' exchange
+  __shared__ double sP[2][3][64];
+  __shared__ double sX[128][4];
+  __shared__ int sE[K];  // exponent of each eigenpair's scale
   const InstDesc& D = *P.desc;
-  const int l0 = blockIdx.x * 32, k0 = blockIdx.y * 64, s = blockIdx.z;
-  const bool two = k0 + 32 < P.K_alloc;  // the second eigenpair block exists
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  if (t < 128) (&sX[0][0])[t] = D.xs[4 * l0 + t];  // rows l0 .. l0 + 31 < L_pad
-  const int64_t p0 = (int64_t)s * P.split_len;
-  int64_t p1 = p0 + P.split_len;
-  if (p1 > P.n_pix) p1 = P.n_pix;
-  const float* Er = P.E;
-  const float* Ei = P.E + (int64_t)P.K_alloc * P.n_pix;
-  // the next chunk's M (16 values per thread: eigenpair k0 + 4 j + t / 64,
-  // pixel t % 64; rows up to K_alloc hold M or zeros, an absent second block
-  // reads row k0 and keeps zeros) and pixel coordinates (threads < 192: axis
-  // t / 64); lanes past the split load the split's last pixel and keep zeros
-  float2 mnext[16];
-  double pnext = 0.0;
-  auto load_chunk = [&](int64_t pc) {
-    const int64_t p = pc + (t & 63);
-    const bool p_ok = p < p1;
-    const int64_t pq = p_ok ? p : p1 - 1;
-    const int64_t r0 = (int64_t)(k0 + (t >> 6)) * P.n_pix + pq, st4 = 4 * P.n_pix;  // rows advance by 4 per j
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const bool k_ok = j < 8 || two;
-      const int64_t e = k_ok ? r0 + j * st4 : pq;
-      const float er = Er[e], ei = Ei[e];
-      mnext[j] = (p_ok && k_ok) ? make_float2(er, ei) : make_float2(0.0f, 0.0f);
-    }
-    if (t < 192) pnext = p_ok ? P.pix[pq + (t >> 6) * P.pix_ld] : 0.0;
-  };
-  load_chunk(p0);
-  bwd_f32x16 are[2], aim[2];
-#pragma unroll
-  for (int q = 0; q < 2; ++q)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) are[q][r] = aim[q][r] = 0.0f;
-  for (int64_t pc = p0; pc < p1; pc += 64) {
-#pragma unroll
-    for (int j = 0; j < 16; ++j) sM[t & 63][4 * j + (t >> 6)] = mnext[j];
-    if (t < 192) sP[t >> 6][t & 63] = pnext;
-    __syncthreads();
-    if (pc + 64 < p1) load_chunk(pc + 64);  // workgroup-uniform
-    // phases: 32 antennas x 64 pixels, 8 per thread (zero past the split)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int i = t + 256 * j;
-      const int pp = i >> 5, ll = i & 31;
-      float c, sn;
-      phase_b(&sX[ll][0], sP[0][pp], sP[1][pp], sP[2][pp], c, sn);
-      sB[pp][ll] = pc + pp < p1 ? make_float2(c, sn) : make_float2(0.0f, 0.0f);
-    }
-    __syncthreads();
-    dw2_chunk(are, aim, sB, sM, wave, lane);  // an absent second block multiplies zeros
-    __syncthreads();
+  const int l0 = blockIdx.x * 128, k0 = blockIdx.y * K, s = blockIdx.z;
+  const int t = threadIdx.x, lane = t & 63, r16 = lane & 15, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6), wl = wave >> 1, half = wave & 1;
+  const bool live = l0 + 32 * wl < P.L_pad;  // the wave's antennas exist
+  if (t < 512) {
+    const int row = l0 + (t >> 2);
+    (&sX[0][0])[t] = row < P.L_pad ? D.xs[4 * l0 + t] : 0.0;
   }
-  // fixed-order sum of the four waves' tiles, one block at a time: wave w's
-  // register r of lane q holds (l, k) = (8 (r / 4) + 4 (q / 32) + r % 4, q % 32)
-  float* const red = reinterpret_cast<float*>(&sB[0][0]);  // [4 waves][16 regs][64 lanes] re, then im in sM
-  float* const redi = reinterpret_cast<float*>(&sM[0][0]);
+  {  // scales: 512 / K threads per eigenpair
+    constexpr int TP = 512 / K;
+    const int k = t / TP;
+    float top = 0.0f;
+    if (k0 + k < P.K_alloc)
+      for (int i = t % TP; i < P.n_split; i += TP) top = fmaxf(top, P.m_top[(int64_t)(k0 + k) * P.n_split + i]);
+    for (int o = TP / 2; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+    // 2^-e top in [2^13, 2^14); within the range of a normal factor 2^-e
+    int e = top > 0.0f && top < INFINITY ? ilogbf(top) - 13 : 0;
+    if (t % TP == 0) sE[k] = max(-120, min(120, e));
+  }
+  __syncthreads();
+  const int64_t p0 = (int64_t)s * P.dw_len;
+  const int64_t p1 = min(p0 + P.dw_len, P.n_pix);
+  // M rows kr + 32 q, pixels 4 px .. + 3 of a chunk
+  const int px = t & 15, kr = t >> 4;
+  float scale[Q];
 #pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    if (b == 1 && !two) break;
+  for (int q = 0; q < Q; ++q) scale[q] = __int_as_float((127 - sE[kr + 32 * q]) << 23);
+  // rows q0 .. q0 + Q / 2 - 1, real and imaginary parts, of the chunk at pc
+  constexpr int QH = Q / 2;
+  bwd_f32x4 next[2][QH];
+  auto load = [&](int64_t pc, int q0) {
+    const int64_t p = pc + 4 * px;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      red[(wave * 16 + r) * 64 + lane] = are[b][r];
-      redi[(wave * 16 + r) * 64 + lane] = aim[b][r];
-    }
-    __syncthreads();
-    for (int i = t; i < 16 * 64; i += 256) {
-      const int r = i >> 6, q = i & 63;
-      double re = 0.0, im = 0.0;
+    for (int c = 0; c < 2; ++c)
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        re += red[(w * 16 + r) * 64 + q];
-        im += redi[(w * 16 + r) * 64 + q];
+      for (int q = 0; q < QH; ++q) {
+        const int k = k0 + kr + 32 * (q0 + q);
+        const float* const row = P.E + ((int64_t)c * P.K_alloc + k) * P.n_pix;
+        bwd_f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (k < P.K_alloc) {
+          if (p + 4 <= p1) {
+            v = *reinterpret_cast<const bwd_f32x4u*>(row + p);
+          } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (p + i < p1) v[i] = row[p + i];
+          }
+        }
+        next[c][q] = v;
       }
-      const int l = 8 * (r >> 2) + 4 * (q >> 5) + (r & 3), k = 32 * b + (q & 31);
-      double* out = P.dW_part + (((int64_t)s * P.L_pad + (l0 + l)) * P.K_alloc + k0 + k) * 2;
-      out[0] = re;
-      out[1] = im;
-    }
+  };
+  auto store = [&](int buf, int q0) {
+    uint2* const dst = reinterpret_cast<uint2*>(s_m + buf * 4 * PLANE);
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int q = 0; q < QH; ++q) {
+        const bwd_f32x4 v = next[c][q] * scale[q0 + q];
+        uint2 hi, lo;
+        split2<_Float16>(v[0], v[1], hi.x, lo.x);
+        split2<_Float16>(v[2], v[3], hi.y, lo.y);
+        // [half = px / 8][k][8 words of 8 bytes]
+        const int at = ((px >> 3) * K + kr + 32 * (q0 + q)) * 8 + (px & 7);
+        dst[2 * (2 * c) * PLANE + at] = hi;
+        dst[2 * (2 * c + 1) * PLANE + at] = lo;
+      }
+  };
+  double pnext = 0.0;
+  auto load_pix = [&](int64_t pc) {
+    const int64_t p = pc + (t & 63);
+    if (t < 192) pnext = p < p1 ? P.pix[p + (t >> 6) * P.pix_ld] : 0.0;
+  };
+  load(p0, 0);
+  store(0, 0);
+  load(p0, QH);
+  store(0, QH);
+  load_pix(p0);
+  if (t < 192) sP[0][t >> 6][t & 63] = pnext;
+  bwd_f32x4 acc[2][NKT][2];  // [antennas][eigenpairs][re, im]
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < NKT; ++j) acc[i][j][0] = acc[i][j][1] = bwd_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  int buf = 0;
+  for (int64_t pc = p0; pc < p1; pc += 64, buf ^= 1) {
+    const bool more = pc + 64 < p1;  // the same for the workgroup
     __syncthreads();
+    if (more) {
+      load(pc + 64, 0);
+      load_pix(pc + 64);
+    }
+    uint4 bh[2][2], bl[2][2];  // phases [antennas][cos, sin], 8 pixels each
+    if (live) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const double* const xs = sX[32 * wl + 16 * i + r16];
+        const double x0 = xs[0], x1 = xs[1], x2 = xs[2];
+        uint32_t* const ch = reinterpret_cast<uint32_t*>(&bh[i][0]);
+        uint32_t* const cl = reinterpret_cast<uint32_t*>(&bl[i][0]);
+        uint32_t* const sh = reinterpret_cast<uint32_t*>(&bh[i][1]);
+        uint32_t* const sl = reinterpret_cast<uint32_t*>(&bl[i][1]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          float c[2], sn[2];
+#pragma unroll
+          for (int v = 0; v < 2; ++v) {
+            const int pp = 32 * half + 8 * kq + 2 * u + v;
+            const double xsv[3] = {x0, x1, x2};
+            phase_b(xsv, sP[buf][0][pp], sP[buf][1][pp], sP[buf][2][pp], c[v], sn[v]);
+          }
+          split2<_Float16>(c[0], c[1], ch[u], cl[u]);
+          split2<_Float16>(sn[0], sn[1], sh[u], sl[u]);
+        }
+      }
+    }
+    const uint4* const m = s_m + buf * 4 * PLANE + half * K * 4 + r16 * 4 + kq;
+    auto products = [&](int j) {
+      const uint4 rh = m[j * 64], rl = m[PLANE + j * 64], ih = m[2 * PLANE + j * 64], il = m[3 * PLANE + j * 64];
+      auto neg = [](uint4 v) {
+        return make_uint4(v.x ^ 0x80008000u, v.y ^ 0x80008000u, v.z ^ 0x80008000u, v.w ^ 0x80008000u);
+      };
+      const uint4 nh = neg(ih), nl = neg(il);
+      // the chunk's sum by itself, low products first, then one rounding in the
+      // split's sum: [re, im] += cos x [Mr, Mi] + sin x [-Mi, Mr]
+      bwd_f32x4 sum[2][2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) sum[i][0] = sum[i][1] = bwd_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      auto add = [&](const uint4(&b)[2][2], const uint4& mr, const uint4& mi, const uint4& mn) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          sum[i][0] = mfma_h(b[i][0], mr, sum[i][0]);
+          sum[i][1] = mfma_h(b[i][0], mi, sum[i][1]);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          sum[i][0] = mfma_h(b[i][1], mn, sum[i][0]);
+          sum[i][1] = mfma_h(b[i][1], mr, sum[i][1]);
+        }
+      };
+      add(bh, rl, il, nl);
+      add(bl, rh, ih, nh);
+      add(bh, rh, ih, nh);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        acc[i][j][0] += sum[i][0];
+        acc[i][j][1] += sum[i][1];
+      }
+    };
+    if (live)
+#pragma unroll
+      for (int j = 0; j < NKT / 2; ++j) products(j);
+    if (more) {
+      store(buf ^ 1, 0);
+      if (t < 192) sP[buf ^ 1][t >> 6][t & 63] = pnext;
+      load(pc + 64, QH);
+    }
+    if (live)
+#pragma unroll
+      for (int j = NKT / 2; j < NKT; ++j) products(j);
+    if (more) store(buf ^ 1, QH);
+  }
+  // the second halves' sums go through LDS to the first halves, real parts then imaginary
+  float* const ex = reinterpret_cast<float*>(s_m) + wl * (2 * NKT * 4 * 64) + lane;
+#pragma unroll
+  for (int part = 0; part < 2; ++part) {
+    __syncthreads();
+    if (half == 1)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NKT; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) ex[((i * NKT + j) * 4 + r) * 64] = acc[i][j][part][r];
+    __syncthreads();
+    if (half == 0 && live)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NKT; ++j) {
+          const int k = 16 * j + r16;
+          if (k0 + k >= P.K_alloc) continue;
+          const double back = ldexp(1.0, sE[k]);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int l = l0 + 32 * wl + 16 * i + 4 * kq + r;
+            P.dW_part[(((int64_t)s * P.L_pad + l) * P.K_alloc + k0 + k) * 2 + part] =
+                ((double)acc[i][j][part][r] + (double)ex[((i * NKT + j) * 4 + r) * 64]) * back;
+          }
+        }
   }
 }
 
@@ -301,16 +378,16 @@ __global__ __launch_bounds__(256) void bwd_dw_kernel(const BwdParams P) {
 // pixels t / 32 + 8 j), which evaluate the phases.  WONCE (K_alloc <= 128):
 // conj(W) of all the instance's eigenpairs is staged once, and the steps
 // stage only M.
-template <bool WONCE>
-__global__ __launch_bounds__(256) void bwd_dx_kernel(const BwdParams P) {
+template <int KONCE>
+__global__ __launch_bounds__(256, KONCE == 64 ? 3 : 2) void bwd_dx_kernel(const BwdParams P) {
   __shared__ float2 sW[32][65];   // conj(W) for 32 antennas x 64 eigenpairs (+1 pad: column reads)
   __shared__ float sWn[32][65];   // its negated imaginary parts
   __shared__ float2 sM[64][65];   // M for 64 eigenpairs x 64 pixels; then H re / im [2][64 p][33] floats
   __shared__ double sP[3][64];    // the chunk's pixel coordinates
   __shared__ double sX[32][4];    // the tile's scaled antenna positions
-  __shared__ double sh[3][256];
   __shared__ int sOff[kMaxEig];   // staged eigenpair -> offset of its column of W (src * L), -1 if none
-  __shared__ float2 sWall[32][129];  // WONCE: conj(W) for 32 antennas x 128 eigenpairs (+1 pad)
+  constexpr bool WONCE = KONCE > 0;
+  __shared__ float2 sWall[32][KONCE + 1];  // WONCE: conj(W) for 32 antennas x KONCE eigenpairs (+1 pad)
   const InstDesc& D = *P.desc;
   const int l0 = blockIdx.x * 32, s = blockIdx.y;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -363,7 +440,7 @@ __global__ __launch_bounds__(256) void bwd_dx_kernel(const BwdParams P) {
     if (kc == 0 && t < 192) pnext = p_ok ? P.pix[pq + (t >> 6) * P.pix_ld] : 0.0;
   };
   if constexpr (WONCE) {
-    for (int i = t; i < 32 * 128; i += 256) {
+    for (int i = t; i < 32 * KONCE; i += 256) {
       const int ll = i & 31, kk = i >> 5;  // a wave reads 32 consecutive antennas of two columns of W
       const int src = kk < K_pad ? D.perm[kk] : -1;
       float2 wv = make_float2(0.0f, 0.0f);
@@ -404,9 +481,9 @@ __global__ __launch_bounds__(256) void bwd_dx_kernel(const BwdParams P) {
       if (npc < p1) load_step(npc, last ? 0 : 64 * (kq + 1));  // workgroup-uniform
       if constexpr (WONCE) {
         if (part == 0)
-          h_chunk_all<0, 129>(acc, sWall, 64 * kq, sM, blk, lane);
+          h_chunk_all<0, KONCE + 1>(acc, sWall, 64 * kq, sM, blk, lane);
         else
-          h_chunk_all<1, 129>(acc, sWall, 64 * kq, sM, blk, lane);
+          h_chunk_all<1, KONCE + 1>(acc, sWall, 64 * kq, sM, blk, lane);
       } else {
         if (part == 0)
           h_chunk<0>(acc, sW, sWn, sM, blk, lane);
@@ -440,166 +517,6 @@ __global__ __launch_bounds__(256) void bwd_dx_kernel(const BwdParams P) {
     }
     __syncthreads();  // sH (in sM) and sP are restaged by the next chunk
   }
-  sh[0][t] = gx;
-  sh[1][t] = gy;
-  sh[2][t] = gz;
-  __syncthreads();
-  if (tp == 0 && l < P.L_pad) {
-    double a = 0, b = 0, c = 0;
-    for (int j = 0; j < 8; ++j) {
-      a += sh[0][t + 32 * j];
-      b += sh[1][t + 32 * j];
-      c += sh[2][t + 32 * j];
-    }
-    double* o = P.dx_part + ((int64_t)s * P.L_pad + l) * 3;
-    o[0] = a;
-    o[1] = b;
-    o[2] = c;
-  }
-}
-
-// dW and dx partials together when every eigenpair fits one 64-wide slice
-// (K_alloc <= 64): each 64-pixel chunk's phases [64 p][32 l] and M [64 k][64 p]
-// are staged once and serve both contractions.  grid (L_pad/32, n_split), 256
-// threads; wave w owns
-//   the dW block of eigenpairs 32 (w / 2) .. + 31, part w % 2 (re / im),
-//     accumulated over the split (A = phases, rows l; B = M, columns k);
-//   the H block of pixels 32 (w / 2) .. + 31 of the chunk, part w % 2
-//     (A = conj(W), rows l; B = M, columns p).
-// H goes through LDS to the threads that own (antenna t % 32, pixels t / 32 + 8 j),
-// which form Im(H B) p with the staged phases.  The next chunk's M and pixel
-// coordinates are loaded into registers while the current chunk is processed.
-__global__ __launch_bounds__(256) void bwd_fused_kernel(const BwdParams P) {
-  __shared__ float2 sW[32][65];   // conj(W) [32 l][64 k], staged once (+1 pad: column reads)
-  __shared__ float2 sM[64][65];   // M [64 k][64 p] (+1 pad: column reads); then H re / im [2][64 p][33] floats
-  __shared__ float2 sB[64][32];   // phases [64 p][32 l]
-  __shared__ float sBn[64][32];   // their negated sines
-  __shared__ double sP[3][64];    // the chunk's pixel coordinates
-  __shared__ double sX[32][4];    // the tile's scaled antenna positions, staged once
-  const InstDesc& D = *P.desc;
-  const int l0 = blockIdx.x * 32, s = blockIdx.y;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  // Im(H B) p: consecutive lanes take consecutive antennas, so the reads of
-  // the phases and of H (stored pixel-major, rows padded to 33) are free of
-  // bank conflicts
-  const int tl = t & 31, tp = t >> 5;
-  const int l = l0 + tl;
-  const int blk = __builtin_amdgcn_readfirstlane(wave >> 1), part = __builtin_amdgcn_readfirstlane(wave & 1);
-  const bool dw_active = 32 * blk < P.K_alloc;  // this wave's dW block exists
-  const int64_t p0 = (int64_t)s * P.split_len;
-  int64_t p1 = p0 + P.split_len;
-  if (p1 > P.n_pix) p1 = P.n_pix;
-  const int K_pad = P.dyn->K_pad;
-  const float* Er = P.E;
-  const float* Ei = P.E + (int64_t)P.K_alloc * P.n_pix;
-  const float* Wf = (const float*)P.W;
-  float* const sH = reinterpret_cast<float*>(&sM[0][0]);  // [2 parts][64 p][33]
-  if (t < 128) (&sX[0][0])[t] = D.xs[4 * l0 + t];            // rows l0 .. l0 + 31 < L_pad
-  for (int i = t; i < 32 * 64; i += 256) {
-    const int ll = i & 31, kk = i >> 5;  // a wave reads 32 consecutive antennas of two columns of W
-    float2 wv = make_float2(0.0f, 0.0f);
-    if (l0 + ll < P.L && kk < K_pad) {
-      const int src = D.perm[kk];
-      if (src >= 0) {
-        const float* w = Wf + 2 * ((int64_t)src * P.L + l0 + ll);
-        wv = make_float2(w[0], -w[1]);
-      }
-    }
-    sW[ll][kk] = wv;
-  }
-  // the next chunk's M (16 values per thread: eigenpair 4 j + t / 64, pixel
-  // t % 64) and pixel coordinates (threads < 192: axis t / 64, pixel t % 64)
-  // are loaded into registers while the current chunk is processed
-  float2 mnext[16];
-  double pnext = 0.0;
-  // Every lane loads (pixels past the split and eigenpairs past K_pad from
-  // row 0 and the split's last pixel) and then zeroes what lies outside, so
-  // the loads carry no branches.
-  auto load_chunk = [&](int64_t pc) {
-    const int pp = t & 63;
-    const int64_t p = pc + pp;
-    const bool p_ok = p < p1;
-    const int64_t pq = p_ok ? p : p1 - 1;
-    const int64_t r0 = (int64_t)(t >> 6) * P.n_pix + pq, st4 = 4 * P.n_pix;  // rows advance by 4 per j
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const int kk = 4 * j + (t >> 6);
-      const int64_t e = kk < K_pad ? r0 + j * st4 : pq;
-      const float er = Er[e], ei = Ei[e];
-      mnext[j] = (p_ok && kk < K_pad) ? make_float2(er, ei) : make_float2(0.0f, 0.0f);
-    }
-    if (t < 192) pnext = p_ok ? P.pix[pq + (t >> 6) * P.pix_ld] : 0.0;
-  };
-  load_chunk(p0);
-  // -Im conj(W) of this lane's rows, for the real part of H (waves of part 0)
-  float wny[32];
-  __syncthreads();  // conj(W) is staged
-  if (part == 0)
-#pragma unroll
-    for (int st = 0; st < 32; ++st) wny[st] = -sW[lane & 31][2 * st + (lane >> 5)].y;
-  bwd_f32x16 dw;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) dw[r] = 0.0f;
-  double gx = 0.0, gy = 0.0, gz = 0.0;
-  for (int64_t pc = p0; pc < p1; pc += 64) {
-#pragma unroll
-    for (int j = 0; j < 16; ++j) sM[4 * j + (t >> 6)][t & 63] = mnext[j];
-    if (t < 192) sP[t >> 6][t & 63] = pnext;
-    __syncthreads();
-    if (pc + 64 < p1) load_chunk(pc + 64);  // workgroup-uniform
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int i = t + 256 * j;
-      const int pp = i >> 5, ll = i & 31;
-      float c, sn;  // pixels past the split have coordinates 0 and get phases 0
-      phase_b(&sX[ll][0], sP[0][pp], sP[1][pp], sP[2][pp], c, sn);
-      const bool ok = pc + pp < p1;
-      sB[pp][ll] = ok ? make_float2(c, sn) : make_float2(0.0f, 0.0f);
-      sBn[pp][ll] = ok ? -sn : 0.0f;
-    }
-    __syncthreads();
-    // dW += B M^T over the chunk's pixels, then H = conj(W) M for this wave's
-    // pixel half
-    bwd_f32x16 h;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) h[r] = 0.0f;
-    if (part == 0) {
-      if (dw_active) dw_chunk<0>(dw, sB, sBn, sM, blk, lane);
-      h_chunk_w<0>(h, sW, wny, sM, blk, lane);
-    } else {
-      if (dw_active) dw_chunk<1>(dw, sB, sBn, sM, blk, lane);
-      h_chunk_w<1>(h, sW, wny, sM, blk, lane);
-    }
-    __syncthreads();  // every wave is done with sM
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int ll = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      sH[(part * 64 + 32 * blk + (lane & 31)) * 33 + ll] = h[r];
-    }
-    __syncthreads();
-    if (l < P.L) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        // pixels past the split add exact zeros (their phases, M and hence
-        // H, and coordinates are all 0)
-        const int pp = tp + 8 * j;
-        const float2 b = sB[pp][tl];
-        const float hr = sH[pp * 33 + tl], hi = sH[(64 + pp) * 33 + tl];
-        const double v = (double)fmaf(hr, b.y, hi * b.x);  // Im(H B)
-        gx += v * sP[0][pp];
-        gy += v * sP[1][pp];
-        gz += v * sP[2][pp];
-      }
-    }
-    __syncthreads();  // sB, sP and sM (holding H) are restaged by the next chunk
-  }
-  if (dw_active) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int ll = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), k = 32 * blk + (lane & 31);
-      P.dW_part[(((int64_t)s * P.L_pad + (l0 + ll)) * P.K_alloc + k) * 2 + part] = dw[r];
-    }
-  }
   double* const sh = reinterpret_cast<double*>(&sM[0][0]);  // [3][256]; sM is free after the loop
   sh[t] = gx;
   sh[256 + t] = gy;
@@ -631,7 +548,9 @@ __global__ __launch_bounds__(256) void bwd_zero_kernel(int64_t n_w, int K, float
 }
 
 // Fixed-order sums over splits, scattered back to the caller's eigenpair order.
-__global__ __launch_bounds__(256) void bwd_reduce_kernel(const BwdParams P, float* __restrict__ dW,
+// Bound by reads in flight (67 MB for 256 antennas and 64 eigenpairs): one wave
+// per workgroup spreads them over the chip.
+__global__ __launch_bounds__(64) void bwd_reduce_kernel(const BwdParams P, float* __restrict__ dW,
                                                          float* __restrict__ dd, double* __restrict__ dx) {
   const InstDesc& D = *P.desc;
   const int K_pad = P.dyn->K_pad;
@@ -642,7 +561,8 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(const BwdParams P, floa
     const int src = D.perm[k];
     if (src >= 0) {
       double re = 0.0, im = 0.0;
-      for (int s = 0; s < P.n_split; ++s) {
+#pragma unroll 8
+      for (int s = 0; s < P.n_dw; ++s) {
         const double* q = P.dW_part + (((int64_t)s * P.L_pad + l) * P.K_alloc + k) * 2;
         re += q[0];
         im += q[1];
@@ -651,6 +571,7 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(const BwdParams P, floa
       dW[2 * ((int64_t)src * P.L + l) + 1] = (float)(2.0 * im);
       if (l == 0) {
         double a = 0.0;
+#pragma unroll 8
         for (int s = 0; s < P.n_split; ++s) a += P.dd_part[(int64_t)k * P.n_split + s];
         dd[src] = (float)a;
       }
@@ -659,6 +580,7 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(const BwdParams P, floa
   if (idx < (int64_t)P.L * 3) {
     const int l = (int)(idx % P.L), c = (int)(idx / P.L);
     double a = 0.0;
+#pragma unroll 8
     for (int s = 0; s < P.n_split; ++s) a += P.dx_part[((int64_t)s * P.L_pad + l) * 3 + c];
     dx[(int64_t)c * P.L + l] = P.scale_x * a;
   }
@@ -668,17 +590,19 @@ hipError_t launch_backward(const BwdParams& p, hipStream_t s) {
   hipLaunchKernelGGL(bwd_m_kernel, dim3(p.K_alloc, p.n_split), dim3(256), 0, s, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (p.K_alloc <= 64) {  // one eigenpair slice: both contractions share their staged tiles
-    hipLaunchKernelGGL(bwd_fused_kernel, dim3(p.L_pad / 32, p.n_split), dim3(256), 0, s, p);
+  auto dw = [&](auto* fn, int nkt) -> hipError_t {
+    const size_t lds = (size_t)2 * 4 * (2 * 16 * nkt * 4) * sizeof(uint4);
+    const hipError_t r = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (r != hipSuccess) return r;
+    hipLaunchKernelGGL(fn, dim3((p.L_pad + 127) / 128, (p.K_alloc + 16 * nkt - 1) / (16 * nkt), p.n_dw), dim3(512),
+                       lds, s, p);
     return hipGetLastError();
-  }
-  hipLaunchKernelGGL(bwd_dw_kernel, dim3(p.L_pad / 32, (p.K_alloc + 63) / 64, p.n_split), dim3(256), 0, s, p);
-  e = hipGetLastError();
+  };
+  e = p.K_alloc <= 64 ? dw(&bwd_dw_kernel<4>, 4) : dw(&bwd_dw_kernel<8>, 8);
   if (e != hipSuccess) return e;
-  if (p.K_alloc <= 128)
-    hipLaunchKernelGGL(bwd_dx_kernel<true>, dim3(p.L_pad / 32, p.n_split), dim3(256), 0, s, p);
-  else
-    hipLaunchKernelGGL(bwd_dx_kernel<false>, dim3(p.L_pad / 32, p.n_split), dim3(256), 0, s, p);
+  auto* const dx = p.K_alloc <= 64 ? &bwd_dx_kernel<64> : p.K_alloc <= 128 ? &bwd_dx_kernel<128> : &bwd_dx_kernel<0>;
+  hipLaunchKernelGGL(dx, dim3(p.L_pad / 32, p.n_split), dim3(256), 0, s, p);
   return hipGetLastError();
 }
 
@@ -691,7 +615,7 @@ hipError_t launch_backward_reduce(const BwdParams& p, void* dW, float* dd, doubl
   if (e != hipSuccess) return e;
   n = (int64_t)p.L * p.K_alloc;
   if (n < (int64_t)p.L * 3) n = (int64_t)p.L * 3;
-  hipLaunchKernelGGL(bwd_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p,
+  hipLaunchKernelGGL(bwd_reduce_kernel, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, s, p,
                      static_cast<float*>(dW), dd, dx);
   return hipGetLastError();
 }
