@@ -102,10 +102,6 @@ bool synth_tile_info(int precision, int id, int* kc, int* nt, int* waves);
 // Whether a class may use a tile (its eigenpairs per pass do not exceed the class's largest K).
 bool synth_tile_allowed(int precision, int id, int k_class);
 hipError_t launch_synth_tile(const FwdParams& p, int precision, int id, hipStream_t s);
-// The default tile for the largest K_alloc of the call.
-hipError_t launch_synth(const FwdParams& p, int max_K_alloc, int precision, int tile_pixels_out[1],
-                        hipStream_t s);
-int synth_tile_pixels(int max_K_alloc, int precision);
 
 // Zero-fill of a float buffer (graph-capture safe, no memset nodes).
 hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t s);

@@ -31,7 +31,6 @@ struct cd {
   double x, y;
 };
 __device__ __forceinline__ cd operator+(cd a, cd b) { return {a.x + b.x, a.y + b.y}; }
-__device__ __forceinline__ cd operator*(double s, cd a) { return {s * a.x, s * a.y}; }
 // a b, a conj(b), and accumulating forms
 __device__ __forceinline__ cd mul(cd a, cd b) { return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
 __device__ __forceinline__ void fma_c(cd& r, cd a, cd b) {

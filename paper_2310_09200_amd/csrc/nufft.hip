@@ -35,8 +35,6 @@
 
 namespace bb {
 
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
 // ---------------------------------------------------------------------------
 // Per instance: eigenpair order grouped by level (stable), level starts, and
 // the diagonal term sum_{k in l} d_k ||w_k||^2 added into diag[l].  Workgroup

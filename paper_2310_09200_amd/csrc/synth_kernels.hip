@@ -57,11 +57,8 @@ namespace bb {
 
 constexpr size_t kMaxLds = 160 * 1024;  // LDS of a gfx950 compute unit
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
 // Pointers read out of an instance descriptor are generic to the compiler, and
@@ -785,7 +782,11 @@ struct Form {
 // 128, or more.  Each class has a default shape (the measured best on this
 // GPU) and may use every shape of the list whose eigenpairs per pass do not
 // exceed the class's largest K (so that no wave of a tile is idle at that K).
-// Register budget: 512 / OCC VGPRs a wave at OCC waves per SIMD.
+// Register budget: 512 / OCC VGPRs a wave at OCC waves per SIMD.  Three waves suit
+// the 32 x 64 tile (four spill 60 registers: 20 antennas, 20 eigenpairs, 1500^2
+// pixels 269 us against 327), and in the four-product form four waves of 2 x 4
+// blocks the 64 x 128 one (50 antennas, 40 eigenpairs, 2048^2 pixels: 656 us
+// against 732 in sixteen waves of 1 x 2).
 template <class... T>
 struct TileList {};
 
@@ -795,8 +796,8 @@ template <>
 struct Cands<0> {  // 4 products: Er / Ei accumulators, half as many as three planes need, so twice the pixels a wave
   using L = TileList<Tile<2, 8, 8, 1>,      // 0: 256 x 128
                      Tile<2, 4, 4, 2>,      // 1: 128 x 128
-                     Tile<1, 2, 4, 4, 4>,   // 2: 64 x 128, 16 waves
-                     Tile<1, 2, 2, 2, 4>,   // 3: 32 x 64, 4 waves
+                     Tile<2, 4, 2, 2>,      // 2: 64 x 128, 4 waves
+                     Tile<1, 2, 2, 2, 3>,   // 3: 32 x 64, 4 waves
                      Tile<2, 4, 4, 1>>;     // 4: 128 x 64, 4 waves
   static constexpr int dflt[4] = {3, 2, 1, 0};
 };
@@ -804,8 +805,8 @@ template <>
 struct Cands<1> {
   using L = TileList<Tile<2, 8, 8, 1>,      // 0: 256 x 128
                      Tile<2, 4, 4, 2>,      // 1: 128 x 128
-                     Tile<1, 2, 4, 4, 4>,   // 2: 64 x 128, 16 waves
-                     Tile<1, 2, 2, 2, 4>,   // 3: 32 x 64, 4 waves
+                     Tile<2, 4, 2, 2>,      // 2: 64 x 128, 4 waves
+                     Tile<1, 2, 2, 2, 3>,   // 3: 32 x 64, 4 waves
                      Tile<2, 4, 4, 1>,      // 4: 128 x 64, 4 waves
                      Tile<2, 4, 8, 1>>;     // 5: 256 x 64
   static constexpr int dflt[4] = {3, 2, 1, 0};
@@ -815,7 +816,7 @@ struct Cands<2> {  // 3 products: k1, k2, k3 accumulators
   using L = TileList<Tile<2, 4, 8, 1>,      // 0: 256 x 64
                      Tile<2, 4, 4, 1>,      // 1: 128 x 64, 4 waves
                      Tile<2, 2, 2, 4>,      // 2: 64 x 128
-                     Tile<1, 2, 2, 2, 4>,   // 3: 32 x 64, 4 waves, up to four workgroups a CU
+                     Tile<1, 2, 2, 2, 3>,   // 3: 32 x 64, 4 waves, three workgroups a CU
                      Tile<2, 2, 4, 2>,      // 4: 128 x 64
                      Tile<1, 4, 4, 2>,      // 5: 64 x 128
                      Tile<1, 4, 8, 2, 4>,   // 6: 128 x 128, 16 waves
@@ -831,7 +832,7 @@ struct Cands<3> {
   using L = TileList<Tile<2, 4, 8, 1>,      // 0: 256 x 64
                      Tile<2, 4, 4, 2>,      // 1: 128 x 128
                      Tile<1, 2, 4, 4, 4>,   // 2: 64 x 128, 16 waves
-                     Tile<1, 2, 2, 2, 4>,   // 3: 32 x 64, 4 waves
+                     Tile<1, 2, 2, 2, 3>,   // 3: 32 x 64, 4 waves
                      Tile<2, 4, 4, 1>>;     // 4: 128 x 64, 4 waves
   static constexpr int dflt[4] = {3, 2, 1, 0};
 };
@@ -851,6 +852,10 @@ struct Narrow<Tile<2, 4, 4, 2>> {
   using T = Tile<2, 4, 4, 1>;
 };
 template <>
+struct Narrow<Tile<2, 4, 2, 2>> {
+  using T = Tile<2, 2, 2, 2>;
+};
+template <>
 struct Narrow<Tile<1, 2, 4, 4, 4>> {
   using T = Tile<1, 2, 4, 2, 4>;
 };
@@ -859,8 +864,10 @@ template <class C, class H, int NPL>
 static hipError_t launch_shape(FwdParams p, hipStream_t s) {
   using N = typename Narrow<C>::T;
   if constexpr (!std::is_same<N, C>::value) {
-    if (p.n_tiles < compute_units()) {
-      p.n_tiles = (p.n_pix + N::NT - 1) / N::NT;
+    // only where its tiles still run all at once
+    const int64_t n = (p.n_pix + N::NT - 1) / N::NT;
+    if (p.n_tiles < compute_units() && n <= (int64_t)compute_units() * std::max(1, 4 * N::OCC / N::WAVES)) {
+      p.n_tiles = n;
       return launch_cfg<N, H, NPL>(p, s);
     }
   }
@@ -950,18 +957,6 @@ hipError_t launch_synth_tile(const FwdParams& p, int precision, int id, hipStrea
     case 3: return launch_prec_tile<3>(p, id, s);
     default: return launch_prec_tile<0>(p, id, s);
   }
-}
-
-int synth_tile_pixels(int max_K_alloc, int precision) {
-  int nt = 0;
-  synth_tile_info(precision, synth_default_tile(precision, synth_k_class(max_K_alloc)), nullptr, &nt, nullptr);
-  return nt;
-}
-
-hipError_t launch_synth(const FwdParams& p, int max_K_alloc, int precision, int tile_pixels_out[1],
-                        hipStream_t s) {
-  if (tile_pixels_out) tile_pixels_out[0] = synth_tile_pixels(max_K_alloc, precision);
-  return launch_synth_tile(p, precision, synth_default_tile(precision, synth_k_class(max_K_alloc)), s);
 }
 
 // Phase-generation throughput probe (measurement only): every thread takes one
