@@ -560,8 +560,10 @@ __global__ __launch_bounds__(512) void hetrd_kernel(cd* __restrict__ A, int n, d
         if (t == 0) atomicOr(info, kTrdLate);
         return;
       }
-      p = s_p[t];
-      y = s_y[t];
+      if (t < n) {  // the records cover R NW rows, which may be fewer than the threads
+        p = s_p[t];
+        y = s_y[t];
+      }
       if (t < 64 && t < kRec) {  // clear the buffer of the column before: every workgroup has published this one
         uint64_t* const old = pub + ((j + 2) % 3) * kAll + wg * kRec;
         for (int e = t; e < kRec; e += 64)
