@@ -860,8 +860,31 @@ struct Narrow<Tile<1, 2, 4, 4, 4>> {
   using T = Tile<1, 2, 4, 2, 4>;
 };
 
+// The shape of the same rows and pixels that takes a tile's place where local
+// memory (antenna positions, level partials) leaves a CU fewer workgroups than the
+// registers do: more waves a workgroup (391 antennas, 36 eigenpairs, 12 levels,
+// 1680^2 pixels, 3 epochs in bf16: 5.3 ms against 7.3), or more registers a wave
+// (29 antennas, 18 eigenpairs, 10 levels: 236 us against 243).
+template <class C>
+struct Roomy {
+  using T = C;
+};
+template <>
+struct Roomy<Tile<2, 4, 2, 2>> {
+  using T = Tile<2, 2, 2, 4>;
+};
+template <>
+struct Roomy<Tile<1, 2, 2, 2, 3>> {
+  using T = Tile<1, 2, 2, 2, 2>;
+};
+
 template <class C, class H, int NPL>
 static hipError_t launch_shape(FwdParams p, hipStream_t s) {
+  using R = typename Roomy<C>::T;
+  if constexpr (!std::is_same<R, C>::value) {
+    if (kMaxLds / C::lds_bytes(NPL, p.max_L_pad, p.n_levels) < (size_t)(4 * C::OCC / C::WAVES))
+      return launch_cfg<R, H, NPL>(p, s);
+  }
   using N = typename Narrow<C>::T;
   if constexpr (!std::is_same<N, C>::value) {
     // only where its tiles still run all at once
