@@ -436,6 +436,12 @@ __global__ __launch_bounds__(256, MF == 1 && NL < 2 ? 3 : 2) void nufft_gather_s
   }
 }
 
+// Blocks of `px` points of a periodic axis of n points that w consecutive points
+// (w <= n / 2) reach at most.  Across the wrap the last block may be a remainder
+// of r = n mod px points, one block more: with a points before the wrap and w - a
+// behind it, 1 + ceil((a - r) / px) + ceil((w - a) / px) blocks.
+int64_t axis_reach(int n, int px, int w) { return (w - 1 + px - 1) / px + 1 + (n % px ? 1 : 0); }
+
 }  // namespace
 
 int nufft_gather_z(const NufftGeom& g) {
@@ -480,8 +486,9 @@ hipError_t launch_nufft_spread_gather(const NufftGeom& g, const NufftInst* insts
                      128 / Zc, nbx, nby, nparts);
   e = launch_scan_i32(nparts, n_blocks, part_off, nullptr, scan_tmp, s);
   if (e != hipSuccess) return e;
-  // a baseline reaches at most 2 x 5 blocks of 8 x 2 columns, 3 x 5 of 4 x 2, 5 x 5 of 2 x 2
-  const int64_t parts = n_blocks + (Zc == 16 ? 10 : Zc == 32 ? 15 : 25) * max_src / kPartLoad;
+  // a wave takes one part: sum over blocks of ceil(load / kPartLoad) of them at most
+  const int64_t reach = axis_reach(g.N[0], 128 / Zc, g.w) * axis_reach(g.N[1], kBlockY, g.w);
+  const int64_t parts = n_blocks + reach * max_src / kPartLoad;
   const int64_t per = 4 * kXcds * (kRun / 4);  // whole runs for every XCD
   const unsigned wgs = (unsigned)((parts + per - 1) / per * (kRun / 4) * kXcds);
   auto run = [&](auto zc, auto mc, auto lc) -> hipError_t {

@@ -113,3 +113,36 @@ def test_line_lengths(ctx, length):
     uvw = np.array([extent * 1.01, 0.35, 0.35])
     assert nf.plan_params(eps, uvw, nf.rotate(pix, frame))["M"][0] == length
     _check(ctx, 1, items, pix, frame, uvw, eps, 1)
+
+
+# Blocks of more than one part (1024 baselines), where a baseline reaches the most of them: stations on a short
+# diagonal, ordered along it, so that every baseline lies just past the grid's origin, and 18 points on axes 0 and 1,
+# of which the last block of 8 or 4 columns holds 2.
+@pytest.mark.parametrize("eps, depth, n_ant", [(1e-7, 16, 305), (1e-6, 16, 305), (1e-7, 32, 240)])
+def test_spread_parts_across_the_wrap(ctx, eps, depth, n_ant):
+    from paper_2310_09200_amd import Batch, NufftSynthesis
+    print(f"case nufft parts eps={eps} depth={depth} antennas={n_ant}", flush=True)
+    w = nf.kernel_width(eps)
+    g = np.random.default_rng(n_ant + w)
+    frame = np.array(sims.tangent_basis(40.0))
+    pix = _pixels(14, 20.0, frame)
+    c = nf.rotate(pix, frame)
+    S = 0.5 * (c.max(axis=0) - c.min(axis=0))
+    uvw = np.array([(18 - w - 0.5) / (8 * S[0]), (18 - w - 0.5) / (8 * S[1]), (depth - w - 0.5) / (8 * S[2])])
+    P = nf.plan_params(eps, uvw, c)
+    assert list(P["N"]) == [18, 18, depth]
+    x = np.sort(g.random(n_ant))[::-1, None] * (np.array([0.3, 0.3, 0.0]) * P["h"]) @ frame
+    W = (g.normal(size=(n_ant, 6)) + 1j * g.normal(size=(n_ant, 6))).astype(np.complex64)
+    d, lev = g.normal(size=6).astype(np.float32), np.array([0, 1, 0, 1, 0, -1], np.int32)
+    plan = NufftSynthesis(ctx, pix, 2, n_ant, 6, eps, frame, uvw)
+    plan.collect_eig_batched(Batch([(0, x, 1.0, W, d, lev)], ctx.device))
+    plan.emit()
+    plan.sync()
+    got = plan.images.double().cpu().numpy()
+    plan.close()
+    ref = [(x, 1.0, W.astype(np.complex128), d.astype(np.float64), np.arange(2)[:, None] == lev[None])]
+    want = nf.nufft_images(ref, pix, eps, X=uvw, frame=frame)
+    lo, hi = c.min(axis=0), c.max(axis=0)
+    inside = np.all(np.abs(c - (lo + hi) / 2) < (hi - lo) / 2 * (1 - 1e-9), axis=1)
+    for a, b in zip(got, want):
+        assert np.max(np.abs(a - b)[inside]) <= 1e-5 * np.max(np.abs(b))
