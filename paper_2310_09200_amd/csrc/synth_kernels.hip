@@ -333,7 +333,7 @@ struct Tile {
   // and each k-wave's level partials, sized by the launch so that small problems
   // leave room for a second workgroup on the CU.
   static constexpr size_t buf_bytes(int npl) { return (size_t)npl * NPB * 256 * sizeof(uint2); }
-  static size_t lds_bytes(int npl, int max_L_pad, int n_part_levels) {
+  static constexpr size_t lds_bytes(int npl, int max_L_pad, int n_part_levels) {
     return 2 * buf_bytes(npl) + (size_t)max_L_pad * 32 + (size_t)WK * n_part_levels * NT * sizeof(float);
   }
 };
@@ -864,7 +864,8 @@ struct Narrow<Tile<1, 2, 4, 4, 4>> {
 // memory (antenna positions, level partials) leaves a CU fewer workgroups than the
 // registers do: more waves a workgroup (391 antennas, 36 eigenpairs, 12 levels,
 // 1680^2 pixels, 3 epochs in bf16: 5.3 ms against 7.3), or more registers a wave
-// (29 antennas, 18 eigenpairs, 10 levels: 236 us against 243).
+// (29 antennas, 18 eigenpairs, 10 levels: 236 us against 243).  The sixteen waves of
+// 128 x 128 need more than a CU holds (512 antennas from 13 levels, 1024 from 9).
 template <class C>
 struct Roomy {
   using T = C;
@@ -877,16 +878,23 @@ template <>
 struct Roomy<Tile<1, 2, 2, 2, 3>> {
   using T = Tile<1, 2, 2, 2, 2>;
 };
+template <>
+struct Roomy<Tile<1, 4, 8, 2, 4>> {
+  using T = Tile<2, 4, 4, 2>;
+};
 
 template <class C, class H, int NPL>
 static hipError_t launch_shape(FwdParams p, hipStream_t s) {
   using R = typename Roomy<C>::T;
+  static_assert(R::NT == C::NT && R::KC == C::KC, "the same rows and pixels");
+  static_assert(R::lds_bytes(NPL, kMaxAnt, kMaxLevels) <= kMaxLds, "a listed shape runs every instance");
   if constexpr (!std::is_same<R, C>::value) {
     if (kMaxLds / C::lds_bytes(NPL, p.max_L_pad, p.n_levels) < (size_t)(4 * C::OCC / C::WAVES))
       return launch_cfg<R, H, NPL>(p, s);
   }
   using N = typename Narrow<C>::T;
   if constexpr (!std::is_same<N, C>::value) {
+    static_assert(N::lds_bytes(NPL, kMaxAnt, kMaxLevels) <= kMaxLds, "and so does its narrow form");
     // only where its tiles still run all at once
     const int64_t n = (p.n_pix + N::NT - 1) / N::NT;
     if (p.n_tiles < compute_units() && n <= (int64_t)compute_units() * std::max(1, 4 * N::OCC / N::WAVES)) {
