@@ -44,6 +44,10 @@
  *    0xFF bytes (NaN as float32 / float64) before use, at handle or plan
  *    creation and at each call that takes a workspace, so that a read of
  *    unwritten workspace memory shows in the results.
+ *  - Debug aid: with BB_DEBUG_TRD_LATE set likewise, the workgroups that share
+ *    a pre-step eigenproblem (129 to 512 antennas) give up waiting for each
+ *    other at once, as they do when other work keeps them from running
+ *    together for a second, and the call takes the library's solver instead.
  */
 #ifndef BLUEBILD_H
 #define BLUEBILD_H

@@ -540,7 +540,8 @@ static bb_status solve_eigen(bb_synth h, int n, double wavelength_m, const doubl
   b.tau = at<double>(h, L.tau);
   b.pub = at<uint64_t>(h, L.pub);
   b.status = at<bb::EigStatus>(h, L.status);
-  BB_HIP(ctx, bb::launch_eig_reduce(b, ant_xyz, vis, n, wavelength_m, identity, s));
+  const uint64_t wait = bb_host::debug_trd_late() ? 0 : bb::kTrdWaitTicks;
+  BB_HIP(ctx, bb::launch_eig_reduce(b, ant_xyz, vis, n, wavelength_m, identity, wait, s));
   rocblas_set_stream(ctx->rb, s);
   if (L.solver_bytes > 0 && rocblas_set_workspace(ctx->rb, h->ws + L.solver, L.solver_bytes) != rocblas_status_success)
     return fail(ctx, BB_ERR_DEVICE, "rocblas_set_workspace failed");

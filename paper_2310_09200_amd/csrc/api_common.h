@@ -46,14 +46,22 @@ inline bb_status fail(bb_context ctx, bb_status s, const char* fmt, ...) {
 
 inline bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
 
+// Whether an environment variable is set (and not "0").
+inline bool debug_flag(const char* name) {
+  const char* v = std::getenv(name);
+  return v && v[0] && !(v[0] == '0' && v[1] == 0);
+}
+
 // Debug aid: with BB_DEBUG_FILL set (and not "0") in the environment, the
 // library fills every workspace it is given with 0xFF bytes (a NaN in float32
 // and float64, -1 in integers) before using it, so that a read of workspace
 // memory that no kernel wrote shows up in the results.
-inline bool debug_fill() {
-  const char* v = std::getenv("BB_DEBUG_FILL");
-  return v && v[0] && !(v[0] == '0' && v[1] == 0);
-}
+inline bool debug_fill() { return debug_flag("BB_DEBUG_FILL"); }
+
+// Debug aid: with BB_DEBUG_TRD_LATE set the workgroups of a tridiagonalisation
+// give up their first wait for each other, as they do when they cannot run
+// together in time, and the call takes the library's solver.
+inline bool debug_trd_late() { return debug_flag("BB_DEBUG_TRD_LATE"); }
 
 }  // namespace bb_host
 

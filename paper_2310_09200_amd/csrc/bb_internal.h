@@ -143,6 +143,7 @@ constexpr int kEigMaxN = 512;
 constexpr int kHermParts = 64;       // workgroups (partial sums) of the Hermiticity check
 constexpr int kTrdLate = 1;          // EigStatus::trd: a wait between workgroups ran out (nothing computed)
 constexpr int kTrdNotFinite = 2;     // the tridiagonal matrix is not finite
+constexpr uint64_t kTrdWaitTicks = 100000000ULL;  // longest wait: one second of the 100 MHz clock
 struct EigStatus {
   int chol;                          // 0, or the first leading minor of G that is not positive
   int trd;
@@ -164,8 +165,9 @@ struct EigBuffers {
 };
 size_t eig_pub_bytes();
 // Inputs (ant n x 3 column-major, vis n x n complex128) to the tridiagonal matrix (D, E).
+// wait_ticks: bound of the waits between workgroups (0: the first one gives up).
 hipError_t launch_eig_reduce(const EigBuffers& b, const double* ant, const double* vis, int n, double wl,
-                             bool identity, hipStream_t s);
+                             bool identity, uint64_t wait_ticks, hipStream_t s);
 // Eigenvectors in A from those of the tridiagonal matrix in T.
 hipError_t launch_eig_vectors(const EigBuffers& b, int n, bool identity, hipStream_t s);
 

@@ -338,12 +338,12 @@ __global__ __launch_bounds__(256) void tri_product_kernel(const double* __restri
 // The exchange goes through 64-bit words in memory, valid once they differ from a
 // signalling NaN that arithmetic cannot produce, in three buffers by turns: a
 // buffer is cleared by its rows' owners after the next column's exchange, when all
-// have read it, and used again one column later.  Waits end after kWaitTicks;
-// then info says so and every workgroup returns.
+// have read it, and used again one column later.  Waits end after wait_ticks;
+// then info says so, every workgroup returns, and D and E are zeros: the solver
+// that is already queued behind must not iterate on half a matrix.
 // Bound by its dependent steps: 2.1 us a column in one workgroup (n = 64), 5.3 us
 // with 32 of them (n = 512).
 constexpr uint64_t kEmpty = 0xFFF4DEADBEEF5A5AULL;
-constexpr uint64_t kWaitTicks = 100000000ULL;  // one second of the 100 MHz clock
 
 template <int NW, int TR, int RA, int CB>
 struct TrdCfg {
@@ -401,7 +401,8 @@ __device__ __forceinline__ void halve(double (&s)[N], int h, bool up) {
 template <class K, int NW, int TR, int RA, int CB>
 __global__ __launch_bounds__(512) void hetrd_kernel(cd* __restrict__ A, int n, double* __restrict__ D,
                                                     double* __restrict__ E, cd* __restrict__ tau_out,
-                                                    uint64_t* __restrict__ pub, int* __restrict__ info) {
+                                                    uint64_t* __restrict__ pub, uint64_t wait_ticks,
+                                                    int* __restrict__ info) {
   constexpr int TC = K::TC, R = K::R;
   if (NW > 1 && blockIdx.x % 8 != 0) return;  // every eighth workgroup: neighbours in one L2, as it happens
   const int wg = NW > 1 ? blockIdx.x / 8 : 0;
@@ -423,6 +424,12 @@ __global__ __launch_bounds__(512) void hetrd_kernel(cd* __restrict__ A, int n, d
       }
       C[a][b] = v;
     }
+  auto no_matrix = [&]() {  // by one thread of the first workgroup
+    for (int j = 0; j < n; ++j) {
+      D[j] = 0.0;
+      if (j < n - 1) E[j] = 0.0;
+    }
+  };
   s_x[t] = t < n ? A[t] : cd{0.0, 0.0};  // column 0
   bool finite = true;
   bool late = false;
@@ -529,9 +536,10 @@ __global__ __launch_bounds__(512) void hetrd_kernel(cd* __restrict__ A, int n, d
                              __HIP_MEMORY_SCOPE_AGENT);
       }
       {
-        uint64_t w4[kAll / 512];
+        uint64_t w4[kAll / 512] = {};
         uint64_t t0 = 0;
-        for (int spin = 0;; ++spin) {
+        late = wait_ticks == 0;
+        for (int spin = 0; !late; ++spin) {
           bool ok = true;
 #pragma unroll
           for (int e = 0; e < kAll / 512; ++e) {
@@ -542,10 +550,7 @@ __global__ __launch_bounds__(512) void hetrd_kernel(cd* __restrict__ A, int n, d
           if ((spin & 63) == 0) {
             const uint64_t now = wall_clock64();
             if (spin == 0) t0 = now;
-            if (now - t0 > kWaitTicks) {
-              late = true;
-              break;
-            }
+            late = now - t0 > wait_ticks;
           }
         }
 #pragma unroll
@@ -558,6 +563,7 @@ __global__ __launch_bounds__(512) void hetrd_kernel(cd* __restrict__ A, int n, d
       }
       if (__syncthreads_or(late)) {  // a row's owner did not come: give up, all of them will
         if (t == 0) atomicOr(info, kTrdLate);
+        if (wg == 0 && t == 0) no_matrix();
         return;
       }
       if (t < n) {  // the records cover R NW rows, which may be fewer than the threads
@@ -620,10 +626,7 @@ __global__ __launch_bounds__(512) void hetrd_kernel(cd* __restrict__ A, int n, d
     D[n - 1] = d;
     if (!finite) {  // nothing for the tridiagonal solver: zeros, and say so
       atomicOr(info, kTrdNotFinite);
-      for (int j = 0; j < n; ++j) {
-        D[j] = 0.0;
-        if (j < n - 1) E[j] = 0.0;
-      }
+      no_matrix();
     }
   }
 }
@@ -694,10 +697,10 @@ __global__ __launch_bounds__(256) void reflect_kernel(const cd* __restrict__ V, 
 }
 
 template <int NW, int TR, int RA, int CB>
-void launch_trd(const EigBuffers& b, int n, hipStream_t s) {
+void launch_trd(const EigBuffers& b, int n, uint64_t wait_ticks, hipStream_t s) {
   using K = TrdCfg<NW, TR, RA, CB>;
   hipLaunchKernelGGL((hetrd_kernel<K, NW, TR, RA, CB>), dim3(NW > 1 ? 8 * NW : 1), dim3(512), 0, s, (cd*)b.A, n, b.D,
-                     b.E, (cd*)b.tau, b.pub, &b.status->trd);
+                     b.E, (cd*)b.tau, b.pub, wait_ticks, &b.status->trd);
 }
 
 }  // namespace
@@ -707,7 +710,7 @@ constexpr int kPubWords = 3 * 4 * kEigMaxN;
 size_t eig_pub_bytes() { return kPubWords * sizeof(uint64_t); }
 
 hipError_t launch_eig_reduce(const EigBuffers& b, const double* ant, const double* vis, int n, double wl,
-                             bool identity, hipStream_t s) {
+                             bool identity, uint64_t wait_ticks, hipStream_t s) {
   hipLaunchKernelGGL(eig_clear_kernel, dim3(kPubWords / 256), dim3(256), 0, s, b.pub, (int*)b.status,
                      (int)(offsetof(EigStatus, herm) / sizeof(int)));
   hipLaunchKernelGGL(eig_inputs_kernel, dim3(kHermParts), dim3(256), 0, s, ant, n, 1.0 / wl, identity ? 1 : 0, vis,
@@ -733,13 +736,13 @@ hipError_t launch_eig_reduce(const EigBuffers& b, const double* ant, const doubl
   }
   // rows over as few workgroups as hold them in registers; one needs no exchange
   if (n <= 64)
-    launch_trd<1, 16, 4, 2>(b, n, s);
+    launch_trd<1, 16, 4, 2>(b, n, wait_ticks, s);
   else if (n <= 128)
-    launch_trd<1, 16, 8, 4>(b, n, s);
+    launch_trd<1, 16, 8, 4>(b, n, wait_ticks, s);
   else if (n <= 256)
-    launch_trd<16, 8, 2, 4>(b, n, s);
+    launch_trd<16, 8, 2, 4>(b, n, wait_ticks, s);
   else
-    launch_trd<32, 4, 4, 4>(b, n, s);
+    launch_trd<32, 4, 4, 4>(b, n, wait_ticks, s);
   return hipGetLastError();
 }
 
