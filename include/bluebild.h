@@ -165,7 +165,10 @@ bb_status bb_synth_create(bb_context ctx, const bb_options* opt, int64_t n_pix, 
  * Returns BB_ERR_NOT_POSDEF if the Cholesky factorisation of G fails and
  * BB_ERR_EIGEN if the eigensolver fails; this status is read back from the
  * device, so the call waits for its own pre-step.  On those errors the images
- * are unchanged. */
+ * are unchanged.  With up to 512 antennas, two of them in one place always
+ * fail; otherwise, and in batches, an array whose G is singular to rounding
+ * fails or passes by the sign that its last pivots round to in the library's
+ * factorisation, and its smallest eigenpairs are then noise. */
 bb_status bb_synth_collect(bb_synth h, int32_t slot, int32_t n_ant, double wavelength_m,
                            const double* ant_xyz, const double* vis, int32_t n_eig,
                            const double* intervals);

@@ -520,11 +520,12 @@ static bb_status check_hermitian(bb_context ctx, double diff2, double norm2) {
 
 // The eigenproblem of one instance with the library's kernels (eigen.hip) and
 // rocSOLVER's tridiagonal solver: eigenvalues ascending in the evals region,
-// eigenvectors in the A region.  Waits for the status.  `late` (with BB_OK) when
-// the workgroups of the tridiagonalisation could not run together in time:
-// nothing is computed then, and the caller takes the other solver.
+// eigenvectors in the A region.  Waits for the status.  `undone` (with BB_OK) when
+// the workgroups of the tridiagonalisation could not run together in time, or a
+// pivot of the Cholesky factorisation was within rounding of zero without two
+// antennas in one place: nothing is computed then, and the other solver answers.
 static bb_status solve_eigen(bb_synth h, int n, double wavelength_m, const double* ant_xyz, const double* vis,
-                             std::vector<double>* evals_host, bool& late) {
+                             std::vector<double>* evals_host, bool& undone) {
   bb_context ctx = h->ctx;
   hipStream_t s = ctx->stream;
   const Layout& L = h->lay;
@@ -565,9 +566,10 @@ static bb_status solve_eigen(bb_synth h, int n, double wavelength_m, const doubl
   }
   const bb_status hs = check_hermitian(ctx, diff2, norm2);
   if (hs != BB_OK) return hs;
-  if (st.chol != 0) return fail(ctx, BB_ERR_NOT_POSDEF, "Gram matrix not positive definite (leading minor %d)", st.chol);
-  late = (st.trd & bb::kTrdLate) != 0;
-  if (late) return BB_OK;
+  if (st.chol > 0 || (st.chol < 0 && st.coincident))
+    return fail(ctx, BB_ERR_NOT_POSDEF, "Gram matrix not positive definite (leading minor %d)", std::abs(st.chol));
+  undone = st.chol < 0 || (st.trd & bb::kTrdLate) != 0;
+  if (undone) return BB_OK;
   if (st.trd & bb::kTrdNotFinite) return fail(ctx, BB_ERR_EIGEN, "tridiagonal matrix not finite");
   if (st.stedc != 0) return fail(ctx, BB_ERR_EIGEN, "eigensolver did not converge (info %d)", st.stedc);
   return BB_OK;

@@ -145,10 +145,10 @@ constexpr int kTrdLate = 1;          // EigStatus::trd: a wait between workgroup
 constexpr int kTrdNotFinite = 2;     // the tridiagonal matrix is not finite
 constexpr uint64_t kTrdWaitTicks = 100000000ULL;  // longest wait: one second of the 100 MHz clock
 struct EigStatus {
-  int chol;                          // 0, or the first leading minor of G that is not positive
+  int chol;                          // 0, or the first leading minor of G that fails (< 0: in doubt, see chol_diag_kernel)
   int trd;
   int stedc;                         // the tridiagonal solver's info
-  int pad;
+  int coincident;                    // two antennas are in one place
   double herm[2 * kHermParts];       // sums of ||V - V^H||_F^2 and ||V||_F^2, to be added in order
 };
 struct EigBuffers {

@@ -64,15 +64,16 @@ __device__ __forceinline__ double lane_of(double x, int lane) {  // wave-uniform
 
 // ---- inputs -----------------------------------------------------------------
 // A = V from its lower triangle (diagonal real), the real Gram matrix (unless
-// G = I), and per-workgroup sums of the Hermiticity check: part[2 b] of
+// G = I; `same` is set where two antennas are in one place), and per-workgroup sums of the Hermiticity check: part[2 b] of
 // ||V - V^H||_F^2 and part[2 b + 1] of ||V||_F^2 (kHermParts workgroups; the
 // host adds them in order).
 __global__ __launch_bounds__(256) void eig_inputs_kernel(const double* __restrict__ ant, int n, double inv_wl,
                                                          int identity, const double* __restrict__ V,
                                                          double* __restrict__ A, double* __restrict__ G,
-                                                         double* __restrict__ part) {
+                                                         double* __restrict__ part, int* __restrict__ same) {
   __shared__ double s[2][4];
   double dsum = 0.0, nsum = 0.0;
+  bool coincide = false;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < (int64_t)n * n; i += (int64_t)gridDim.x * 256) {
     const int p = (int)(i % n), q = (int)(i / n);
     const cd a = ((const cd*)V)[i];                          // V_pq
@@ -87,8 +88,10 @@ __global__ __launch_bounds__(256) void eig_inputs_kernel(const double* __restric
       const double dz = ant[p + 2 * n] - ant[q + 2 * n];
       const double u = 2.0 * sqrt(dx * dx + dy * dy + dz * dz) * inv_wl;
       G[i] = (u == 0.0) ? 1.0 : sinpi(u) / (M_PI * u);
+      coincide = coincide || (u == 0.0 && p != q);
     }
   }
+  if (coincide) atomicOr(same, 1);
   for (int o = 32; o > 0; o >>= 1) {
     dsum += __shfl_xor(dsum, o);
     nsum += __shfl_xor(nsum, o);
@@ -116,8 +119,11 @@ constexpr int kNB = 64;
 // inverse's once it is used: thread (r, g) keeps row r of columns g + 8 m in
 // registers.  A column's step publishes its multipliers and the pivot row, one
 // barrier, and eight multiply-adds a thread; bound by its 64 dependent steps
-// (0.2 us each).  A pivot within 2^-50 of zero is rounding noise of a singular
-// matrix (the diagonal of G is 1) and reported like a negative one.
+// (0.2 us each).  info becomes c + 1 at a pivot c that is NaN and -(c + 1) at one
+// of at most kPivotNoise: with the diagonal of G at 1 its sign is then rounding,
+// which this elimination and the library's need not share, and the library
+// decides (kPivotNoise is 8 n eps at n = 512).
+constexpr double kPivotNoise = 0x1p-40;
 __global__ __launch_bounds__(512) void chol_diag_kernel(const double* __restrict__ G, double* __restrict__ Y, int n,
                                                         int k, int* __restrict__ info) {
   __shared__ double s_l[2][kNB];        // multipliers L[r][c]
@@ -137,7 +143,7 @@ __global__ __launch_bounds__(512) void chol_diag_kernel(const double* __restrict
       const int c = gc + 8 * mc, buf = c & 1;
       if (g == gc) {  // the wave that holds column c
         const double d = lane_of(v[mc], c);
-        if (r == c && !(d > 0x1p-50) && r0 + c < n && *info == 0) *info = r0 + c + 1;
+        if (r == c && !(d > kPivotNoise) && r0 + c < n && *info == 0) *info = d != d ? r0 + c + 1 : -(r0 + c + 1);
         const double inv = rsqrt_newton(d), l = v[mc] * inv;
         s_l[buf][r] = l;
         if (r > c) s_f[buf][r & 7][r >> 3] = l;
@@ -340,7 +346,8 @@ __global__ __launch_bounds__(256) void tri_product_kernel(const double* __restri
 // buffer is cleared by its rows' owners after the next column's exchange, when all
 // have read it, and used again one column later.  Waits end after wait_ticks;
 // then info says so, every workgroup returns, and D and E are zeros: the solver
-// that is already queued behind must not iterate on half a matrix.
+// that is already queued behind must not iterate on half a matrix.  The same
+// where the Cholesky factorisation failed (chol).
 // Bound by its dependent steps: 2.1 us a column in one workgroup (n = 64), 5.3 us
 // with 32 of them (n = 512).
 constexpr uint64_t kEmpty = 0xFFF4DEADBEEF5A5AULL;
@@ -402,7 +409,7 @@ template <class K, int NW, int TR, int RA, int CB>
 __global__ __launch_bounds__(512) void hetrd_kernel(cd* __restrict__ A, int n, double* __restrict__ D,
                                                     double* __restrict__ E, cd* __restrict__ tau_out,
                                                     uint64_t* __restrict__ pub, uint64_t wait_ticks,
-                                                    int* __restrict__ info) {
+                                                    const int* __restrict__ chol, int* __restrict__ info) {
   constexpr int TC = K::TC, R = K::R;
   if (NW > 1 && blockIdx.x % 8 != 0) return;  // every eighth workgroup: neighbours in one L2, as it happens
   const int wg = NW > 1 ? blockIdx.x / 8 : 0;
@@ -410,6 +417,16 @@ __global__ __launch_bounds__(512) void hetrd_kernel(cd* __restrict__ A, int n, d
   __shared__ cd s_x[512], s_v[512], s_w[512], s_p[512], s_y[512], s_own[NW == 1 ? 1 : R];
   __shared__ double s_sum[3][8];
   __shared__ double s_part[K::PARTS][R][2];
+  auto no_matrix = [&]() {  // by one thread of the first workgroup
+    for (int j = 0; j < n; ++j) {
+      D[j] = 0.0;
+      if (j < n - 1) E[j] = 0.0;
+    }
+  };
+  if (*chol != 0) {  // the same for every workgroup
+    if (wg == 0 && t == 0) no_matrix();
+    return;
+  }
   cd C[RA][CB];
 #pragma unroll
   for (int a = 0; a < RA; ++a)
@@ -424,12 +441,6 @@ __global__ __launch_bounds__(512) void hetrd_kernel(cd* __restrict__ A, int n, d
       }
       C[a][b] = v;
     }
-  auto no_matrix = [&]() {  // by one thread of the first workgroup
-    for (int j = 0; j < n; ++j) {
-      D[j] = 0.0;
-      if (j < n - 1) E[j] = 0.0;
-    }
-  };
   s_x[t] = t < n ? A[t] : cd{0.0, 0.0};  // column 0
   bool finite = true;
   bool late = false;
@@ -700,7 +711,7 @@ template <int NW, int TR, int RA, int CB>
 void launch_trd(const EigBuffers& b, int n, uint64_t wait_ticks, hipStream_t s) {
   using K = TrdCfg<NW, TR, RA, CB>;
   hipLaunchKernelGGL((hetrd_kernel<K, NW, TR, RA, CB>), dim3(NW > 1 ? 8 * NW : 1), dim3(512), 0, s, (cd*)b.A, n, b.D,
-                     b.E, (cd*)b.tau, b.pub, wait_ticks, &b.status->trd);
+                     b.E, (cd*)b.tau, b.pub, wait_ticks, &b.status->chol, &b.status->trd);
 }
 
 }  // namespace
@@ -714,7 +725,7 @@ hipError_t launch_eig_reduce(const EigBuffers& b, const double* ant, const doubl
   hipLaunchKernelGGL(eig_clear_kernel, dim3(kPubWords / 256), dim3(256), 0, s, b.pub, (int*)b.status,
                      (int)(offsetof(EigStatus, herm) / sizeof(int)));
   hipLaunchKernelGGL(eig_inputs_kernel, dim3(kHermParts), dim3(256), 0, s, ant, n, 1.0 / wl, identity ? 1 : 0, vis,
-                     b.A, b.G, b.status->herm);
+                     b.A, b.G, b.status->herm, &b.status->coincident);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (!identity) {
