@@ -44,6 +44,7 @@ struct Layout {  // byte offsets into a handle's workspace
   size_t meta, err, apack, xs, wts, levs, kbr, perm;
   size_t A, G, T, U, evals, E, info, dsel, lsel, wcol, solver, solver_bytes;
   size_t tau, pub, status;
+  size_t km, km_bytes;  // k-means run costs
   size_t total;
 };
 
@@ -110,6 +111,9 @@ Layout make_layout(const bb_options& o, size_t solver_bytes) {
   p += align_up(bb::eig_pub_bytes());
   l.status = p;
   p += align_up(sizeof(bb::EigStatus));
+  l.km = p;
+  l.km_bytes = std::min(bb::kmeans_scratch_bytes(bb::kMaxEig), 64 * Lm * Lm);
+  p += align_up(l.km_bytes);
   l.solver = p;
   l.solver_bytes = solver_bytes;
   p += align_up(solver_bytes);
@@ -132,6 +136,8 @@ struct bb_synth_ {
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   bool timed = false;
   int tiles[bb::kKClasses] = {-1, -1, -1, -1};  // tile id per K class (set to the defaults at creation)
+  bool km_used = false;             // the k-means region may be in use by work on km_stream
+  hipStream_t km_stream = nullptr;
 };
 
 namespace {
@@ -950,9 +956,21 @@ bb_status bb_synth_levels_kmeans(bb_synth h, int32_t n, const double* lam, int32
   if (k < 1) return fail(ctx, BB_ERR_INVALID_ARG, "no positive level left (n_levels %d)", h->opt.n_levels);
   if (!lam || !intervals || !level_of) return fail(ctx, BB_ERR_INVALID_ARG, "null device pointer");
   BB_HIP(ctx, hipSetDevice(ctx->device));
-  // the run costs go to the pre-step matrices' region (free between calls) where they fit
+  // The run costs go to the handle's region for them, which calls on one stream use
+  // in turn.  A call on another stream than the last one's, not known to be over, or
+  // one under capture, whose replays may run beside any later call, does without.
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    cap = hipStreamCaptureStatusActive;
+  }
+  const bool own = cap == hipStreamCaptureStatusNone && (!h->km_used || h->km_stream == ctx->stream);
+  if (own) {
+    h->km_used = true;
+    h->km_stream = ctx->stream;
+  }
   BB_HIP(ctx, bb::launch_kmeans_levels(lam, n, k, negative_level, intervals, level_of, at<int>(h, h->lay.err),
-                                       h->ws + h->lay.A, h->lay.evals - h->lay.A, ctx->stream));
+                                       own ? h->ws + h->lay.km : nullptr, own ? h->lay.km_bytes : 0, ctx->stream));
   return BB_OK;
 }
 
@@ -1465,6 +1483,7 @@ bb_status bb_synth_sync(bb_synth h) {
   bb_context ctx = h->ctx;
   BB_HIP(ctx, hipSetDevice(ctx->device));
   BB_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  if (h->km_stream == ctx->stream) h->km_used = false;
   int err = 0;
   BB_HIP(ctx, hipMemcpy(&err, at<int>(h, h->lay.err), sizeof err, hipMemcpyDeviceToHost));
   if (err) {

@@ -172,7 +172,8 @@ hipError_t launch_eig_reduce(const EigBuffers& b, const double* ant, const doubl
 hipError_t launch_eig_vectors(const EigBuffers& b, int n, bool identity, hipStream_t s);
 
 // Level determination and weighting (levels_weighting.hip).
-// scratch: n x n doubles make it faster (may be smaller, or null with 0 bytes).
+// scratch: kmeans_scratch_bytes(n) make it faster (may be smaller, or null with 0 bytes).
+size_t kmeans_scratch_bytes(int n);
 hipError_t launch_kmeans_levels(const double* lam, int n, int k, int negative_level, double* intervals,
                                 int* level_of, int* err, void* scratch, size_t scratch_bytes, hipStream_t s);
 struct UvFrame {

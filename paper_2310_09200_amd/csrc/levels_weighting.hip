@@ -147,8 +147,8 @@ __device__ void km_finish(const KmArgs& K, const KmSorted& S, const int16_t (*cu
 
 // All in one workgroup and its LDS: for at most a wave of positive values, whose
 // runs' costs LDS holds (64 values into 8 + 1 levels: 66 us when every sweep
-// formed them again with a division a step, 24 us now), and for handles whose workspace does
-// not hold the costs; there every sweep still forms them.
+// formed them again with a division a step, 24 us now), and for calls without room
+// for the costs in memory; there every sweep still forms them.
 constexpr int kKmLds = 64;
 
 __global__ __launch_bounds__(kKmThreads) void kmeans_levels_kernel(KmArgs K) {
@@ -293,12 +293,14 @@ __global__ __launch_bounds__(kKmThreads) void km_finish_kernel(KmArgs K, const K
   if (M->ok) km_finish(K, M->S, M->cut);
 }
 
+size_t kmeans_scratch_bytes(int n) { return sizeof(KmScratch) + (size_t)n * n * sizeof(double); }
+
 hipError_t launch_kmeans_levels(const double* lam, int n, int k, int negative_level, double* intervals,
                                 int* level_of, int* err, void* scratch, size_t scratch_bytes, hipStream_t s) {
   if (n < 1 || n > kKmThreads || k < 1 || k + (negative_level ? 1 : 0) > kMaxLevels) return hipErrorInvalidValue;
   const KmArgs K{lam, n, k, negative_level, k + (negative_level ? 1 : 0), intervals, level_of, err};
   // below a wave of values, or with a single run, one workgroup is done before the launches are
-  if (n <= 64 || k < 2 || sizeof(KmScratch) + (size_t)n * n * sizeof(double) > scratch_bytes) {
+  if (n <= 64 || k < 2 || kmeans_scratch_bytes(n) > scratch_bytes) {
     hipLaunchKernelGGL(kmeans_levels_kernel, dim3(1), dim3(kKmThreads), 0, s, K);
     return hipGetLastError();
   }
