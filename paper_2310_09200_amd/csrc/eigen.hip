@@ -454,7 +454,8 @@ __global__ __launch_bounds__(512) void hetrd_kernel(cd* __restrict__ A, int n, d
     const cd alpha = s_x[j + 1];
     cd tau = {0.0, 0.0}, scale = {0.0, 0.0};
     double beta = alpha.x;
-    if (xn != 0.0 || alpha.y != 0.0) {
+    // nothing to reflect below 2^-480, where squares leave the range of normal numbers
+    if (!(xn < 0x1p-960 && fabs(alpha.y) < 0x1p-480)) {
       const double s2 = fma(alpha.x, alpha.x, fma(alpha.y, alpha.y, xn)), rs = rsqrt_newton(s2), rt = s2 * rs;
       beta = -copysign(fma(fma(-rt, rt, s2), 0.5 * rs, rt), alpha.x);
       const double dx = alpha.x - beta, ib = -copysign(rs, alpha.x);
