@@ -959,12 +959,7 @@ bb_status bb_synth_levels_kmeans(bb_synth h, int32_t n, const double* lam, int32
   // The run costs go to the handle's region for them, which calls on one stream use
   // in turn.  A call on another stream than the last one's, not known to be over, or
   // one under capture, whose replays may run beside any later call, does without.
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
-    (void)hipGetLastError();
-    cap = hipStreamCaptureStatusActive;
-  }
-  const bool own = cap == hipStreamCaptureStatusNone && (!h->km_used || h->km_stream == ctx->stream);
+  const bool own = !bb_host::capturing(ctx->stream) && (!h->km_used || h->km_stream == ctx->stream);
   if (own) {
     h->km_used = true;
     h->km_stream = ctx->stream;

@@ -44,6 +44,14 @@ inline bb_status fail(bb_context ctx, bb_status s, const char* fmt, ...) {
   return s;
 }
 
+// Whether work put on s now is recorded for later replays (also where that cannot be told).
+inline bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 inline bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
 
 // Whether an environment variable is set (and not "0").

@@ -348,6 +348,7 @@ struct bb_nufft_ {
   rocfft_execution_info info = nullptr;
   int64_t count = 0;  // instances spread since the last emit
   bool dirty = false;  // a spread was launched since the grid was cleared
+  bool replayed = false;  // a captured spread may run at any time
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   bool spread_timed = false, emit_timed = false;
 };
@@ -917,13 +918,14 @@ bb_status bb_nufft_collect_eig_batched(bb_nufft h, int32_t n_inst, const bb_inst
   int* count = reinterpret_cast<int*>(ws + cl.count);
   int* offset = reinterpret_cast<int*>(ws + cl.offset);
   int* scan_tmp = reinterpret_cast<int*>(ws + cl.scan_tmp);
-  const bool was_dirty = h->dirty;
+  h->replayed = h->replayed || bb_host::capturing(s);
+  const bool fresh = !h->dirty && !h->replayed;
   h->dirty = true;
   if (cl.mode == 2) {
     BB_HIP(ctx, bb::launch_nufft_spread_gather(h->g, d_inst, n_inst, max_ant, cl.pairs, ant_xyz_packed, n_ant_rows,
                                                ws + cl.vp, count, offset, ws + cl.list, n_levels, ws + cl.rec,
                                                ws + cl.cv, reinterpret_cast<int*>(ws + cl.nparts),
-                                               reinterpret_cast<int*>(ws + cl.part_off), scan_tmp, !was_dirty,
+                                               reinterpret_cast<int*>(ws + cl.part_off), scan_tmp, fresh,
                                                tnat<float>(h, h->lay.grid), n_cell, pnat<int>(h, h->lay.err), s));
   } else if (cl.mode == 1) {
     uint64_t* list = reinterpret_cast<uint64_t*>(ws + cl.list);
@@ -1007,7 +1009,7 @@ bb_status bb_nufft_emit(bb_nufft h) {
                                         h->images, s));
   }
   BB_HIP(ctx, bb::launch_fill_zero(tnat<float>(h, h->lay.grid), 2 * n_cell * h->opt.n_levels, s));
-  h->dirty = false;
+  if (!bb_host::capturing(s)) h->dirty = false;  // a captured clear is one of a later time
   BB_HIP(ctx, bb::launch_fill_zero_f64(pnat<double>(h, h->lay.diag), bb::kMaxLevels, s));
   BB_HIP(ctx, hipEventRecord(h->ev[3], s));
   h->emit_timed = true;

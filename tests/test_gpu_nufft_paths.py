@@ -8,6 +8,7 @@ the oracle's convention may choose different windows, equally good to epsilon.
 """
 import numpy as np
 import pytest
+import torch
 
 import sims
 from oracle import nufft_ref as nf
@@ -146,3 +147,36 @@ def test_spread_parts_across_the_wrap(ctx, eps, depth, n_ant):
     inside = np.all(np.abs(c - (lo + hi) / 2) < (hi - lo) / 2 * (1 - 1e-9), axis=1)
     for a, b in zip(got, want):
         assert np.max(np.abs(a - b)[inside]) <= 1e-5 * np.max(np.abs(b))
+
+
+def test_emit_under_capture(ctx):
+    """A transform captured between two spreads and replayed after them images both."""
+    from paper_2310_09200_amd import Batch, NufftSynthesis
+    print("case nufft emit under capture", flush=True)
+    pix, items, frame, uvw = _case(3, (14.0, 17.0, 20.0), 9)
+    batches = [Batch([(0, *it)], ctx.device) for it in items]
+    plans = [NufftSynthesis(ctx, pix, 3, 64, 64, 1e-5, frame, uvw) for _ in range(2)]
+    for b in batches:
+        plans[0].collect_eig_batched(b)
+    plans[0].emit()
+    plans[0].sync()
+    want = plans[0].images.double().cpu().numpy()
+    p = plans[1]
+    p.collect_eig_batched(batches[0])
+    p.sync()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        p.emit()
+    for rnd in range(3):
+        p.images.zero_()
+        p.collect_eig_batched(batches[1])
+        if rnd > 0:
+            p.collect_eig_batched(batches[0])
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = p.images.double().cpu().numpy()
+        for a, b in zip(got, want):
+            assert np.max(np.abs(a - b)) <= 1e-5 * np.max(np.abs(b)), rnd
+    for q in plans:
+        q.close()
