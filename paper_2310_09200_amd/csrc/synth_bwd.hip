@@ -179,10 +179,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dw_kernel(const BwdParams P) {
   const int t = threadIdx.x, lane = t & 63, r16 = lane & 15, kq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6), wl = wave >> 1, half = wave & 1;
   const bool live = l0 + 32 * wl < P.L_pad;  // the wave's antennas exist
-  if (t < 512) {
-    const int row = l0 + (t >> 2);
-    (&sX[0][0])[t] = row < P.L_pad ? D.xs[4 * l0 + t] : 0.0;
-  }
+  (&sX[0][0])[t] = l0 + (t >> 2) < P.L_pad ? D.xs[4 * l0 + t] : 0.0;
   {  // scales: 512 / K threads per eigenpair
     constexpr int TP = 512 / K;
     const int k = t / TP;
