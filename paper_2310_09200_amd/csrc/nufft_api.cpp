@@ -795,14 +795,16 @@ CallLayout call_layout(bb_nufft h, int32_t n_inst, const bb_instance* inst) {
     p += align_up(4 * (size_t)c.n_bins);
     c.offset = p;
     p += align_up(4 * ((size_t)c.n_bins + 1));
-    c.cursor = p;
-    p += align_up(4 * (size_t)c.n_bins);
     c.list = p;
     p += align_up(8 * std::max<size_t>(pairs, 1));
-    c.nch = p;  // tiles and bins share one grid
-    p += align_up(4 * (size_t)c.n_bins);
-    c.choff = p;
-    p += align_up(4 * ((size_t)c.n_bins + 1));
+    if (c.mode == 1) {
+      c.cursor = p;
+      p += align_up(4 * (size_t)c.n_bins);
+      c.nch = p;  // tiles and bins share one grid
+      p += align_up(4 * (size_t)c.n_bins);
+      c.choff = p;
+      p += align_up(4 * ((size_t)c.n_bins + 1));
+    }
   }
   c.total = p;
   return c;
