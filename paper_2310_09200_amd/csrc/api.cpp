@@ -60,7 +60,7 @@ size_t staging_bytes(int L_pad, int K_alloc, size_t* off_xs = nullptr, size_t* o
   if (off_levs) *off_levs = o;
   o += align_up((size_t)K_alloc * 4);
   if (off_kbr) *off_kbr = o;
-  o += align_up((size_t)(K_alloc / 32 + K_alloc / 16) * 8);
+  o += align_up((size_t)(K_alloc / 16) * 8);
   if (off_perm) *off_perm = o;
   o += align_up((size_t)K_alloc * 4);
   return o;

@@ -47,8 +47,7 @@ struct InstDesc {
   double* xs;            // [L_pad][4] scaled positions
   float* wts;            // [K_alloc] weights after level sort (0 beyond K_eff)
   int* levs;             // [K_alloc] level ids after sort (-1 beyond K_eff)
-  int2* kbr;             // [K_alloc/32] (lowest, highest) level of each 32-block, then
-                         // [K_alloc/16] the same for each 16-block
+  int2* kbr;             // [K_alloc/16] (lowest, highest) level of each 16-block
   int* perm;             // [K_alloc] source eigenpair of each sorted position (-1 = pad)
   int* wexp;             // [K_alloc] binary exponent that undoes the staged column's scale
 };

@@ -101,7 +101,7 @@ __device__ __forceinline__ void phase_pair(double x, double y, double z, double 
 
 // ---------------------------------------------------------------------------
 // Staging, part 1 (one workgroup per instance): sort eigenpairs by level
-// (stable, dropping level -1), scaled positions, per-32-block level ranges.
+// (stable, dropping level -1), scaled positions, level ranges of 16-blocks.
 __global__ __launch_bounds__(256) void stage_meta_kernel(const InstDesc* __restrict__ descs,
                                                          InstDyn* __restrict__ dyn, int n_levels, bool relative,
                                                          int* __restrict__ err) {
@@ -150,15 +150,13 @@ __global__ __launch_bounds__(256) void stage_meta_kernel(const InstDesc* __restr
     D.levs[pos] = -1;
   }
   __syncthreads();
-  // level range of each 32-block, then of each 16-block, of sorted positions
-  // (levels are non-decreasing; (1, 0) for a block with no kept eigenpair)
-  const int nb32 = D.K_alloc / 32;
-  for (int i = tid; i < nb32 + D.K_alloc / 16; i += blockDim.x) {
-    const int rows = i < nb32 ? 32 : 16;
-    const int p0 = (i < nb32 ? i : i - nb32) * rows;
+  // level range of each 16-block of sorted positions (levels are
+  // non-decreasing; (1, 0) for a block with no kept eigenpair)
+  for (int i = tid; i < D.K_alloc / 16; i += blockDim.x) {
+    const int p0 = i * 16;
     int lo = 1, hi = 0;
     if (p0 < K_eff) {
-      const int p1 = min(p0 + rows - 1, K_eff - 1);
+      const int p1 = min(p0 + 15, K_eff - 1);
       // sorted positions: find their levels through the base offsets
       int l0 = 0, l1 = 0;
       for (int l = 0; l < n_levels; ++l) {
@@ -537,8 +535,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void synth_fwd_kernel(const Fwd
       const BB_GLOBAL float* const wts = as_global<float>(Dg.wts);
       const BB_GLOBAL int* const wexp = as_global<int>(Dg.wexp);
       const BB_GLOBAL int* const levs = as_global<int>(Dg.levs);
-      const BB_GLOBAL int* const kbr =
-          as_global<int>(Dg.kbr) + 2 * (__builtin_amdgcn_readfirstlane(Dg.K_alloc) / 32);  // (lo, hi) of each 16-block
+      const BB_GLOBAL int* const kbr = as_global<int>(Dg.kbr);
       const int nkb = __builtin_amdgcn_readfirstlane(P.dyn[inst].K_eff + 15) / 16;
       const int L_pad = __builtin_amdgcn_readfirstlane(Dg.L_pad);
       const int n_chunks = L_pad / C::LCH;
