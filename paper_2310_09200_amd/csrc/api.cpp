@@ -230,7 +230,7 @@ bb_status launch_single(bb_context ctx, SingleMeta* meta, int* err, const InstDe
     return fail(ctx, BB_ERR_INVALID_ARG, "unknown tile %d", tile);
   hipLaunchKernelGGL(write_meta_kernel, dim3(1), dim3(1), 0, s, meta, d, d.slot);
   BB_HIP(ctx, hipGetLastError());
-  BB_HIP(ctx, bb::launch_stage(&meta->desc, &meta->dyn, 1, d.K_alloc, n_levels, precision, err, s));
+  BB_HIP(ctx, bb::launch_stage(&meta->desc, &meta->dyn, 1, d.K_alloc, d.L_pad, n_levels, precision, err, s));
   if (ev_staged) BB_HIP(ctx, hipEventRecord(ev_staged, s));
   bb::FwdParams p{};
   p.pix = pix;
@@ -1205,8 +1205,8 @@ bb_status bb_synth_collect_eig_batched(bb_synth h, int32_t n_inst, const bb_inst
   st = upload_plan(ctx, bp, ws, n_inst, true);
   if (st != BB_OK) return st;
   BB_HIP(ctx, bb::launch_stage(reinterpret_cast<InstDesc*>(ws + bp.off_descs), reinterpret_cast<InstDyn*>(ws + bp.off_dyn),
-                               n_inst, bp.max_K_alloc, h->opt.n_levels, h->opt.precision,
-                               at<int>(h, h->lay.err), s));
+                               n_inst, bp.max_K_alloc, bp.max_L_pad, h->opt.n_levels,
+                               h->opt.precision, at<int>(h, h->lay.err), s));
   BB_HIP(ctx, hipEventRecord(h->ev[2], s));
   st = launch_buckets(h, bp, ws, h->images);
   if (st != BB_OK) return st;
@@ -1289,7 +1289,7 @@ bb_status bb_synth_autotune_batched(bb_synth h, int32_t n_inst, const bb_instanc
   if (st != BB_OK) return st;
   BB_HIP(ctx, bb::launch_stage(reinterpret_cast<InstDesc*>(ws + full.off_descs),
                                reinterpret_cast<InstDyn*>(ws + full.off_dyn), n_inst, full.max_K_alloc,
-                               h->opt.n_levels, h->opt.precision, at<int>(h, h->lay.err), s));
+                               full.max_L_pad, h->opt.n_levels, h->opt.precision, at<int>(h, h->lay.err), s));
   BB_HIP(ctx, bb::launch_fill_zero(scratch_images, (int64_t)h->opt.n_slots * h->opt.n_levels * h->n_pix, s));
   bool present[bb::kKClasses] = {false, false, false, false};
   for (int i = 0; i < n_inst; ++i) present[bb::synth_k_class(bb::round_up(inst[i].n_eig, 32))] = true;

@@ -84,8 +84,8 @@ struct FwdParams {
 // precision's synthesis kernel.
 hipError_t launch_stage_meta(const InstDesc* d_descs, InstDyn* d_dyn, int n_inst, int n_levels, bool relative,
                              int* d_err, hipStream_t s);
-hipError_t launch_stage(const InstDesc* d_descs, InstDyn* d_dyn, int n_inst, int max_K_alloc, int n_levels,
-                        int precision, int* d_err, hipStream_t s);
+hipError_t launch_stage(const InstDesc* d_descs, InstDyn* d_dyn, int n_inst, int max_K_alloc, int max_L_pad,
+                        int n_levels, int precision, int* d_err, hipStream_t s);
 // Resident workgroups of a kernel with static LDS on the current device.
 int resident_blocks(const void* kernel, int threads);
 

@@ -194,20 +194,17 @@ __global__ __launch_bounds__(256) void stage_meta_kernel(const InstDesc* __restr
   if (tid == 0) dyn[blockIdx.x].fast_phase = near;
 }
 
+// Component l of a column of W; T: its real type.
+template <class T>
 __device__ __forceinline__ void load_w(const InstDesc& D, int l, int col, float& wr, float& wi) {
-  if (D.W_c128) {
-    const double* w = (const double*)D.W + 2 * ((int64_t)col * D.W_ld + l);
-    wr = (float)w[0];
-    wi = (float)w[1];
-  } else {
-    const float* w = (const float*)D.W + 2 * ((int64_t)col * D.W_ld + l);
-    wr = w[0];
-    wi = w[1];
-  }
+  const BB_GLOBAL T* const w = as_global<T>(D.W) + 2 * ((int64_t)col * D.W_ld + l);
+  wr = (float)w[0];
+  wi = (float)w[1];
 }
 
-// Staging, part 2 (one workgroup per (32 eigenpairs, instance)): the W^H
-// operand in MFMA order, each value split into two 16-bit words hi + lo.
+// Staging, part 2 (workgroup = 32 eigenpairs of an instance, every gridDim.z-th
+// group of 128 antennas): the W^H operand in MFMA order, each value split into two
+// 16-bit words hi + lo.
 //
 // An eigenpair's column is first scaled by a power of two of its own: its
 // largest component lands in [2^13, 2^14), so that hi and lo of every value
@@ -220,50 +217,65 @@ __device__ __forceinline__ void load_w(const InstDesc& D, int l, int col, float&
 // (k1 - k3) + j (k1 + k2)): Wr - Wi, Wr, -Wi.  Vectors of 8 antennas, ordered
 // (16-eigenpair block, 32-antenna step, plane, hi / lo, lane): lane = row +
 // 16 kk holds antennas 32 step + 8 kk + e, the operand of one 16x16x32 MFMA.
-template <class H, int NPL>
-__global__ __launch_bounds__(512) void stage_pack_kernel(const InstDesc* __restrict__ descs) {
+template <class H, int NPL, class T>
+__device__ __forceinline__ void stage_pack(const InstDesc& D, int* s_ex) {
   typedef H h8 __attribute__((ext_vector_type(8)));
-  const InstDesc D = descs[blockIdx.y];
-  if ((int)blockIdx.x * 32 >= D.K_alloc) return;
   constexpr bool kScaled = std::is_same<H, _Float16>::value;
-  __shared__ float s_max[16][32];
-  const int tid = threadIdx.x;
-  // thread = (part of the antennas, eigenpair), the eigenpair's row in its
-  // 16-block in the low four bits so that it is also an operand lane
+  const int tid = threadIdx.x, lane = tid & 63, steps = D.L_pad / 32;
+  auto column = [&](int k) {
+    const int src = D.perm[k];
+    return src < 0 ? -1 : (D.wcol ? D.wcol[src] : src);
+  };
+  if (kScaled) {  // the columns' largest finite components, four of them a wave
+    const int c0 = (tid >> 6) * 4;
+    int col[4];
+    float m[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      col[c] = column(blockIdx.x * 32 + c0 + c);
+      m[c] = 0.0f;
+    }
+    for (int l0 = 0; l0 < D.L; l0 += 256) {  // a turn's reads in flight at once; past the end the last antenna again
+      float a[4][4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          float x, y;
+          load_w<T>(D, min(l0 + 64 * u + lane, D.L - 1), max(col[c], 0), x, y);
+          a[u][c] = fmaxf(fabsf(x), fabsf(y));
+        }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) m[c] = a[u][c] <= 3.4028235e38f ? fmaxf(m[c], a[u][c]) : m[c];
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      for (int o = 32; o > 0; o >>= 1) m[c] = fmaxf(m[c], __shfl_xor(m[c], o));
+      int ex = 0;
+      if (m[c] > 0.0f && col[c] >= 0) {
+        (void)frexpf(m[c], &ex);  // m < 2^ex
+        ex = 14 - ex;
+      }
+      if (lane == 0) s_ex[c0 + c] = ex;
+    }
+    __syncthreads();
+  }
+  // wave = (16 eigenpairs, step); the eigenpair's row in its 16-block in the low four bits of the lane
   const int col32 = (tid & 15) + 16 * (tid >> 8);
   const int k = blockIdx.x * 32 + col32;
-  const int src = D.perm[k];
-  const int col = src < 0 ? -1 : (D.wcol ? D.wcol[src] : src);
-  const int part = (tid >> 4) & 15;
-  int ex = 0;
-  if (kScaled) {
-    float m = 0.0f;
-    if (col >= 0)
-      for (int l = part; l < D.L; l += 16) {
-        float wr, wi;
-        load_w(D, l, col, wr, wi);
-        const float a = fmaxf(fabsf(wr), fabsf(wi));
-        if (a <= 3.4028235e38f) m = fmaxf(m, a);  // the largest finite component
-      }
-    s_max[part][col32] = m;
-    __syncthreads();
-    for (int i = 0; i < 16; ++i) m = fmaxf(m, s_max[i][col32]);
-    if (m > 0.0f) {
-      (void)frexpf(m, &ex);  // m < 2^ex
-      ex = 14 - ex;
-    }
-  }
-  if (part == 0) D.wexp[k] = -ex;
-  const int steps = D.L_pad / 32;
-  const int lane = tid & 63;
+  const int col = column(k);
+  const int ex = kScaled ? s_ex[col32] : 0;
+  if (blockIdx.z == 0 && (tid & 0xf0) == 0) D.wexp[k] = -ex;
   h8* const out = (h8*)D.apack + (int64_t)(k >> 4) * steps * NPL * 128;
-  for (int st = (tid >> 6) & 3; st < steps; st += 4) {
+  for (int st = 4 * blockIdx.z + ((tid >> 6) & 3); st < steps; st += 4 * gridDim.z) {
     h8 hi[NPL], lo[NPL];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int l = 32 * st + 8 * (lane >> 4) + e;
       float wr = 0.0f, wi = 0.0f;
-      if (col >= 0 && l < D.L) load_w(D, l, col, wr, wi);
+      if (col >= 0 && l < D.L) load_w<T>(D, l, col, wr, wi);
       if (kScaled) {
         wr = ldexpf(wr, ex);
         wi = ldexpf(wi, ex);
@@ -284,6 +296,17 @@ __global__ __launch_bounds__(512) void stage_pack_kernel(const InstDesc* __restr
   }
 }
 
+template <class H, int NPL>
+__global__ __launch_bounds__(512) void stage_pack_kernel(const InstDesc* __restrict__ descs) {
+  __shared__ int s_ex[32];
+  const InstDesc D = descs[blockIdx.y];
+  if ((int)blockIdx.x * 32 >= D.K_alloc || (int)blockIdx.z * 128 >= D.L_pad) return;
+  if (D.W_c128)
+    stage_pack<H, NPL, double>(D, s_ex);
+  else
+    stage_pack<H, NPL, float>(D, s_ex);
+}
+
 hipError_t launch_stage_meta(const InstDesc* d_descs, InstDyn* d_dyn, int n_inst, int n_levels, bool relative,
                              int* d_err, hipStream_t s) {
   if (n_inst <= 0) return hipSuccess;
@@ -291,12 +314,17 @@ hipError_t launch_stage_meta(const InstDesc* d_descs, InstDyn* d_dyn, int n_inst
   return hipGetLastError();
 }
 
-hipError_t launch_stage(const InstDesc* d_descs, InstDyn* d_dyn, int n_inst, int max_K_alloc, int n_levels,
-                        int precision, int* d_err, hipStream_t s) {
+hipError_t launch_stage(const InstDesc* d_descs, InstDyn* d_dyn, int n_inst, int max_K_alloc, int max_L_pad,
+                        int n_levels, int precision, int* d_err, hipStream_t s) {
   if (n_inst <= 0) return hipSuccess;
   const hipError_t e = launch_stage_meta(d_descs, d_dyn, n_inst, n_levels, true, d_err, s);
   if (e != hipSuccess) return e;
-  const dim3 grid(max_K_alloc / 32, n_inst), block(512);
+  // antennas over workgroups until those are about two a compute unit: a single
+  // instance is otherwise the latency of a loop over its antennas (900 antennas, 24
+  // eigenpairs: 4.3 us in bf16, 12.2 in one workgroup), while each finds its columns'
+  // scales itself
+  const int64_t cols = (int64_t)(max_K_alloc / 32) * n_inst, parts = (max_L_pad + 127) / 128;
+  const dim3 grid(max_K_alloc / 32, n_inst, (unsigned)std::max<int64_t>(1, std::min(parts, 512 / cols))), block(512);
   switch (precision) {
     case 1: hipLaunchKernelGGL((stage_pack_kernel<__bf16, 2>), grid, block, 0, s, d_descs); break;
     case 2: hipLaunchKernelGGL((stage_pack_kernel<_Float16, 3>), grid, block, 0, s, d_descs); break;
