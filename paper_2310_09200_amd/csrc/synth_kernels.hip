@@ -497,6 +497,23 @@ __device__ __forceinline__ void mma3(f32x4 (&acc)[MR][NP], int n, const AFrag<H,
     }
 }
 
+// Sums over the wave's four rows of 16 lanes: row q gets that of v[q], as
+// (row 0 + row 1) + (row 2 + row 3).
+__device__ __forceinline__ float row_sums(const float (&v)[4]) {
+  float t[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {  // rows 0, 2 take the even value, rows 1, 3 the odd one
+    const auto x = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v[2 * i]),
+                                                    __builtin_bit_cast(unsigned, v[2 * i + 1]), false, false);
+    const unsigned a = x[0], b = x[1];  // a bit cast of a vector's element would take its first
+    t[i] = __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
+  }
+  const auto x = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, t[0]),
+                                                  __builtin_bit_cast(unsigned, t[1]), false, false);
+  const unsigned a = x[0], b = x[1];
+  return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
+}
+
 // MFMAs of one step.  NPL = 3: accumulators k1, k2, k3; NPL = 2: Er = Wr Br + Wi Bi, Ei = Wr Bi - Wi Br.
 template <class C, class H, int NPL, int NV>
 __device__ __forceinline__ void mma_step(f32x4 (&acc)[NPL][C::MR][C::NP], const AFrag<H, NV>& a,
@@ -708,28 +725,37 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void synth_fwd_kernel(const Fwd
               lv[r] = levs[k];
               ex[r] = wexp[k];
             }
+            // G pixel blocks together: weighted |E|^2 by level, a lane's rows summed in
+            // place, the four row groups of G NL sums by halving (row_sums)
+            constexpr int G = NP >= 4 ? 4 : 2, NL = 4 / G;
 #pragma unroll
-            for (int n = 0; n < NP; ++n) {
-              float e2[4];
+            for (int n0 = 0; n0 < NP; n0 += G) {
+              float e2[G][4];
 #pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                // fields (Er, Ei) of the accumulators, the columns' power-of-two scale undone
-                float er = NPL == 3 ? acc[0][m][n][r] - acc[NPL - 1][m][n][r] : acc[0][m][n][r];
-                float ei = NPL == 3 ? acc[0][m][n][r] + acc[1][m][n][r] : acc[1][m][n][r];
-                if (std::is_same<H, _Float16>::value) {
-                  er = ldexpf(er, ex[r]);
-                  ei = ldexpf(ei, ex[r]);
+              for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                  const int n = n0 + g;
+                  // fields (Er, Ei) of the accumulators, the columns' power-of-two scale undone
+                  float er = NPL == 3 ? acc[0][m][n][r] - acc[NPL - 1][m][n][r] : acc[0][m][n][r];
+                  float ei = NPL == 3 ? acc[0][m][n][r] + acc[1][m][n][r] : acc[1][m][n][r];
+                  if (std::is_same<H, _Float16>::value) {
+                    er = ldexpf(er, ex[r]);
+                    ei = ldexpf(ei, ex[r]);
+                  }
+                  e2[g][r] = w[r] * fmaf(er, er, ei * ei);
                 }
-                e2[r] = w[r] * fmaf(er, er, ei * ei);
-              }
-              // weighted |E|^2 into per-level partial sums
-              for (int l = lev_lo; l <= lev_hi; ++l) {
-                float sum = 0.0f;
+              for (int l = lev_lo; l <= lev_hi; l += NL) {
+                float sum[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) sum += (lv[r] == l) ? e2[r] : 0.0f;
-                sum += __shfl_xor(sum, 16);
-                sum += __shfl_xor(sum, 32);
-                if (lane < 16) part(wk, l, (pb0 + n) * 16 + lane) += sum;
+                for (int q = 0; q < 4; ++q) {
+                  sum[q] = 0.0f;
+#pragma unroll
+                  for (int r = 0; r < 4; ++r) sum[q] += (lv[r] == l + q / G) ? e2[q % G][r] : 0.0f;
+                }
+                const float t = row_sums(sum);
+                const int q = lane >> 4;  // this lane's sum: pixel block q % G, level l + q / G
+                if (NL == 1 || l + q / G <= lev_hi) part(wk, l + q / G, (pb0 + n0 + q % G) * 16 + (lane & 15)) += t;
               }
             }
           }
