@@ -194,6 +194,23 @@ __global__ __launch_bounds__(256) void stage_meta_kernel(const InstDesc* __restr
   if (tid == 0) dyn[blockIdx.x].fast_phase = near;
 }
 
+// f over the wave's four rows of 16 lanes: row q gets that of v[q], as
+// f(f(row 0, row 1), f(row 2, row 3)).
+template <class F>
+__device__ __forceinline__ float over_rows(const float (&v)[4], F f) {
+  auto swapped = [&](auto x) {
+    const unsigned a = x[0], b = x[1];  // a bit cast of a vector's element would take its first
+    return f(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
+  };
+  float t[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)  // rows 0, 2 take the even value, rows 1, 3 the odd one
+    t[i] = swapped(__builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v[2 * i]),
+                                                    __builtin_bit_cast(unsigned, v[2 * i + 1]), false, false));
+  return swapped(__builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, t[0]),
+                                                  __builtin_bit_cast(unsigned, t[1]), false, false));
+}
+
 // Component l of a column of W; T: its real type.
 template <class T>
 __device__ __forceinline__ void load_w(const InstDesc& D, int l, int col, float& wr, float& wi) {
@@ -226,63 +243,73 @@ __device__ __forceinline__ void stage_pack(const InstDesc& D, int* s_ex) {
     const int src = D.perm[k];
     return src < 0 ? -1 : (D.wcol ? D.wcol[src] : src);
   };
-  if (kScaled) {  // the columns' largest finite components, four of them a wave
-    const int c0 = (tid >> 6) * 4;
-    int col[4];
-    float m[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      col[c] = column(blockIdx.x * 32 + c0 + c);
-      m[c] = 0.0f;
-    }
-    for (int l0 = 0; l0 < D.L; l0 += 256) {  // a turn's reads in flight at once; past the end the last antenna again
-      float a[4][4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          float x, y;
-          load_w<T>(D, min(l0 + 64 * u + lane, D.L - 1), max(col[c], 0), x, y);
-          a[u][c] = fmaxf(fabsf(x), fabsf(y));
-        }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) m[c] = a[u][c] <= 3.4028235e38f ? fmaxf(m[c], a[u][c]) : m[c];
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      for (int o = 32; o > 0; o >>= 1) m[c] = fmaxf(m[c], __shfl_xor(m[c], o));
-      int ex = 0;
-      if (m[c] > 0.0f && col[c] >= 0) {
-        (void)frexpf(m[c], &ex);  // m < 2^ex
-        ex = 14 - ex;
-      }
-      if (lane == 0) s_ex[c0 + c] = ex;
-    }
-    __syncthreads();
-  }
   // wave = (16 eigenpairs, step); the eigenpair's row in its 16-block in the low four bits of the lane
   const int col32 = (tid & 15) + 16 * (tid >> 8);
   const int k = blockIdx.x * 32 + col32;
   const int col = column(k);
-  const int ex = kScaled ? s_ex[col32] : 0;
-  if (blockIdx.z == 0 && (tid & 0xf0) == 0) D.wexp[k] = -ex;
-  h8* const out = (h8*)D.apack + (int64_t)(k >> 4) * steps * NPL * 128;
-  for (int st = 4 * blockIdx.z + ((tid >> 6) & 3); st < steps; st += 4 * gridDim.z) {
-    h8 hi[NPL], lo[NPL];
+  float wr[8], wi[8];
+  auto load = [&](int st) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int l = 32 * st + 8 * (lane >> 4) + e;
-      float wr = 0.0f, wi = 0.0f;
-      if (col >= 0 && l < D.L) load_w<T>(D, l, col, wr, wi);
-      if (kScaled) {
-        wr = ldexpf(wr, ex);
-        wi = ldexpf(wi, ex);
-      }
+      wr[e] = wi[e] = 0.0f;
+      if (col >= 0 && l < D.L) load_w<T>(D, l, col, wr[e], wi[e]);
+    }
+  };
+  int st = 4 * blockIdx.z + ((tid >> 6) & 3);
+  load(st);  // in flight beside the reads of the scales
+  if (kScaled) {  // the columns' largest finite components, four of them a wave
+    const int c0 = (tid >> 6) * 4;
+    int col4[4];
+    float m[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      col4[c] = column(blockIdx.x * 32 + c0 + c);
+      m[c] = 0.0f;
+    }
+    auto turn = [&](auto n_c, int l0) {  // 64 n antennas, all reads in flight at once; past the end the last antenna again
+      constexpr int N = decltype(n_c)::value;
+      float a[N][4];
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          float x, y;
+          load_w<T>(D, min(l0 + 64 * u + lane, D.L - 1), max(col4[c], 0), x, y);
+          a[u][c] = fmaxf(fabsf(x), fabsf(y));
+        }
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) m[c] = a[u][c] <= 3.4028235e38f ? fmaxf(m[c], a[u][c]) : m[c];
+    };
+    if (D.L <= 64)
+      turn(std::integral_constant<int, 1>{}, 0);
+    else
+      for (int l0 = 0; l0 < D.L; l0 += 256) turn(std::integral_constant<int, 4>{}, l0);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) m[c] = col4[c] >= 0 ? m[c] : 0.0f;
+    float top = over_rows(m, [](float x, float y) { return fmaxf(x, y); });  // of column c0 + lane / 16
+    for (int o = 8; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+    int ex = 0;
+    if (top > 0.0f) {
+      (void)frexpf(top, &ex);  // top < 2^ex
+      ex = 14 - ex;
+    }
+    if ((lane & 15) == 0) s_ex[c0 + (lane >> 4)] = ex;
+    __syncthreads();
+  }
+  const int ex = kScaled ? s_ex[col32] : 0;
+  if (blockIdx.z == 0 && (tid & 0xf0) == 0) D.wexp[k] = -ex;
+  h8* const out = (h8*)D.apack + (int64_t)(k >> 4) * steps * NPL * 128;
+  while (st < steps) {
+    h8 hi[NPL], lo[NPL];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float r = kScaled ? ldexpf(wr[e], ex) : wr[e], i = kScaled ? ldexpf(wi[e], ex) : wi[e];
 #pragma unroll
       for (int q = 0; q < NPL; ++q) {
-        const float v = NPL == 2 ? (q == 0 ? wr : wi) : (q == 0 ? wr - wi : (q == 1 ? wr : -wi));
+        const float v = NPL == 2 ? (q == 0 ? r : i) : (q == 0 ? r - i : (q == 1 ? r : -i));
         const H vh = (H)v;
         hi[q][e] = vh;
         lo[q][e] = (H)(v - (float)vh);
@@ -293,6 +320,8 @@ __device__ __forceinline__ void stage_pack(const InstDesc& D, int* s_ex) {
       out[(st * NPL + q) * 128 + lane] = hi[q];
       out[(st * NPL + q) * 128 + 64 + lane] = lo[q];
     }
+    st += 4 * gridDim.z;
+    load(st);
   }
 }
 
@@ -495,23 +524,6 @@ __device__ __forceinline__ void mma3(f32x4 (&acc)[MR][NP], int n, const AFrag<H,
       const typename Mma<H>::h8 av = a.v[m][t == 0 ? 1 : 0];
       acc[m][n] = Mma<H>::op(NEG ? negated(av) : av, b[t == 1 ? 1 : 0], acc[m][n]);
     }
-}
-
-// Sums over the wave's four rows of 16 lanes: row q gets that of v[q], as
-// (row 0 + row 1) + (row 2 + row 3).
-__device__ __forceinline__ float row_sums(const float (&v)[4]) {
-  float t[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {  // rows 0, 2 take the even value, rows 1, 3 the odd one
-    const auto x = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v[2 * i]),
-                                                    __builtin_bit_cast(unsigned, v[2 * i + 1]), false, false);
-    const unsigned a = x[0], b = x[1];  // a bit cast of a vector's element would take its first
-    t[i] = __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
-  }
-  const auto x = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, t[0]),
-                                                  __builtin_bit_cast(unsigned, t[1]), false, false);
-  const unsigned a = x[0], b = x[1];
-  return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
 }
 
 // MFMAs of one step.  NPL = 3: accumulators k1, k2, k3; NPL = 2: Er = Wr Br + Wi Bi, Ei = Wr Bi - Wi Br.
@@ -726,7 +738,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void synth_fwd_kernel(const Fwd
               ex[r] = wexp[k];
             }
             // G pixel blocks together: weighted |E|^2 by level, a lane's rows summed in
-            // place, the four row groups of G NL sums by halving (row_sums)
+            // place, the four row groups of G NL sums by halving
             constexpr int G = NP >= 4 ? 4 : 2, NL = 4 / G;
 #pragma unroll
             for (int n0 = 0; n0 < NP; n0 += G) {
@@ -753,7 +765,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void synth_fwd_kernel(const Fwd
 #pragma unroll
                   for (int r = 0; r < 4; ++r) sum[q] += (lv[r] == l + q / G) ? e2[q % G][r] : 0.0f;
                 }
-                const float t = row_sums(sum);
+                const float t = over_rows(sum, [](float x, float y) { return x + y; });
                 const int q = lane >> 4;  // this lane's sum: pixel block q % G, level l + q / G
                 if (NL == 1 || l + q / G <= lev_hi) part(wk, l + q / G, (pb0 + n0 + q % G) * 16 + (lane & 15)) += t;
               }
