@@ -631,6 +631,12 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void synth_fwd_kernel(const Fwd
       __syncthreads();
       for (int64_t tile = blockIdx.x; tile < P.n_tiles; tile += gridDim.x) {
         const int64_t p0 = tile * C::NT;
+        // Where the registers allow it, the images are read before the last pass's
+        // epilogue: with a chunk or two per instance the latency of these reads is a
+        // tile's longest wait (29 antennas, 10 levels, 512^2 pixels: 70 us against 74).
+        constexpr bool kEarly = MR == 1 && C::OCC == 2;
+        constexpr int RP = kMaxLevels * C::NT / C::THREADS;
+        float was[RP];
         for (int pass = 0; pass < n_pass; ++pass) {
           const int b0 = pass * MR * WK + wk;  // this wave's first block; block m is b0 + m WK
           int nv = nkb > b0 ? (nkb - b0 + WK - 1) / WK : 0;
@@ -722,6 +728,13 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void synth_fwd_kernel(const Fwd
             by_form(std::integral_constant<int, 0>{});
           static_assert(MR <= 2, "block counts covered above");
 
+          if (kEarly && pass == n_pass - 1) {
+#pragma unroll
+            for (int r = 0; r < RP; ++r) {
+              const int i = tid + r * C::THREADS, l = i / C::NT, pl = i % C::NT;
+              if (l < n_levels && p0 + pl < P.n_pix) was[r] = P.img[((int64_t)slot * n_levels + l) * P.img_ld + p0 + pl];
+            }
+          }
 #pragma unroll
           for (int m = 0; m < MR; ++m) {
             if (m >= nv) continue;
@@ -774,9 +787,8 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void synth_fwd_kernel(const Fwd
         }
         // sum over the waves in a fixed order; the partials are cleared for the next tile
         __syncthreads();
-        for (int i = tid; i < n_levels * C::NT; i += C::THREADS) {
+        auto finish = [&](int i, float& was_i) {
           const int l = i / C::NT, pl = i % C::NT;
-          const int64_t p = p0 + pl;
           float sum = 0.0f;
 #pragma unroll
           for (int q = 0; q < WK; ++q) {
@@ -784,10 +796,17 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void synth_fwd_kernel(const Fwd
             sum += x;
             x = 0.0f;
           }
-          if (p < P.n_pix) {
-            float* dst = P.img + ((int64_t)slot * n_levels + l) * P.img_ld + p;
-            *dst += sum;
+          if (p0 + pl < P.n_pix) {
+            float* const dst = P.img + ((int64_t)slot * n_levels + l) * P.img_ld + p0 + pl;
+            *dst = (kEarly ? was_i : *dst) + sum;
           }
+        };
+        if constexpr (kEarly) {
+#pragma unroll
+          for (int r = 0; r < RP; ++r)
+            if (tid + r * C::THREADS < n_levels * C::NT) finish(tid + r * C::THREADS, was[r]);
+        } else {
+          for (int i = tid; i < n_levels * C::NT; i += C::THREADS) finish(i, was[0]);
         }
       }
     }
@@ -900,8 +919,9 @@ struct Cands<3> {
   static constexpr int dflt[4] = {3, 2, 1, 0};
 };
 
-// The shape that takes a tile's place for an image with fewer tiles than
-// compute units: half the pixels, the same eigenpairs per pass.
+// The shape of half the pixels and the same eigenpairs per pass that takes a
+// tile's place where the image leaves the last round of tiles nearly empty, or has
+// fewer of them than compute units (launch_shape).
 template <class C>
 struct Narrow {
   using T = C;
@@ -927,8 +947,10 @@ struct Narrow<Tile<1, 2, 4, 4, 4>> {
 // memory (antenna positions, level partials) leaves a CU fewer workgroups than the
 // registers do: more waves a workgroup (391 antennas, 36 eigenpairs, 12 levels,
 // 1680^2 pixels, 3 epochs in bf16: 5.3 ms against 7.3), or more registers a wave
-// (29 antennas, 18 eigenpairs, 10 levels: 236 us against 243).  The sixteen waves of
-// 128 x 128 need more than a CU holds (512 antennas from 13 levels, 1024 from 9).
+// (29 antennas, 18 eigenpairs, 10 levels: 236 us against 243; 900 antennas, 40
+// eigenpairs, 314^2 pixels, 10 epochs in fp32_3m: 1.39 ms against 1.67).  The
+// sixteen waves of 128 x 128 need more than a CU holds (512 antennas from 13
+// levels, 1024 from 9).
 template <class C>
 struct Roomy {
   using T = C;
@@ -942,30 +964,83 @@ struct Roomy<Tile<1, 2, 2, 2, 3>> {
   using T = Tile<1, 2, 2, 2, 2>;
 };
 template <>
+struct Roomy<Tile<1, 2, 4, 2, 4>> {
+  using T = Tile<2, 2, 2, 2>;
+};
+template <>
 struct Roomy<Tile<1, 4, 8, 2, 4>> {
   using T = Tile<2, 4, 4, 2>;
 };
 
+// Of those, the shape of twice the pixels in eight waves that is better still in
+// the three-product form, whose chunks leave a CU eight waves of either: each row of
+// W is read once per 128 pixels (900 antennas, 24 eigenpairs, 512^2 pixels in bf16:
+// 323 us against 340), unless its tiles fill the rounds worse.
+template <class C>
+struct Wide {
+  using T = C;
+};
+template <>
+struct Wide<Tile<1, 2, 2, 2, 3>> {
+  using T = Tile<1, 2, 2, 4>;
+};
+
+template <class C>
+static int64_t tiles_of(int64_t n_pix) {
+  return (n_pix + C::NT - 1) / C::NT;
+}
+// Pixels that the busiest compute unit takes.
+template <class C>
+static int64_t cu_pixels(int64_t n_pix) {
+  const int64_t n = std::max(compute_units(), 1);
+  return (tiles_of<C>(n_pix) + n - 1) / n * C::NT;
+}
+template <class C, int NPL>
+static int by_lds(const FwdParams& p) {  // workgroups of a CU's local memory
+  return (int)(kMaxLds / C::lds_bytes(NPL, p.max_L_pad, p.n_levels));
+}
+template <class C>
+constexpr int kByRegs = std::max(1, 4 * C::OCC / C::WAVES);  // ... and of its registers
+
 template <class C, class H, int NPL>
-static hipError_t launch_shape(FwdParams p, hipStream_t s) {
+static hipError_t launch_fitting(FwdParams p, hipStream_t s) {
   using R = typename Roomy<C>::T;
+  using W = typename Wide<C>::T;
   static_assert(R::NT == C::NT && R::KC == C::KC, "the same rows and pixels");
   static_assert(R::lds_bytes(NPL, kMaxAnt, kMaxLevels) <= kMaxLds, "a listed shape runs every instance");
   if constexpr (!std::is_same<R, C>::value) {
-    if (kMaxLds / C::lds_bytes(NPL, p.max_L_pad, p.n_levels) < (size_t)(4 * C::OCC / C::WAVES))
+    // (fewer waves help only where a second workgroup has a tile)
+    const int fit = by_lds<C, NPL>(p);
+    if (fit < kByRegs<C> && (fit == 0 || R::WAVES >= C::WAVES || p.n_tiles > compute_units())) {
+      if constexpr (NPL == 3 && !std::is_same<W, C>::value) {
+        static_assert(W::lds_bytes(NPL, kMaxAnt, kMaxLevels) <= kMaxLds, "and so does its wide form");
+        if (cu_pixels<W>(p.n_pix) <= cu_pixels<C>(p.n_pix)) {
+          p.n_tiles = tiles_of<W>(p.n_pix);
+          return launch_cfg<W, H, NPL>(p, s);
+        }
+      }
       return launch_cfg<R, H, NPL>(p, s);
-  }
-  using N = typename Narrow<C>::T;
-  if constexpr (!std::is_same<N, C>::value) {
-    static_assert(N::lds_bytes(NPL, kMaxAnt, kMaxLevels) <= kMaxLds, "and so does its narrow form");
-    // only where its tiles still run all at once
-    const int64_t n = (p.n_pix + N::NT - 1) / N::NT;
-    if (p.n_tiles < compute_units() && n <= (int64_t)compute_units() * std::max(1, 4 * N::OCC / N::WAVES)) {
-      p.n_tiles = n;
-      return launch_cfg<N, H, NPL>(p, s);
     }
   }
   return launch_cfg<C, H, NPL>(p, s);
+}
+
+template <class C, class H, int NPL>
+static hipError_t launch_shape(FwdParams p, hipStream_t s) {
+  using N = typename Narrow<C>::T;
+  if constexpr (!std::is_same<N, C>::value) {
+    // Compute units work through their tiles at one rate, whether one workgroup at a
+    // time or two, so that the launch takes what the busiest one does: 200^2 pixels are
+    // 313 tiles of 128, two on some of 256 units, or 625 of 64, three (391 antennas, 100
+    // eigenpairs in bf16: 81 us against 95).  A tenth is what the narrow form loses
+    // where both are even, but with fewer tiles than units (300 antennas, 200
+    // eigenpairs, 150^2 pixels in bf16: 78 us against 84).
+    if (p.n_tiles < compute_units() || 10 * cu_pixels<N>(p.n_pix) <= 9 * cu_pixels<C>(p.n_pix)) {
+      p.n_tiles = tiles_of<N>(p.n_pix);
+      return launch_fitting<N, H, NPL>(p, s);
+    }
+  }
+  return launch_fitting<C, H, NPL>(p, s);
 }
 
 template <int I, class F, class T0, class... Ts>
