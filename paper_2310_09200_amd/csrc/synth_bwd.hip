@@ -47,12 +47,14 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
   return t;
 }
 
-// M = d c conj(E) in place, dd partial sums, and the largest |Re M|, |Im M| of the
-// split; grid (K_alloc, n_split), 256 threads.
+// M = d c conj(E) in place, dd partial sums, and the largest finite |Re M|, |Im M| of
+// the split, negative (at least the smallest normal number) where some are infinite;
+// grid (K_alloc, n_split), 256 threads.
 __global__ __launch_bounds__(256) void bwd_m_kernel(const BwdParams P) {
   __shared__ double sh[4];
   __shared__ float shm[4];
   float top = 0.0f;
+  bool wild = false;
   const int k = blockIdx.x;
   const int s = blockIdx.y;
   const InstDesc& D = *P.desc;
@@ -78,15 +80,19 @@ __global__ __launch_bounds__(256) void bwd_m_kernel(const BwdParams P) {
       const float mr = w * c * a, mi = -w * c * b;
       er[p] = mr;
       ei[p] = mi;
-      top = fmaxf(top, fmaxf(fabsf(mr), fabsf(mi)));
+      const float ar = fabsf(mr), ai = fabsf(mi);
+      top = fmaxf(top, fmaxf(ar < INFINITY ? ar : 0.0f, ai < INFINITY ? ai : 0.0f));
+      wild = wild || ar == INFINITY || ai == INFINITY;
     }
   }
   for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
   if ((threadIdx.x & 63) == 0) shm[threadIdx.x >> 6] = top;
+  wild = __syncthreads_or(wild);
   const double t = block_sum<256>(acc, sh);
   if (threadIdx.x == 0) {
     P.dd_part[(int64_t)k * P.n_split + s] = t;
-    P.m_top[(int64_t)k * P.n_split + s] = fmaxf(fmaxf(shm[0], shm[1]), fmaxf(shm[2], shm[3]));
+    top = fmaxf(fmaxf(shm[0], shm[1]), fmaxf(shm[2], shm[3]));
+    P.m_top[(int64_t)k * P.n_split + s] = wild ? -fmaxf(top, 0x1p-126f) : top;
   }
 }
 
@@ -174,6 +180,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dw_kernel(const BwdParams P) {
   __shared__ double sP[2][3][64];
   __shared__ double sX[128][4];
   __shared__ int sE[K];  // exponent of each eigenpair's scale
+  __shared__ int sWild[K];  // whether it has infinite values
   const InstDesc& D = *P.desc;
   const int l0 = blockIdx.x * 128, k0 = blockIdx.y * K, s = blockIdx.z;
   const int t = threadIdx.x, lane = t & 63, r16 = lane & 15, kq = lane >> 4;
@@ -184,12 +191,23 @@ __global__ __launch_bounds__(512, 2) void bwd_dw_kernel(const BwdParams P) {
     constexpr int TP = 512 / K;
     const int k = t / TP;
     float top = 0.0f;
+    int wild = 0;
     if (k0 + k < P.K_alloc)
-      for (int i = t % TP; i < P.n_split; i += TP) top = fmaxf(top, P.m_top[(int64_t)(k0 + k) * P.n_split + i]);
-    for (int o = TP / 2; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+      for (int i = t % TP; i < P.n_split; i += TP) {
+        const float m = P.m_top[(int64_t)(k0 + k) * P.n_split + i];
+        top = fmaxf(top, fabsf(m));
+        wild |= m < 0.0f;
+      }
+    for (int o = TP / 2; o > 0; o >>= 1) {
+      top = fmaxf(top, __shfl_xor(top, o));
+      wild |= __shfl_xor(wild, o);
+    }
     // 2^-e top in [2^13, 2^14); within the range of a normal factor 2^-e
-    int e = top > 0.0f && top < INFINITY ? ilogbf(top) - 13 : 0;
-    if (t % TP == 0) sE[k] = max(-120, min(120, e));
+    const int e = top > 0.0f ? ilogbf(top) - 13 : 0;
+    if (t % TP == 0) {
+      sE[k] = max(-120, min(120, e));
+      sWild[k] = wild;
+    }
   }
   __syncthreads();
   const int64_t p0 = (int64_t)s * P.dw_len;
@@ -197,8 +215,12 @@ __global__ __launch_bounds__(512, 2) void bwd_dw_kernel(const BwdParams P) {
   // M rows kr + 32 q, pixels 4 px .. + 3 of a chunk
   const int px = t & 15, kr = t >> 4;
   float scale[Q];
+  unsigned wild = 0;  // bit q: row q has infinite values
 #pragma unroll
-  for (int q = 0; q < Q; ++q) scale[q] = __int_as_float((127 - sE[kr + 32 * q]) << 23);
+  for (int q = 0; q < Q; ++q) {
+    scale[q] = __int_as_float((127 - sE[kr + 32 * q]) << 23);
+    wild |= (unsigned)sWild[kr + 32 * q] << q;
+  }
   // rows q0 .. q0 + Q / 2 - 1, real and imaginary parts, of the chunk at pc
   constexpr int QH = Q / 2;
   bwd_f32x4 next[2][QH];
@@ -233,6 +255,13 @@ __global__ __launch_bounds__(512, 2) void bwd_dw_kernel(const BwdParams P) {
         uint2 hi, lo;
         split2<_Float16>(v[0], v[1], hi.x, lo.x);
         split2<_Float16>(v[2], v[3], hi.y, lo.y);
+        if (wild >> (q0 + q) & 1) {  // infinite values are low words alone: their products are infinite, not NaN
+          uint16_t* const h = reinterpret_cast<uint16_t*>(&hi);
+          uint16_t* const l = reinterpret_cast<uint16_t*>(&lo);
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (fabsf(v[i]) == INFINITY) l[i] = h[i], h[i] = 0;
+        }
         // [half = px / 8][k][8 words of 8 bytes]
         const int at = ((px >> 3) * K + kr + 32 * (q0 + q)) * 8 + (px & 7);
         dst[2 * (2 * c) * PLANE + at] = hi;

@@ -310,7 +310,8 @@ __device__ __forceinline__ void stage_pack(const InstDesc& D, int* s_ex) {
 #pragma unroll
       for (int q = 0; q < NPL; ++q) {
         const float v = NPL == 2 ? (q == 0 ? r : i) : (q == 0 ? r - i : (q == 1 ? r : -i));
-        const H vh = (H)v;
+        // an infinite component is a low word alone: its products are infinite, not NaN
+        const H vh = kScaled && fabsf(v) == INFINITY ? (H)0.0f : (H)v;
         hi[q][e] = vh;
         lo[q][e] = (H)(v - (float)vh);
       }
