@@ -74,8 +74,9 @@ typedef enum {
  * accumulators in every mode).  Every operand value is split into two 16-bit
  * words, hi + lo, and a real product is hi*hi + hi*lo + lo*hi on 16-bit MFMAs:
  * fp16 words in the FP32 modes (22 bits, the eigenvectors scaled by powers of
- * two; images at least as close to 64 bits as with FP32 MFMAs), bf16 words in
- * the BF16 modes (16 bits).
+ * two; images at least as close to 64 bits as with FP32 MFMAs, but for the
+ * three-product form of fewer than 12 antennas: up to 18 % farther), bf16 words
+ * in the BF16 modes (16 bits).
  *  BB_PREC_FP32     four real products per complex product
  *  BB_PREC_BF16X3   four real products, BF16 words
  *  BB_PREC_FP32_3M  three real products per complex product (Gauss):

@@ -323,7 +323,7 @@ __global__ __launch_bounds__(T) void line_fft_kernel(LineFft p, const float2* __
 // many instructions as the butterflies (360 us).
 //
 // 32 k lines of 3200 or 3240 points, half of them stored and half kept (0.83 GB,
-// 0.17 ms): 250 us, the vector units 70 % busy; 440 and 540 us in line_fft_kernel
+// 0.17 ms): 250 us, the vector units 70 to 74 % busy; 440 and 540 us in line_fft_kernel
 // (six or seven passes through LDS with bank conflicts in the early ones).  A
 // workgroup takes one set of lines: as a loop over lines with the twiddles kept
 // (in LDS or registers) fewer workgroups fit a CU and it took 500 us.

@@ -14,8 +14,10 @@
 // running sum: against 64 bits the images are closer than with FP32 MFMAs
 // (relative error of all levels, measured: 512 antennas x 512 eigenpairs
 // 1.0e-7 against 1.2e-7 in the three-product form and 3.2e-7 against 5.0e-7 in
-// the four-product form at 65 km; 64 x 64 1.2e-7 against 1.7e-7), at 2.7 times
-// the products per second of the FP32 matrix rate.  With bf16 words (the BF16
+// the four-product form at 65 km; 64 x 64 1.2e-7 against 1.7e-7; with fewer than
+// 12 antennas there is little to save, and the three-product form is 3 to 18 %
+// farther, 1.2e-7 to 1.5e-7), at 2.7 times the products per second of the FP32
+// matrix rate.  With bf16 words (the BF16
 // modes) hi + lo holds 16 bits.
 //
 // The complex product takes four real products (planes Wr, Wi and Br, Bi) or,
@@ -42,8 +44,8 @@
 // MFMA), and 1.39 with the W loads, LDS reads and phase instructions of this
 // kernel beside them; a large fp16 matrix product of the vendor library
 // reaches 1.12.  512 antennas x 512 eigenpairs x 1024^2 pixels x 16 epochs:
-// 66.3 ms in the three-product form (1.19 PFLOP/s, 6.6e13 products/s) against
-// 197.8 ms on FP32 MFMAs (85 % of their peak).
+// 64.7 ms in the three-product form (1.22 PFLOP/s, 6.8e13 products/s; 67.0 on
+// another card) against 197.6 ms on FP32 MFMAs (85 % of their peak).
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
